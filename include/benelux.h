@@ -212,9 +212,9 @@ typedef struct {
   uint64_t joined;            /* entries the join kernels read (equals entries)   */
   uint64_t false_candidates;  /* candidates whose sets differ (dropped by verify) */
   uint32_t l2_entry_bytes;    /* bytes per second-level entry: 8 (compact words) or 12 */
-  uint32_t word_matches;      /* compact words whose kept bits met (each pair read back
-                                 from the first level; candidates are those of them
-                                 with equal whole fingerprints and queries)        */
+  uint32_t word_matches;      /* compact words whose kept bits met (candidates are
+                                 those of them with equal whole fingerprints and
+                                 queries)                                          */
 } bx_stats;
 int bx_get_stats(bx_ctx* ctx, bx_stats* out);
 
@@ -225,7 +225,8 @@ int bx_get_stats(bx_ctx* ctx, bx_stats* out);
  *   "b1_bits"      force the first partition fan-out (0 = plan)
  *   "b2_bits"      force the second partition fan-out, <= 11 (0 = plan)
  *   "group"        first-level buckets per second-level launch (1, 2, 4, 8; 0 = 8)
- *   "tile"         sieve LDS tile: 2048 (two workgroups per CU) or 8192 (one; 0 = 8192)
+ *   "tile"         the radical sieve's LDS tile: 2048 or 8192 (0 = 8192); the
+ *                  searches' sieve has one shape
  *   "graph"        1 = batched calls run as one captured HIP graph (default 1)
  *   "fp_bits"      for tests of the verification: keep only the top 11 and
  *                  the low fp_bits bits of the 53-bit fingerprints (v in
@@ -253,13 +254,11 @@ int bx_get_stats(bx_ctx* ctx, bx_stats* out);
  *   "submit_wait"  serving: 1 = bx_submit queues (default), 0 = bx_submit
  *                  refuses with BX_EBUSY what cannot be admitted at once
  *   "compact"      the second partition level stores 8-byte words (the
- *                  entry's index among its first-level bucket's regions and
- *                  the low fingerprint bits; the partition index stands for
- *                  the top bits) instead of 12-byte entries where the plan
- *                  allows it: full fingerprints, hash join, and at most 3e5
- *                  expected random matches of the kept bits (the join reads
- *                  both entries of a match back from the first level).
- *                  0 = never, 1 = where the plan allows (default)
+ *                  integer's index in its sieve workgroup's sequence, the
+ *                  workgroup, and the low fingerprint bits; the partition
+ *                  index stands for the top bits) instead of 12-byte entries
+ *                  where the plan allows it: full fingerprints and the hash
+ *                  join.  0 = never, 1 = where the plan allows (default)
  *   "compact_fp_bits" for tests of the compact join: keep only this many low
  *                  fingerprint bits in a compact word (12 .. 40; 0 = all the
  *                  word holds), so that different sets meet

@@ -24,6 +24,7 @@
 #include "bx_alg2.h"
 #include "bx_alg3.h"
 #include "bx_kernels.h"
+#include "bx_keysieve.h"
 #include "bx_small.h"
 
 using namespace bx;
@@ -114,6 +115,10 @@ struct bx_ctx {
   uint32_t* d_primes = nullptr;
   PrimeInv* d_pinv = nullptr;  // per prime: p^-1 mod 2^64 and floor((2^64 - 1) / p) (divisibility tests)
   PrimePow* d_pp = nullptr;
+  // The key sieve's tables: static slots of the powers up to kMidMax, and the powers above.
+  MidSlot* d_mid = nullptr;
+  SparsePow* d_sp = nullptr;
+  uint32_t* d_sp_p = nullptr;
   DenseTab* d_dense[2] = {nullptr, nullptr};
   DevBuf l1, l2, cnt1, cnt2, cand, out, flags, spill, queries, segpref, rad, acc, a3tab, smallq;
   DevBuf a2k[2], a2v[2], a2hist, a2offs, a2tot;  // Algorithm 2: list (double-buffered), sort counts
@@ -308,6 +313,36 @@ int build_tables(bx_ctx* c) {
     BX_HIP(hipMalloc(&c->d_dense[which], sizeof(DenseTab)));
     BX_HIP(hipMemcpy(c->d_dense[which], &dt, sizeof(DenseTab), hipMemcpyHostToDevice));
   }
+  {
+    // 1/q a little low: ceil(S * invq) is then exact for every S < 2^42.
+    auto inv = [](double q) { return 1.0 / q * (1.0 - std::ldexp(1.0, -46)); };
+    std::vector<MidSlot> mid;
+    std::vector<SparsePow> sp;
+    std::vector<uint32_t> sp_p;
+    for (const auto& w : c->pp) {
+      const double q = static_cast<double>(w.q);
+      if (w.q <= kFixedQMax || w.q == 729) continue;  // the subtile's own slots
+      if (w.q <= kMidMax) {
+        for (uint64_t jq = 0; jq <= kKeyLen; jq += w.q) mid.push_back(MidSlot{q, inv(q), static_cast<uint32_t>(jq), w.p});
+      } else {
+        sp.push_back(SparsePow{q, inv(q)});
+        sp_p.push_back(w.p);
+      }
+    }
+    std::sort(mid.begin(), mid.end(), [](const MidSlot& a, const MidSlot& b) { return a.jq < b.jq; });
+    if (mid.size() > static_cast<size_t>(kMidPer) * kKeyBlock) return fail(BX_EINTERNAL, "mid slot table overflow");
+    // The sieve reads rounds of 4 * kKeyBlock powers until one starts past its range.
+    sp.resize(sp.size() + 8 * kKeyBlock, SparsePow{HUGE_VAL, 0.0});
+    sp_p.resize(sp.size(), 0);
+    // The rest of the slots lie past any block: q = 1 gives offset 0.
+    mid.resize(static_cast<size_t>(kMidPer) * kKeyBlock, MidSlot{1.0, inv(1.0), 1u << 31, 1});
+    BX_HIP(hipMalloc(&c->d_mid, mid.size() * sizeof(MidSlot)));
+    BX_HIP(hipMalloc(&c->d_sp, sp.size() * sizeof(SparsePow)));
+    BX_HIP(hipMalloc(&c->d_sp_p, sp_p.size() * sizeof(uint32_t)));
+    BX_HIP(hipMemcpy(c->d_mid, mid.data(), mid.size() * sizeof(MidSlot), hipMemcpyHostToDevice));
+    BX_HIP(hipMemcpy(c->d_sp, sp.data(), sp.size() * sizeof(SparsePow), hipMemcpyHostToDevice));
+    BX_HIP(hipMemcpy(c->d_sp_p, sp_p.data(), sp_p.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+  }
   BX_HIP(hipMalloc(&c->d_primes, std::max<size_t>(4, c->primes.size() * sizeof(uint32_t))));
   {
     // x is a multiple of odd p iff x * p^-1 mod 2^64 <= floor((2^64 - 1) / p)
@@ -339,27 +374,26 @@ uint32_t ceil_log2(double v) {
 
 uint64_t round_up(uint64_t v, uint64_t m) { return (v + m - 1) / m * m; }
 
-// Sparse hits per workgroup beyond the sieve's LDS list (worst case).
+// Sparse hits per workgroup beyond the radical sieve's LDS list (worst case).
 uint32_t spill_cap_of(const bx_ctx* c) {
   return static_cast<uint32_t>(c->pp.size() - c->n_dense[0] + c->seg_len / 128 + 64);
 }
 
-uint64_t fixed_bytes(const bx_ctx* c, uint32_t sieve_grid) {
-  return static_cast<uint64_t>(sieve_grid) * spill_cap_of(c) * 8ull + kCandCap * (sizeof(Cand) + sizeof(OutPair)) +
+uint64_t fixed_bytes(uint32_t sieve_grid) {
+  return static_cast<uint64_t>(sieve_grid) * kKeySpill * 8ull + kCandCap * (sizeof(Cand) + sizeof(OutPair)) +
          (64ull << 20);
 }
 
 // Choose the number of hash passes P (any integer: pass p keeps the keys whose
 // pass hash falls in the p-th of P equal ranges) and the two partition
-// fan-outs.  One pass's entries live in the first-level buckets (12 B each);
+// fan-outs.  One pass's words live in the first-level buckets (8 B each);
 // the second level only needs a buffer for one group of buckets at a time, so
 // the budget sets P through the first level alone.  Second-level partitions
 // end up near 3800-7600 entries, which one workgroup joins in LDS.
 int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uint32_t sieve_grid, Plan* out) {
-  const uint64_t fixed = fixed_bytes(c, sieve_grid);
+  const uint64_t fixed = fixed_bytes(sieve_grid);
   const uint32_t p_first = c->force_passes > 0 ? static_cast<uint32_t>(c->force_passes) : 1;
   const uint32_t p_last = c->force_passes > 0 ? p_first : 4096;
-  const double W = static_cast<double>(sieve_grid);
   for (uint32_t P = p_first; P <= p_last; ++P) {
     Plan p;
     p.passes = P;
@@ -378,7 +412,6 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
     // that workgroup's integers of the bucket and pass, plus slack.
     const double region = static_cast<double>(share) / P / std::ldexp(1.0, static_cast<int>(b1));
     p.cap1 = round_up(static_cast<uint64_t>(std::ceil(region * 1.05)) + 256, 64);
-    (void)W;
     // Partitions of at most ~7.6k entries on average: with the bucket-to-bucket
     // spread (3%) and the partition-to-partition spread (a few sigma of ~90)
     // they stay within one LDS join chunk (8192 entries).
@@ -396,7 +429,7 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
     uint32_t G = c->force_group > 0 ? static_cast<uint32_t>(c->force_group) : 8u;
     if (G > nb1) G = static_cast<uint32_t>(nb1);
     p.group = G;
-    p.bytes = nb1 * sieve_grid * p.cap1 * sizeof(Entry) + G * nb2 * p.cap2 * sizeof(Entry) +
+    p.bytes = nb1 * sieve_grid * p.cap1 * sizeof(uint64_t) + G * nb2 * p.cap2 * sizeof(Entry) +
               (nb1 * sieve_grid + G * nb2) * 4;
     if (p.bytes + fixed <= c->budget) {
       *out = p;
@@ -653,15 +686,15 @@ int check_query(const bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds) {
   return BX_OK;
 }
 
-template <int MODE>
+// The radical sieve.
 void launch_sieve(const bx_ctx* c, const SieveParams& P, uint32_t grid, hipStream_t st) {
   if (c->tile == kTileLarge)
-    hipLaunchKernelGGL((k_sieve<kTileLarge, 1024, MODE>), dim3(grid), dim3(1024), 0, st, P);
+    hipLaunchKernelGGL((k_sieve<kTileLarge, 1024>), dim3(grid), dim3(1024), 0, st, P);
   else
-    hipLaunchKernelGGL((k_sieve<kTileSmall, 512, MODE>), dim3(grid), dim3(512), 0, st, P);
+    hipLaunchKernelGGL((k_sieve<kTileSmall, 512>), dim3(grid), dim3(512), 0, st, P);
 }
 
-// Sieve workgroups per CU for the key-generating sieve (LDS bound).
+// Radical-sieve workgroups per CU (LDS bound).
 uint32_t sieve_wg_per_cu(const bx_ctx* c) { return c->tile == kTileLarge ? 1u : 2u; }
 
 // One search: plan, buffers and launch shapes.
@@ -673,17 +706,16 @@ struct Job {
   uint32_t sieve_grid = 0, B1 = 1, B2 = 1, G = 1, cpr = 1;
   uint64_t ngsub = 1, n_regions = 1, part_grid = 8;
   uint32_t gmask = 0;
-  // Compact second level (8-byte words): the entry's index among its bucket's
-  // first-level regions, the low fingerprint bits above it.
+  // First-level words: index bits and fingerprint bits above them (l1_word).
+  uint32_t li_bits = 0;
+  uint64_t kl_mask = 0;
+  // Compact second level (8-byte words): index and region, and the low
+  // fingerprint bits above them.
   bool compact = false;
-  uint32_t idx_bits = 0;
+  uint32_t wl_bits = 0;
   uint64_t low_mask = 0;
+  uint64_t cand_fp_mask = 0;  // fingerprint bits the candidates' entries hold
 };
-
-// Random matches of kept word bits a compact plan expects (pairs of different
-// sets whose kept fingerprint bits, bucket and partition agree; the join reads
-// both entries of each back from the first level), at most this many per call.
-constexpr double kCompactMatchMax = 3e5;
 
 // Bytes of every workspace buffer a job needs.
 struct JobBufs {
@@ -697,8 +729,7 @@ int plan_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, Job* j, JobBufs* nb)
   j->s = &s;
   j->batch = batch;
   j->kinds = kinds;
-  j->sieve_grid =
-      static_cast<uint32_t>(std::min<uint64_t>(s.n_segs, static_cast<uint64_t>(c->n_cu) * sieve_wg_per_cu(c)));
+  j->sieve_grid = static_cast<uint32_t>(std::min<uint64_t>(s.n_segs, static_cast<uint64_t>(c->n_cu)));
   if ((rc = make_plan(c, s.n_keys, s.n_expect, max_share(c, s, j->sieve_grid), j->sieve_grid, &j->plan)) != BX_OK)
     return rc;
   const Plan& plan = j->plan;
@@ -715,22 +746,27 @@ int plan_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, Job* j, JobBufs* nb)
   j->part_grid = 8ull * std::min<uint64_t>(std::max(1, c->n_cu / 8), (chunks + per - 1) / per);
   if (j->part_grid > 0x7FFFFFFFull) return fail(BX_EINTERNAL, "partition grid too large");
   j->gmask = batch ? kGrpMask : 0u;
-  nb->l1 = j->n_regions * plan.cap1 * sizeof(Entry);
-  // Compact words need the full fingerprint (no test mask), the hash join, and
-  // enough kept bits that random matches stay few.
+  nb->l1 = j->n_regions * plan.cap1 * sizeof(uint64_t);
   {
-    const uint64_t per_bucket = static_cast<uint64_t>(j->sieve_grid) * plan.cap1;  // first-level slots of a bucket
-    uint32_t ib = 1;
-    while (ib < 64 && (1ull << ib) < per_bucket) ++ib;
-    j->idx_bits = ib;
-    const uint32_t f2 = std::min<uint32_t>(kFpBits, 64 - ib);
-    const uint32_t keep = c->compact_fp_bits ? std::min(f2, c->compact_fp_bits) : f2;
-    const double per_pass = static_cast<double>(s.n_expect) / plan.passes;
-    const double match_est =
-        plan.passes * per_pass * per_pass / 2.0 / std::ldexp(1.0, static_cast<int>(keep + plan.b1bits + plan.b2bits));
-    j->compact = c->compact && c->fp_mask == (1ull << kFpBits) - 1 && !c->join_sort && f2 >= 24 &&
-                 (c->compact_fp_bits || match_est <= kCompactMatchMax);
-    if (j->compact) j->low_mask = (1ull << keep) - 1;
+    auto bits_of = [](uint64_t v) {  // the least b with v < 2^b
+      uint32_t b = 0;
+      while (b < 64 && (v >> b)) ++b;
+      return b;
+    };
+    // Indices run up to segments per workgroup * seg_len - 1; the bit length
+    // of that product keeps the all-ones index free.
+    const uint64_t W = std::max<uint64_t>(1, j->sieve_grid);
+    j->li_bits = std::max(1u, bits_of((s.n_segs + W - 1) / W * c->seg_len));
+    const uint32_t kl = std::min<uint32_t>(42, 53 - j->li_bits);  // li_bits <= 43: x < 2^42
+    j->kl_mask = (1ull << kl) - 1;
+    j->wl_bits = j->li_bits + bits_of(W - 1);
+    uint32_t keep = std::min(kl, 64 - j->wl_bits);
+    if (c->compact_fp_bits) keep = std::min(keep, c->compact_fp_bits);
+    j->low_mask = (1ull << keep) - 1;
+    // Compact words need the full fingerprint (no test mask) and the hash join.
+    j->compact = c->compact && c->fp_mask == (1ull << kFpBits) - 1 && !c->join_sort;
+    j->cand_fp_mask = j->compact ? j->low_mask : c->fp_mask & (j->kl_mask | (0x7FFull << 42));
+    if (s.n_segs == 0) j->cand_fp_mask = c->fp_mask;  // small-class queries only: whole fingerprints
   }
   nb->l2 = j->ngsub * plan.cap2 * (j->compact ? sizeof(uint64_t) : sizeof(Entry));
   nb->cnt1 = j->n_regions * 4ull;
@@ -739,7 +775,7 @@ int plan_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, Job* j, JobBufs* nb)
   nb->out = kCandCap * sizeof(OutPair);
   nb->flags = kFlagCount * 4;
   nb->acc = kAccCount * sizeof(unsigned long long);
-  nb->spill = static_cast<size_t>(j->sieve_grid) * spill_cap_of(c) * 8;
+  nb->spill = static_cast<size_t>(j->sieve_grid) * kKeySpill * 8;
   nb->queries = s.q.size() * sizeof(Query);
   nb->segpref = s.prefix.size() * sizeof(uint64_t);
   nb->smallq = s.small.size() * sizeof(uint32_t);
@@ -800,27 +836,47 @@ int enqueue_init(bx_ctx* c, const Job& j, hipStream_t st) {
 int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStream_t st) {
   const Plan& plan = j.plan;
   uint32_t* d_flags = static_cast<uint32_t*>(c->flags.p);
-  SieveParams P = base_sieve_params(c, *j.s);
+  KeyParams P;
+  P.queries = static_cast<const Query*>(c->queries.p);
+  P.seg_prefix = static_cast<const uint64_t*>(c->segpref.p);
+  P.n_queries = static_cast<uint32_t>(j.s->q.size());
+  P.n_segs = j.s->n_segs;
+  P.seg_len = c->seg_len;
+  P.mid = c->d_mid;
+  P.sp = c->d_sp;
+  P.sp_p = c->d_sp_p;
+  P.spill = static_cast<uint64_t*>(c->spill.p);
+  P.flags = d_flags;
   P.batch = j.batch;
   P.prune = c->prune;
   P.pfilter = !(ph_lo == 0 && ph_hi == (1ull << 32));
   P.ph_lo = ph_lo;
   P.ph_hi = ph_hi;
-  P.b1mask = j.B1 - 1;
-  P.l1 = static_cast<Entry*>(c->l1.p);
+  P.b1bits = plan.b1bits;
+  P.li_bits = j.li_bits;
+  P.kl_mask = j.kl_mask;
+  P.l1 = static_cast<uint64_t*>(c->l1.p);
   P.cap1 = plan.cap1;
   P.cnt1 = static_cast<uint32_t*>(c->cnt1.p);
   {
     LaunchTimer t(c, K_SIEVE, st);
-    launch_sieve<MODE_KEYS>(c, P, j.sieve_grid, st);
+    hipLaunchKernelGGL(k_sieve_keys, dim3(j.sieve_grid), dim3(kKeyBlock), 0, st, P);
   }
   BX_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_sum_counts, dim3(64), dim3(256), 0, st, static_cast<const uint32_t*>(c->cnt1.p), j.n_regions,
                      static_cast<unsigned long long*>(c->acc.p) + kAccEntries);
   BX_HIP(hipGetLastError());
+  WordSource src;
+  src.queries = P.queries;
+  src.seg_prefix = P.seg_prefix;
+  src.n_queries = P.n_queries;
+  src.seg_len = c->seg_len;
+  src.W = j.sieve_grid;
+  src.li_bits = j.li_bits;
+  src.batch = j.batch;
   for (uint32_t first = 0; first < j.B1; first += j.G) {
     PartParams Q;
-    Q.l1 = static_cast<const Entry*>(c->l1.p);
+    Q.l1 = static_cast<const uint64_t*>(c->l1.p);
     Q.cap1 = plan.cap1;
     Q.cnt1 = static_cast<const uint32_t*>(c->cnt1.p);
     Q.W = j.sieve_grid;
@@ -830,23 +886,21 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
     Q.l2 = static_cast<Entry*>(c->l2.p);
     Q.cap2 = plan.cap2;
     Q.cnt2 = static_cast<uint32_t*>(c->cnt2.p);
-    Q.b2shift = plan.b2bits ? kFpBits - plan.b2bits : 0;
+    Q.b2bits = plan.b2bits;
     Q.fp_mask = c->fp_mask;
-    Q.b2mask = j.B2 - 1;
-    Q.gmask = j.gmask;
     Q.flags = d_flags;
+    Q.src = src;
+    Q.kl_mask = j.kl_mask;
     Q.l2c = static_cast<uint64_t*>(c->l2.p);
-    Q.idx_bits = j.idx_bits;
+    Q.wl_bits = j.wl_bits;
     Q.low_mask = j.low_mask;
     {
       LaunchTimer t(c, K_PART, st);
       const dim3 pg(static_cast<uint32_t>(j.part_grid));
-      if (c->fp_mask != (1ull << kFpBits) - 1)
-        hipLaunchKernelGGL((k_partition<kPartBlock, true, false>), pg, dim3(kPartBlock), 0, st, Q);
-      else if (j.compact)
-        hipLaunchKernelGGL((k_partition<kPartBlock, false, true>), pg, dim3(kPartBlock), 0, st, Q);
+      if (j.compact)
+        hipLaunchKernelGGL((k_partition<kPartBlock, true>), pg, dim3(kPartBlock), 0, st, Q);
       else
-        hipLaunchKernelGGL((k_partition<kPartBlock, false, false>), pg, dim3(kPartBlock), 0, st, Q);
+        hipLaunchKernelGGL((k_partition<kPartBlock, false>), pg, dim3(kPartBlock), 0, st, Q);
     }
     BX_HIP(hipGetLastError());
     JoinParams J;
@@ -860,12 +914,12 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
     J.flags = d_flags;
     J.joined = static_cast<unsigned long long*>(c->acc.p) + kAccJoined;
     J.l2c = static_cast<const uint64_t*>(c->l2.p);
-    J.idx_bits = j.idx_bits;
-    J.l1 = static_cast<const Entry*>(c->l1.p);
-    J.cap1 = plan.cap1;
-    J.W = j.sieve_grid;
-    J.first = first;
-    J.b2mask = j.B2 - 1;
+    J.wl_bits = j.wl_bits;
+    J.low_mask = j.low_mask;
+    J.src = src;
+    J.primes = c->d_primes;
+    J.pinv = c->d_pinv;
+    J.n_primes = static_cast<uint32_t>(c->primes.size());
     {
       LaunchTimer t(c, K_JOIN, st);
       if (j.compact)
@@ -943,7 +997,8 @@ int enqueue_verify(bx_ctx* c, const Job& j, uint32_t grid, hipStream_t st) {
   V.batch = j.batch;
   V.kinds = j.kinds;
   V.third_off = c->third_off;
-  V.fp_mask = c->fp_mask;
+  V.fp_mask = j.cand_fp_mask;
+  V.compact = j.compact;
   V.out = static_cast<OutPair*>(c->out.p);
   V.out_cap = kCandCap;
   V.flags = static_cast<uint32_t*>(c->flags.p);
@@ -967,10 +1022,9 @@ int read_flags_acc(bx_ctx* c, uint32_t* fl, unsigned long long* acc, hipStream_t
 int collect_pairs(bx_ctx* c, const uint32_t* fl, const unsigned long long* acc, hipStream_t st,
                   std::vector<OutPair>* result) {
   if (fl[kFlagSpillOverflow]) return fail(BX_EINTERNAL, "sparse-hit spill buffer overflow");
-  if (fl[kFlagCand] > kCandCap) return fail(BX_EINTERNAL, "candidate buffer overflow");
   if (fl[kFlagVerifyFail])
     return fail(BX_EINTERNAL, std::to_string(fl[kFlagVerifyFail]) + " candidate pairs failed exact verification");
-  c->stats.candidates = fl[kFlagCand];
+  c->stats.candidates = fl[kFlagCand] - fl[kFlagDropped];
   c->stats.false_candidates = fl[kFlagFalseCand];
   c->stats.word_matches = fl[kFlagWordMatch];
   const uint32_t n_out = std::min(fl[kFlagOut], kCandCap);
@@ -1000,9 +1054,20 @@ int run_passes_checked(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* 
   std::deque<std::pair<uint64_t, uint64_t>> pending;
   for (uint64_t v = 0; v < j.plan.passes; ++v)
     pending.emplace_back((v << 32) / j.plan.passes, ((v + 1) << 32) / j.plan.passes);
-  uint32_t cand_before = 0;
+  // Candidates are verified after every pass, so the buffer holds one pass's.
+  uint32_t cand_before = 0;  // of the small class, not yet verified
+  uint64_t cand_total = 0;
   unsigned long long acc_before[kAccCount] = {0, 0}, acc[kAccCount] = {0, 0};
   uint32_t fl[kFlagCount] = {};
+  auto verify_found = [&]() -> int {
+    const uint32_t n = fl[kFlagCand];
+    if (n == 0) return BX_OK;
+    if (n > kCandCap) return fail(BX_EINTERNAL, "candidate buffer overflow");
+    cand_total += n;
+    int r = enqueue_verify(c, j, std::min<uint32_t>(n, kVerifyGrid), st);
+    if (r == BX_OK) r = fill_u32(c, static_cast<uint32_t*>(c->flags.p) + kFlagCand, 1, 0, st);
+    return r;
+  };
   if (!j.s->small.empty()) {  // a split pass rolls back to what the small class left
     if ((rc = read_flags_acc(c, fl, acc, st)) != BX_OK) return rc;
     cand_before = fl[kFlagCand];
@@ -1029,14 +1094,13 @@ int run_passes_checked(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* 
       pending.emplace_front(ph_lo, mid);
       continue;
     }
-    cand_before = fl[kFlagCand];
     std::memcpy(acc_before, acc, sizeof(acc));
+    if ((rc = verify_found()) != BX_OK) return rc;
+    cand_before = 0;
   }
-  if (cand_before > 0) {  // otherwise the last read is current
-    if (cand_before > kCandCap) return fail(BX_EINTERNAL, "candidate buffer overflow");
-    if ((rc = enqueue_verify(c, j, std::min<uint32_t>(cand_before, kVerifyGrid), st)) != BX_OK) return rc;
-    if ((rc = read_flags_acc(c, fl, acc, st)) != BX_OK) return rc;
-  }
+  if (j.plan.passes == 0 && (rc = verify_found()) != BX_OK) return rc;  // small-class queries only
+  if (cand_total && (rc = read_flags_acc(c, fl, acc, st)) != BX_OK) return rc;  // otherwise the last read is current
+  fl[kFlagCand] = static_cast<uint32_t>(cand_total);
   return collect_pairs(c, fl, acc, st, result);
 }
 
@@ -1056,7 +1120,7 @@ int run_passes_graph(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* re
                 j.G, static_cast<unsigned long long>(j.s->n_segs), static_cast<uint32_t>(j.s->q.size()), j.batch,
                 j.kinds, c->third_off, c->tile, c->seg_len, c->prune, c->join_sort,
                 static_cast<unsigned long long>(c->fp_mask), c->small_max, c->small_block, j.s->small.size(),
-                static_cast<int>(j.compact), j.idx_bits, static_cast<unsigned long long>(j.low_mask), c->l1.p,
+                static_cast<int>(j.compact), j.wl_bits, static_cast<unsigned long long>(j.low_mask), c->l1.p,
                 c->l2.p, c->spill.p, c->cnt1.p, c->cnt2.p, c->cand.p, c->out.p, c->flags.p, c->acc.p, c->queries.p,
                 c->segpref.p, c->smallq.p, static_cast<void*>(c->d_pp), static_cast<void*>(c->d_primes));
   if (!c->graph_exec || c->graph_key != key) {
@@ -1107,6 +1171,7 @@ int run_passes_graph(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* re
     *redo = 1;
     return BX_OK;
   }
+  if (fl[kFlagCand] > kCandCap) return fail(BX_EINTERNAL, "candidate buffer overflow");
   return collect_pairs(c, fl, acc, st, result);
 }
 
@@ -1160,7 +1225,7 @@ int radicals_into(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t* dev_out, hipStr
   P.rad_hi = hi;
   {
     LaunchTimer t(c, K_RAD, st);
-    launch_sieve<MODE_RAD>(c, P, grid, st);
+    launch_sieve(c, P, grid, st);
   }
   BX_HIP(hipGetLastError());
   return BX_OK;
@@ -1234,6 +1299,7 @@ int run_alg3(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
     Job j;
     j.batch = 0;
     j.kinds = kinds;
+    j.cand_fp_mask = c->fp_mask;
     if ((rc = enqueue_verify(c, j, std::min<uint32_t>(fl[kFlagCand], kVerifyGrid), st)) != BX_OK) return rc;
     if ((rc = read_flags_acc(c, fl, acc_f, st)) != BX_OK) return rc;
   }
@@ -1259,7 +1325,7 @@ int run_alg2(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
   const uint64_t n_tiles_max = (cap + kRsTile - 1) / kRsTile, m_max = 256 * n_tiles_max;
   const uint64_t nt_max = (m_max + kScanTile - 1) / kScanTile;
   const uint64_t need = 4 * cap * 8 + m_max * 12 + nt_max * 8 + (std::min(chunk, b - a) + 1) * 8;
-  if (need + fixed_bytes(c, 0) > c->budget)
+  if (need + fixed_bytes(0) > c->budget)
     return fail(BX_ENOMEM, "Algorithm 2 needs " + std::to_string(need) + " device bytes for its list, budget " +
                                std::to_string(c->budget));
   for (int k = 0; k < 2; ++k) {
@@ -1350,6 +1416,7 @@ int run_alg2(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
     Job j;
     j.batch = 0;
     j.kinds = kinds;
+    j.cand_fp_mask = c->fp_mask;
     if ((rc = enqueue_verify(c, j, std::min<uint32_t>(fl[kFlagCand], kVerifyGrid), st)) != BX_OK) return rc;
     if ((rc = read_flags_acc(c, fl, acc_f, st)) != BX_OK) return rc;
   }
@@ -1654,6 +1721,9 @@ void bx_destroy(bx_ctx* c) {
   if (c->d_primes) (void)hipFree(c->d_primes);
   if (c->d_pinv) (void)hipFree(c->d_pinv);
   if (c->d_pp) (void)hipFree(c->d_pp);
+  if (c->d_mid) (void)hipFree(c->d_mid);
+  if (c->d_sp) (void)hipFree(c->d_sp);
+  if (c->d_sp_p) (void)hipFree(c->d_sp_p);
   for (DenseTab* d : c->d_dense)
     if (d) (void)hipFree(d);
   if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
@@ -1850,7 +1920,7 @@ int bx_radical_segment_dev_noalloc(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t
   P.rad_lo = lo;
   P.rad_hi = hi;
   c->stats.launches[K_RAD]++;
-  launch_sieve<MODE_RAD>(c, P, grid, st);
+  launch_sieve(c, P, grid, st);
   BX_HIP(hipGetLastError());
   // The call waits for its kernels: the overflow word is read back, and the
   // next call may reuse the scratch.

@@ -40,6 +40,19 @@ struct PrimeInv {
   uint64_t inv, lim;
 };
 
+// First-level word (8 B) of a kept integer x, from h = key64 of its set:
+//   bits 53..63  the top 11 bits of h (so of the 53-bit fingerprint h >> 11),
+//   above li     the fingerprint's low kl = min(42, 53 - li_bits) bits,
+//   low li_bits  x's index among the integers that its sieve workgroup visits:
+//                (s / W) * seg_len + (x - first integer of s), s its segment.
+// The bucket it lies in stands for the low bits of h, the region for the
+// workgroup s mod W.  kNoWord is never a word: the index stays below
+// 2^li_bits - 1.
+constexpr uint64_t kNoWord = ~0ull;
+__device__ __forceinline__ uint64_t l1_word(uint64_t h, uint64_t kl_mask, uint32_t li_bits, uint64_t li) {
+  return (h & ~((1ull << 53) - 1)) | (((h >> 11) & kl_mask) << li_bits) | li;
+}
+
 struct Query {
   uint64_t a, b;  // x in [a, b); radicals over [a, b]
 };
@@ -76,8 +89,9 @@ enum : int {
   kFlagVerifyFail = 4,
   kFlagSpillOverflow = 5,
   kFlagFalseCand = 6,  // equal fingerprints of different sets (dropped)
-  kFlagWordMatch = 7,  // compact words with equal kept bits (each re-read from the first level)
-  kFlagCount = 8
+  kFlagWordMatch = 7,  // compact words with equal kept bits
+  kFlagDropped = 8,    // of the candidates made from them, those with different whole fingerprints
+  kFlagCount = 9
 };
 
 // 64-bit per-call counters (acc[]): entries written by the sieve, entries read
@@ -231,6 +245,19 @@ __device__ __forceinline__ Entry make_entry(uint64_t pos43, uint64_t fp53) {
 
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 
+// Inclusive prefix sum over the wave, on the data-parallel-primitive lanes of
+// the VALU (shifts inside rows of 16, then the row totals).
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
+  int x = static_cast<int>(v);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
+  return static_cast<uint32_t>(x);
+}
+
 // Exclusive prefix sum over one value per thread of a workgroup of BLOCK
 // threads; wsum holds BLOCK/64 words of scratch.  Returns the exclusive sum
 // and writes the total to *total.
@@ -238,21 +265,11 @@ template <int BLOCK>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* wsum, uint32_t* total) {
   constexpr int NW = BLOCK / 64;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  uint32_t x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
+  const uint32_t x = wave_inclusive_scan(v);
   if (lane == 63) wsum[wid] = x;
   __syncthreads();
   if (wid == 0) {
-    uint32_t w = lane < NW ? wsum[lane] : 0u;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(w, o, 64);
-      if (lane >= o) w += y;
-    }
+    const uint32_t w = wave_inclusive_scan(lane < NW ? wsum[lane] : 0u);
     if (lane < NW) wsum[lane] = w;
   }
   __syncthreads();

@@ -1,11 +1,7 @@
 // HIP kernels of the Benelux-pair search for gfx950.
 //
-//   k_sieve<MODE_RAD>   Algorithm 1 on LDS tiles, radicals written to HBM.
-//   k_sieve<MODE_KEYS>  Algorithm 1 on LDS tiles, then for every x the member
-//                       test (may_pair), the pass filter of the hash-
-//                       partitioned passes, a fingerprint of the set S_x
-//                       (Section 2.1), wave-ballot compaction and the first
-//                       partition scatter of the join, fused in one kernel.
+//   k_sieve             Algorithm 1 on LDS tiles, radicals written to HBM (the
+//                       searches' sieve is k_sieve_keys, bx_keysieve.h).
 //   k_partition         second partition scatter (fan-out B2), XCD-aware.
 //   k_join              LDS hash join of one partition: inserts that detect
 //                       every earlier equal fingerprint on their probe chain,
@@ -23,9 +19,6 @@
 #include "bx_device.h"
 
 namespace bx {
-
-constexpr int MODE_RAD = 0;
-constexpr int MODE_KEYS = 1;
 
 // Sparse-hit list held in LDS per segment (about 850 hits per 2^18 values
 // with the 8192 tile, 2050 with the 2048 tile); the excess goes to a global
@@ -53,60 +46,16 @@ struct SieveParams {
   uint64_t* spill;  // per workgroup: spill + blockIdx.x * spill_cap
   uint32_t spill_cap;
   uint32_t* flags;
-  // MODE_RAD
   uint64_t* rad_out;
   uint64_t rad_lo, rad_hi;
-  // MODE_KEYS
-  int batch;
-  uint32_t prune;         // drop x that cannot be a member of any pair (may_pair)
-  uint32_t pfilter;       // keep x only when pass_hash(key) is in [ph_lo, ph_hi)
-  uint64_t ph_lo, ph_hi;
-  uint32_t b1mask;  // first-level bucket = low bits of key64
-  Entry* l1;       // region (b, w) of bucket b written by workgroup w: l1 + (b * gridDim.x + w) * cap1
-  uint64_t cap1;   // entries per region
-  uint32_t* cnt1;  // B1 x gridDim.x fill counts, written at the end of the kernel
 };
 
 template <int T, int BLOCK>
-struct SieveShCommon {
+struct SieveSh {
   uint64_t tile[T + 1];
   uint64_t hits[hit_cap<T>()];
   uint32_t dres[kDenseMax], doff[kDenseMax], dq[kDenseMax], dtq[kDenseMax];
-  uint32_t hit_n, n_act, stage_n, pad0;
-  uint32_t wsum[BLOCK / 64];
-};
-
-// The stage collects the kept entries of several tiles; it is written out when
-// less than kMargin slots are free at the start of a tile.  A flush runs
-// between tiles, when the tile array is free: its counting sort keeps its
-// histogram, offsets and permutation there (FlushScratch).
-template <int T, int BLOCK>
-struct SieveShKeys : SieveShCommon<T, BLOCK> {
-  // Stage capacity: 6016 entries with the 8192 tile (one workgroup per CU:
-  // what the LDS leaves beside the 64 KB tile), one tile with the 2048 tile
-  // (two per CU).  The margin holds what a tile keeps in the bulk of a range
-  // (0.107 T on average, below 0.125 T); a tile that keeps more sends the
-  // excess straight to HBM.
-  static constexpr int kStage = T >= 8192 ? 6016 : T;
-  static constexpr int kMargin = T >= 8192 ? 1152 : T / 4;
-  Entry stage[kStage];
-  uint16_t sb[kStage];
-  uint32_t lcur[kB1Max];
-  struct FlushScratch {
-    uint32_t cnt[kB1Max], gofs[kB1Max];
-    uint16_t perm[kStage];
-  };
-  static_assert(sizeof(FlushScratch) <= sizeof(uint64_t) * (T + 1), "flush scratch must fit in the tile");
-  __device__ FlushScratch* flush_scratch() { return reinterpret_cast<FlushScratch*>(this->tile); }
-};
-
-template <int T, int BLOCK, int MODE>
-struct SieveShSel {
-  using type = SieveShCommon<T, BLOCK>;
-};
-template <int T, int BLOCK>
-struct SieveShSel<T, BLOCK, MODE_KEYS> {
-  using type = SieveShKeys<T, BLOCK>;
+  uint32_t hit_n, n_act;
 };
 
 // Counting sort of n staged entries (bucket of entry i in sb[i]) into runs per
@@ -202,17 +151,6 @@ __device__ void scatter_runs(uint32_t n, uint32_t nb, const Item* ent, Bucket sb
   __syncthreads();
 }
 
-// Entry of the kept integer x = x0 + i with rad(x) = a and rad(x + 1) = b;
-// *bucket receives its first-level bucket.
-__device__ __forceinline__ Entry kept_entry(const SieveParams& P, uint64_t a, uint64_t b, uint64_t x, uint64_t qa,
-                                            uint32_t grp, uint32_t* bucket) {
-  const uint64_t klo = a < b ? a : b, khi = a < b ? b : a;
-  const uint64_t h = key64(klo, khi, grp);
-  const uint64_t pos43 = P.batch ? ((x - qa) | (static_cast<uint64_t>(grp) << kGrpShift)) : x;
-  *bucket = static_cast<uint32_t>(h) & P.b1mask;
-  return make_entry(pos43, h >> 11);
-}
-
 // Orders the LDS accesses of one wave (its lanes share stage slots).
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -220,62 +158,14 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Lane mask of the wave's integers x (one per lane, rad(x) = r0 and
-// rad(x + 1) = r1) that pass the member test (may_pair) for the query end qb.
-// UPPER: the tile lies above qb / 2, where no squarefree x or x + 1 passes
-// (the factor t is at least 2), so only both-non-squarefree x remain.  Below,
-// a squarefree y of {x, x + 1} needs y * M <= qb with M = max(2, rad(other)
-// - 1); M > lim_hi fails for the whole segment and settles almost every such
-// y at once, M <= lim_lo passes for the whole segment, and the rare rest take
-// the exact product.  small: the tile starts at x0 <= 3, where x <= 3 is kept.
-template <bool UPPER>
-__device__ __forceinline__ uint64_t member_mask(uint64_t x, uint64_t r0, uint64_t r1, uint64_t lim_hi, uint64_t lim_lo,
-                                                uint64_t qb, bool small) {
-  const bool s0 = r0 == x, s1 = r1 == x + 1;  // x, x + 1 squarefree
-  uint64_t km = ~(__ballot(s0) | __ballot(s1));
-  if constexpr (!UPPER) {
-    const bool c0 = s0 && r1 <= lim_hi + 1, c1 = s1 && r0 <= lim_hi + 1;
-    const uint64_t cm = __ballot(c0 || c1);
-    if (cm) {
-      bool k = false;
-      if (c0 || c1) {
-        const uint64_t M0 = r1 >= 3 ? r1 - 1 : 2, M1 = r0 >= 3 ? r0 - 1 : 2;
-        const bool p0 = !s0 || (c0 && (M0 <= lim_lo || prod_le(x, M0, qb)));
-        const bool p1 = !s1 || (c1 && (M1 <= lim_lo || prod_le(x + 1, M1, qb)));
-        k = p0 && p1;
-      }
-      km = (km & ~cm) | __ballot(k);
-    }
-    if (small) km |= __ballot(x <= 3);
-  }
-  return km;
-}
-
 template <int T, int BLOCK>
-__device__ void flush_stage(SieveShKeys<T, BLOCK>& sh, const SieveParams& P) {
-  __syncthreads();
-  const uint32_t n = min(sh.stage_n, static_cast<uint32_t>(SieveShKeys<T, BLOCK>::kStage));  // later slots went straight out
-  const uint64_t cap1 = P.cap1, W = gridDim.x;
-  Entry* l1 = P.l1 + static_cast<uint64_t>(blockIdx.x) * cap1;
-  const uint16_t* sb = sh.sb;
-  auto* fs = sh.flush_scratch();
-  scatter_runs<BLOCK, kB1Max, SieveShKeys<T, BLOCK>::kStage, true>(
-      n, P.b1mask + 1, sh.stage, [=](uint32_t i) -> uint32_t { return sb[i]; }, fs->perm, fs->cnt, fs->gofs, sh.wsum,
-      sh.lcur, cap1, &P.flags[kFlagL1Overflow],
-      [=](uint32_t b, uint32_t k, const Entry& e) { l1[b * W * cap1 + k] = e; }, [] {});
-  if (threadIdx.x == 0) sh.stage_n = 0;
-  __syncthreads();
-}
-
-template <int T, int BLOCK, int MODE>
 __global__ __launch_bounds__(BLOCK) void k_sieve(SieveParams P) {
-  using Sh = typename SieveShSel<T, BLOCK, MODE>::type;
   constexpr uint32_t kHitCap = hit_cap<T>();
   static_assert(T % BLOCK == 0 && T <= 65536, "tile shape");
   constexpr int ITER = T / BLOCK;                                     // keys per thread per tile
   constexpr int SLOTS = (dense_slot_cap(T) + BLOCK - 1) / BLOCK;      // dense slots per thread
   static_assert(kDenseMax <= 64 && T / 9 < 1024, "dense slot packing (sdj below)");
-  __shared__ Sh sh;
+  __shared__ SieveSh<T, BLOCK> sh;
   const int tid = threadIdx.x;
   const DenseTab* D = P.dense;
   const uint32_t nd = D->n, nslots = D->nslots;
@@ -302,12 +192,6 @@ __global__ __launch_bounds__(BLOCK) void k_sieve(SieveParams P) {
       spinv[k] = 1;
     }
   }
-  if (tid == 0) {
-    sh.stage_n = 0;
-  }
-  if constexpr (MODE == MODE_KEYS) {
-    for (uint32_t b = tid; b < kB1Max; b += BLOCK) sh.lcur[b] = 0;
-  }
   __syncthreads();
   uint64_t* spill = P.spill + static_cast<uint64_t>(blockIdx.x) * P.spill_cap;
 
@@ -326,32 +210,6 @@ __global__ __launch_bounds__(BLOCK) void k_sieve(SieveParams P) {
     const uint64_t start = qa + (s - P.seg_prefix[qi]) * static_cast<uint64_t>(P.seg_len);
     const uint32_t len = static_cast<uint32_t>(min(static_cast<uint64_t>(P.seg_len), qb - start));
     const uint64_t V = start + len;  // largest value sieved in this segment
-    // Every tile starts at x0 = qa (mod T) (segments and tiles are multiples
-    // of T), so the factor-2 shift of x = x0 + j, j = it * BLOCK + tid, is
-    // max(ctz(m), 1) - 1 with m = (qa + j) mod T, the same in every tile,
-    // except at the one j with m = 0 (ctz(x) >= log2 T), taken exactly.
-    // Four bits per integer of this thread.
-    const uint32_t c2 = static_cast<uint32_t>(qa) & static_cast<uint32_t>(T - 1);
-    const uint32_t sp_j = (static_cast<uint32_t>(T) - c2) & static_cast<uint32_t>(T - 1);
-    uint32_t shifts = 0;
-    if constexpr (MODE == MODE_KEYS) {
-#pragma unroll
-      for (int it = 0; it < ITER; ++it) {
-        const uint32_t m = (c2 + static_cast<uint32_t>(it * BLOCK + tid)) & static_cast<uint32_t>(T - 1);
-        const uint32_t tz = m ? static_cast<uint32_t>(__builtin_ctz(m)) : 1u;
-        shifts |= (max(tz, 1u) - 1u) << (4 * it);
-      }
-    }
-    // Member test below b/2: y * M <= b fails for every y of the segment when
-    // M > lim_hi and holds for every y when M <= lim_lo (y in [start, V]);
-    // only M in between needs the exact product.  Both limits are
-    // conservative roundings of double quotients.
-    uint64_t lim_hi = 0, lim_lo = 0;
-    if (MODE == MODE_KEYS && P.prune) {
-      const double bd = static_cast<double>(qb);
-      lim_hi = static_cast<uint64_t>(bd / static_cast<double>(start > 0 ? start : 1) * (1.0 + 1e-9)) + 1;
-      lim_lo = static_cast<uint64_t>(bd / static_cast<double>(V) * (1.0 - 1e-9));
-    }
     if (tid == 0) {
       uint32_t l = P.n_dense, h = P.n_pp;
       while (l < h) {
@@ -401,23 +259,11 @@ __global__ __launch_bounds__(BLOCK) void k_sieve(SieveParams P) {
     const uint32_t nh = min(sh.hit_n, kHitCap + P.spill_cap);
 
     for (uint32_t base = 0; base < len; base += T) {
-      if constexpr (MODE == MODE_KEYS) {
-        // Written out once less than the margin is free; stage_n is stable
-        // here (after the previous barrier), so the decision is uniform.
-        const uint32_t sn = __builtin_amdgcn_readfirstlane(sh.stage_n);
-        if (sn > static_cast<uint32_t>(Sh::kStage - Sh::kMargin)) flush_stage<T, BLOCK>(sh, P);
-      }
       const uint32_t cnt = min(static_cast<uint32_t>(T), len - base);
       const uint64_t x0 = start + base;
       // r[n] <- n with the prime 2 already reduced (count trailing zeros).
       // The whole tile is written (values past cnt are never used).
-      if constexpr (MODE == MODE_KEYS) {
-#pragma unroll
-        for (int it = 0; it < ITER; ++it)
-          sh.tile[it * BLOCK + tid] = (x0 + it * BLOCK + tid) >> ((shifts >> (4 * it)) & 15u);
-        if (static_cast<uint32_t>(tid) == (sp_j & static_cast<uint32_t>(BLOCK - 1))) sh.tile[sp_j] = strip_two(x0 + sp_j);
-        if (tid == 0) sh.tile[T] = strip_two(x0 + T);
-      } else if (const uint32_t x0lo = static_cast<uint32_t>(x0);
+      if (const uint32_t x0lo = static_cast<uint32_t>(x0);
                  x0lo != 0u && x0lo <= 0xFFFFFFFFu - static_cast<uint32_t>(T)) {
         // Uniform: no x of the tile (x0 .. x0 + T) has a zero low word.
 #pragma unroll
@@ -467,131 +313,51 @@ __global__ __launch_bounds__(BLOCK) void k_sieve(SieveParams P) {
       }
       __syncthreads();
 
-      if constexpr (MODE == MODE_RAD) {
-        for (uint32_t i = tid; i < cnt; i += BLOCK) {
-          const uint64_t x = x0 + i;
-          if (x >= P.rad_lo && x < P.rad_hi) P.rad_out[x - P.rad_lo] = sh.tile[i];
-        }
-      } else {
-        const uint32_t grp = P.batch ? qi : 0u;
-        // Above b/2 no squarefree x or x + 1 passes the member test (the
-        // factor t is at least 2): only both-non-squarefree x remain.
-        const bool upper = x0 > 3 && x0 > (qb >> 1);
-        // 1. The member and pass tests for this thread's ITER integers (cheap,
-        // every x).  The tile holds T + 1 values, so the loads need no guard;
-        // every branch below is uniform over the wave.
-        uint64_t ra[ITER], rb[ITER];
-#pragma unroll
-        for (int it = 0; it < ITER; ++it) {
-          const uint32_t i = it * BLOCK + tid;
-          ra[it] = sh.tile[i];
-          rb[it] = sh.tile[i + 1];
-        }
-        // Lane masks of the wave (all 64 lanes are active here): bit l of
-        // mask[it] says whether lane l keeps its it-th integer.  The common
-        // cases (member test on, one pass, a whole tile) run loops of their
-        // own, so that no uniform flag is tested per integer.
-        uint64_t mask[ITER];
-        uint32_t total = 0;
-        const bool full = cnt == static_cast<uint32_t>(T);
-        const bool small = x0 <= 3;
-        if (P.prune && !P.pfilter && full && upper) {
-#pragma unroll
-          for (int it = 0; it < ITER; ++it) {
-            mask[it] = member_mask<true>(x0 + it * BLOCK + tid, ra[it], rb[it], lim_hi, lim_lo, qb, small);
-            total += __popcll(mask[it]);
-          }
-        } else if (P.prune && !P.pfilter && full) {
-#pragma unroll
-          for (int it = 0; it < ITER; ++it) {
-            mask[it] = member_mask<false>(x0 + it * BLOCK + tid, ra[it], rb[it], lim_hi, lim_lo, qb, small);
-            total += __popcll(mask[it]);
-          }
-        } else {
-#pragma unroll
-          for (int it = 0; it < ITER; ++it) {
-            const uint32_t i = it * BLOCK + tid;
-            const uint64_t r0 = ra[it], r1 = rb[it];
-            const uint64_t x = x0 + i;
-            uint64_t km = ~0ull;
-            if (P.prune)
-              km = upper ? member_mask<true>(x, r0, r1, lim_hi, lim_lo, qb, small)
-                         : member_mask<false>(x, r0, r1, lim_hi, lim_lo, qb, small);
-            if (P.pfilter) {
-              const uint64_t ph = pass_hash(r0 < r1 ? r0 : r1, r0 < r1 ? r1 : r0, grp);
-              km &= __ballot(ph >= P.ph_lo && ph < P.ph_hi);
-            }
-            if (!full) km &= __ballot(i < cnt);
-            mask[it] = km;
-            total += __popcll(km);
-          }
-        }
-        // 2. Wave-local compaction: ballots rank the wave's kept integers,
-        // lane 0 reserves their stage slots with one LDS atomic, and each
-        // kept integer writes its tile index into its slot (two bytes, the
-        // only work done per integer with lanes masked off).  The wave then
-        // builds the entries of its slots, one slot per lane, from rad(x)
-        // and rad(x + 1) still in the tile.  Slots past the stage (a tile
-        // that keeps more than the margin left free) are built at once and
-        // go straight to the workgroup's regions.
-        if (total) {  // uniform over the wave
-          const uint64_t below = (1ull << lane_id()) - 1ull;
-          uint32_t sbase = 0;
-          if (lane_id() == 0) sbase = atomicAdd(&sh.stage_n, total);
-          sbase = __builtin_amdgcn_readfirstlane(sbase);
-          const uint32_t send = min(sbase + total, static_cast<uint32_t>(Sh::kStage));
-          uint32_t sl = sbase;
-          if (sbase + total <= static_cast<uint32_t>(Sh::kStage)) {  // the common case: all in the stage
-#pragma unroll
-            for (int it = 0; it < ITER; ++it) {
-              if ((mask[it] >> lane_id()) & 1ull)
-                sh.sb[sl + __popcll(mask[it] & below)] = static_cast<uint16_t>(it * BLOCK + tid);
-              sl += __popcll(mask[it]);
-            }
-          } else {
-#pragma unroll
-            for (int it = 0; it < ITER; ++it) {
-              if ((mask[it] >> lane_id()) & 1ull) {
-                const uint32_t i = it * BLOCK + tid;
-                const uint32_t slot = sl + __popcll(mask[it] & below);
-                if (slot < static_cast<uint32_t>(Sh::kStage)) {
-                  sh.sb[slot] = static_cast<uint16_t>(i);
-                } else {
-                  uint32_t bk;
-                  const Entry e = kept_entry(P, ra[it], rb[it], x0 + i, qa, grp, &bk);
-                  const uint32_t g = atomicAdd(&sh.lcur[bk], 1u);
-                  if (g < P.cap1)
-                    P.l1[(static_cast<uint64_t>(bk) * gridDim.x + blockIdx.x) * P.cap1 + g] = e;
-                  else
-                    atomicOr(&P.flags[kFlagL1Overflow], 1u);
-                }
-              }
-              sl += __popcll(mask[it]);
-            }
-          }
-          wave_sync();
-          for (uint32_t sidx = sbase + lane_id(); sidx < send; sidx += 64) {
-            const uint32_t i = sh.sb[sidx];
-            uint32_t bk;
-            sh.stage[sidx] = kept_entry(P, sh.tile[i], sh.tile[i + 1], x0 + i, qa, grp, &bk);
-            sh.sb[sidx] = static_cast<uint16_t>(bk);
-          }
-        }
+      for (uint32_t i = tid; i < cnt; i += BLOCK) {
+        const uint64_t x = x0 + i;
+        if (x >= P.rad_lo && x < P.rad_hi) P.rad_out[x - P.rad_lo] = sh.tile[i];
       }
       __syncthreads();
     }
   }
-  if constexpr (MODE == MODE_KEYS) {
-    __syncthreads();
-    const uint32_t sn = __builtin_amdgcn_readfirstlane(sh.stage_n);
-    if (sn > 0) flush_stage<T, BLOCK>(sh, P);
-    for (uint32_t b = tid; b <= P.b1mask; b += BLOCK) P.cnt1[static_cast<uint64_t>(b) * gridDim.x + blockIdx.x] = sh.lcur[b];
+}
+
+// Where the first level's words came from: enough to turn a word's index back
+// into its integer.
+struct WordSource {
+  const Query* queries;
+  const uint64_t* seg_prefix;
+  uint32_t n_queries;
+  uint32_t seg_len, W;  // segment length; sieve workgroups
+  uint32_t li_bits;
+  int batch;
+};
+
+// The integer with index li of sieve workgroup w, and its query (0 unless batched).
+__device__ __forceinline__ uint64_t word_integer(const WordSource& S, uint32_t w, uint64_t li, uint32_t* grp) {
+  const uint64_t s = w + (li / S.seg_len) * S.W;
+  uint32_t lo = 0, hi = S.n_queries;
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (S.seg_prefix[mid] <= s)
+      lo = mid;
+    else
+      hi = mid;
   }
+  *grp = S.batch ? lo : 0u;
+  return S.queries[lo].a + (s - S.seg_prefix[lo]) * S.seg_len + li % S.seg_len;
+}
+
+// pos43 of an Entry (bx_device.h).
+__device__ __forceinline__ uint64_t word_pos43(const WordSource& S, uint32_t w, uint64_t li) {
+  uint32_t grp;
+  const uint64_t x = word_integer(S, w, li, &grp);
+  return S.batch ? ((x - S.queries[grp].a) | (static_cast<uint64_t>(grp) << kGrpShift)) : x;
 }
 
 struct PartParams {
-  const Entry* l1;
-  uint64_t cap1;          // entries per first-level region
+  const uint64_t* l1;
+  uint64_t cap1;          // words per first-level region
   const uint32_t* cnt1;   // B1 x W region fill counts
   uint32_t W;             // regions per bucket (sieve workgroups)
   uint32_t first;  // first first-level bucket of this group
@@ -600,22 +366,18 @@ struct PartParams {
   Entry* l2;       // group buffer: G x B2 sub-buckets of cap2 entries
   uint32_t cap2;
   uint32_t* cnt2;  // G x B2 cursors (zero on entry)
-  uint32_t b2shift, b2mask;  // second-level partition = top bits of the fingerprint
+  uint32_t b2bits;  // second-level partition = top b2bits of the fingerprint
   uint64_t fp_mask;          // fingerprint bits kept (all 53 but in tests of the verification)
-  uint32_t gmask;
   uint32_t* flags;
-  // Compact second level: one 64-bit word per entry, fp_low << idx_bits | i,
-  // with i = w * cap1 + k the entry's index among its first-level bucket's
-  // regions (entry k of region (b, w)), which stay intact until the group is
-  // joined.  The top of the fingerprint is the partition's own index.
+  WordSource src;
+  uint64_t kl_mask;  // fingerprint bits above a word's index
+  // Compact second level: one 64-bit word per entry, fp_low << wl_bits |
+  // w << li_bits | li: the first-level word's index with its region.  The top
+  // of the fingerprint is the partition's own index.
   uint64_t* l2c;
-  uint32_t idx_bits;
+  uint32_t wl_bits;
   uint64_t low_mask;  // fingerprint bits a compact word keeps
 };
-
-__device__ __forceinline__ uint64_t compact_word(const PartParams& P, const Entry& e, uint64_t idx) {
-  return ((entry_fp(e) & P.low_mask) << P.idx_bits) | idx;
-}
 
 // Second scatter of one group of first-level buckets into the group buffer.
 // Persistent: workgroup l runs on XCD l mod 8 (round-robin dispatch) and
@@ -624,7 +386,7 @@ __device__ __forceinline__ uint64_t compact_word(const PartParams& P, const Entr
 // before they are written back.  The bucket's chunks are split into nbw
 // contiguous ranges, one per workgroup; the next chunk is loaded into
 // registers while the current one is scattered.
-template <int BLOCK, bool MASK_FP, bool COMPACT>
+template <int BLOCK, bool COMPACT>
 __global__ __launch_bounds__(BLOCK) void k_partition(PartParams P) {
   constexpr int EPT = kPartChunk / BLOCK;
   static_assert(kPartChunk % BLOCK == 0, "chunk shape");
@@ -641,7 +403,7 @@ __global__ __launch_bounds__(BLOCK) void k_partition(PartParams P) {
   const uint32_t k = slot * per + xcd / P.G;  // index among the bucket's nbw workgroups
   const uint32_t nbw = (gridDim.x >> 3) * per;
   const uint32_t b1 = P.first + gb;
-  const uint32_t B2 = P.b2mask + 1;
+  const uint32_t B2 = 1u << P.b2bits;
   const uint32_t cpr = P.chunks_per_region;
   const uint64_t n_chunks = static_cast<uint64_t>(P.W) * cpr;
   const uint64_t c_begin = n_chunks * k / nbw, c_end = n_chunks * (k + 1) / nbw;
@@ -652,15 +414,15 @@ __global__ __launch_bounds__(BLOCK) void k_partition(PartParams P) {
   // The partition of an entry is the top of its fingerprint.
   auto bucket_of = [&](uint32_t i) -> uint32_t { return sbk[i]; };
   // Chunk ci of the bucket: entries [s0, s0 + n) of region ci / cpr.
-  auto chunk = [&](uint64_t ci, const Entry** src) -> uint32_t {  // ci < n_chunks
+  auto chunk = [&](uint64_t ci, const uint64_t** src) -> uint32_t {  // ci < n_chunks
     const uint64_t region = static_cast<uint64_t>(b1) * P.W + ci / cpr;
     const uint64_t n1 = min(static_cast<uint64_t>(P.cnt1[region]), P.cap1);
     const uint64_t s0 = (ci % cpr) * static_cast<uint64_t>(kPartChunk);
     *src = P.l1 + region * P.cap1 + s0;
     return s0 >= n1 ? 0u : static_cast<uint32_t>(min(static_cast<uint64_t>(kPartChunk), n1 - s0));
   };
-  Entry e[EPT];
-  const Entry* src;
+  uint64_t e[EPT];
+  const uint64_t* src;
   uint32_t n = c_begin < c_end ? chunk(c_begin, &src) : 0u;
 #pragma unroll
   for (int q = 0; q < EPT; ++q) {
@@ -668,22 +430,18 @@ __global__ __launch_bounds__(BLOCK) void k_partition(PartParams P) {
     if (i < n) e[q] = src[i];
   }
   for (uint64_t ci = c_begin; ci < c_end; ++ci) {
-    // Index of the chunk's first entry among the bucket's regions (compact words).
-    const uint64_t ibase = COMPACT ? (ci / cpr) * P.cap1 + (ci % cpr) * static_cast<uint64_t>(kPartChunk) : 0ull;
+    const uint32_t w = static_cast<uint32_t>(ci / cpr);  // the chunk's region
+    const uint64_t wl = static_cast<uint64_t>(w) << P.src.li_bits, li_mask = (1ull << P.src.li_bits) - 1;
 #pragma unroll
     for (int q = 0; q < EPT; ++q) {
       const uint32_t i = tid + q * BLOCK;
       if (i < n) {
-        Entry x = e[q];
-        if constexpr (MASK_FP) {  // tests of the verification only
-          const uint64_t pos43 = entry_pos43(x);
-          x = make_entry(pos43, entry_fp(x) & P.fp_mask);
-        }
+        const uint64_t x = e[q], li = x & li_mask, low = (x >> P.src.li_bits) & P.kl_mask;
         if constexpr (COMPACT)
-          ent[i] = compact_word(P, x, ibase + i);
+          ent[i] = ((low & P.low_mask) << P.wl_bits) | wl | li;
         else
-          ent[i] = x;
-        sbk[i] = static_cast<uint16_t>(static_cast<uint32_t>(entry_fp(e[q]) >> P.b2shift) & P.b2mask);
+          ent[i] = make_entry(word_pos43(P.src, w, li), (((x >> 53) << 42) | low) & P.fp_mask);
+        sbk[i] = static_cast<uint16_t>(x >> 53 >> (11 - P.b2bits));
       }
     }
     const uint32_t n_cur = n;
@@ -723,21 +481,15 @@ struct JoinParams {
   uint32_t cand_cap;
   uint32_t* flags;
   unsigned long long* joined;  // entries read, summed over partitions (64-bit: 2^36 searches pass 2^32)
-  // Compact second level (k_join_c): the words and the first level they index.
+  // Compact second level (k_join_c).
   const uint64_t* l2c;
-  uint32_t idx_bits;
-  const Entry* l1;
-  uint64_t cap1;
-  uint32_t W, first;  // regions per bucket; first first-level bucket of the group
-  uint32_t b2mask;    // sub-bucket sbk is partition sbk & b2mask of bucket first + sbk / (b2mask + 1)
+  uint32_t wl_bits;
+  uint64_t low_mask;
+  WordSource src;
+  const uint32_t* primes;  // 2, 3, 5, ...
+  const PrimeInv* pinv;
+  uint32_t n_primes;
 };
-
-// The 12-byte entry a compact word of sub-bucket sbk stands for, read back
-// from its first-level region.
-__device__ __forceinline__ Entry compact_entry(const JoinParams& P, uint64_t w, uint64_t sbk) {
-  const uint64_t b1 = P.first + sbk / (static_cast<uint64_t>(P.b2mask) + 1);
-  return P.l1[b1 * P.W * P.cap1 + (w & ((1ull << P.idx_bits) - 1))];
-}
 
 __device__ __forceinline__ void emit_cand(const JoinParams& P, const Entry& a, const Entry& b) {
   const uint32_t k = atomicAdd(&P.flags[kFlagCand], 1u);
@@ -853,10 +605,56 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
   }
 }
 
+// Two compact words whose kept fingerprint bits met.
+struct WordMatch {
+  uint64_t a, b;
+};
+constexpr uint32_t kMatchMax = 128;  // listed per chunk of a partition, in LDS
+
+// The integers of a match; false if they belong to different queries.
+struct MatchPair {
+  uint64_t x, y;
+  uint32_t grp;
+};
+__device__ __forceinline__ bool match_pair(const WordSource& S, uint32_t wl_bits, uint64_t a, uint64_t b, MatchPair* r) {
+  const uint64_t wl_mask = (1ull << wl_bits) - 1, li_mask = (1ull << S.li_bits) - 1;
+  uint32_t gb;
+  r->x = word_integer(S, static_cast<uint32_t>((a & wl_mask) >> S.li_bits), a & li_mask, &r->grp);
+  r->y = word_integer(S, static_cast<uint32_t>((b & wl_mask) >> S.li_bits), b & li_mask, &gb);
+  return r->grp == gb;
+}
+
+__device__ __forceinline__ void emit_match(const JoinParams& P, uint64_t a, uint64_t b, const MatchPair& r) {
+  const uint64_t off = P.src.batch ? P.src.queries[r.grp].a : 0ull, grp = static_cast<uint64_t>(r.grp) << kGrpShift;
+  emit_cand(P, make_entry((r.x - off) | grp, a >> P.wl_bits), make_entry((r.y - off) | grp, b >> P.wl_bits));
+}
+
+// One wave: whether S_x = S_y can hold, from the primes 3 .. 2^13, one per lane.
+// A prime that divides one of x, x + 1 has to divide the same one of y, y + 1
+// when x and y have the same parity (a pair of the first kind), and the other
+// one else (the second kind; the prime 2 tells).  Different sets seldom pass
+// the first 64 primes.
+__device__ __forceinline__ bool may_be_equal(const JoinParams& P, uint64_t x, uint64_t y) {
+  const bool cross = (x ^ y) & 1;
+  for (uint32_t i0 = 1; i0 < P.n_primes; i0 += 64) {
+    const uint32_t i = i0 + lane_id();
+    const PrimeInv v = P.pinv[i < P.n_primes ? i : P.n_primes - 1];
+    const bool a0 = x * v.inv <= v.lim, a1 = (x + 1) * v.inv <= v.lim;
+    const bool b0 = y * v.inv <= v.lim, b1 = (y + 1) * v.inv <= v.lim;
+    if (__any(cross ? a0 != b1 || a1 != b0 : a0 != b0 || a1 != b1)) return false;
+    if (P.primes[i0] >= (1u << 13)) break;
+  }
+  return true;
+}
+
 // k_join over compact words: the same inserts and probes, on the kept low
-// fingerprint bits (the partition fixes the top ones).  Both entries of a
-// match are read back from the first level and become a candidate when their
-// whole fingerprints and queries agree, as in k_join.
+// fingerprint bits (the partition fixes the top ones).  Matches are listed, and
+// at the end of a chunk each is looked at by one wave: its integers are taken
+// from the words themselves, different queries and sets that a small prime
+// tells apart are dropped, and the rest are candidates.  (The look takes a lane
+// that found it 0.5 ms for an equal pair, a wave about a microsecond.)  A chunk
+// with more matches than the list holds walks its chains once more instead and
+// makes every match a candidate.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void k_join_c(JoinParams P) {
   constexpr int EPT = kJoinCap / BLOCK;
@@ -864,6 +662,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
   constexpr uint32_t kIdxMask = (1u << kJoinIdxBits) - 1;
   static_assert(kJoinCap < (1 << kJoinIdxBits), "index field must not reach the empty marker");
   __shared__ __align__(16) uint32_t table[kJoinSlots];
+  __shared__ uint32_t matches;  // words of this partition whose kept bits met
+  __shared__ WordMatch match[kMatchMax];
   const int tid = threadIdx.x;
   const uint64_t sbk = blockIdx.x;
   if (sbk >= P.n_sub) return;
@@ -875,11 +675,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
   }
   if (n < 2) return;
   const uint64_t* src = P.l2c + sbk * P.cap2;
-  const uint32_t pb = P.idx_bits;
+  const uint32_t pb = P.wl_bits;
+  if (tid == 0) matches = 0;  // (barriers follow before the first match)
   auto emit = [&](uint64_t a, uint64_t b) {
-    atomicAdd(&P.flags[kFlagWordMatch], 1u);
-    const Entry ea = compact_entry(P, a, sbk), eb = compact_entry(P, b, sbk);
-    if (entry_fp(ea) == entry_fp(eb) && entry_grp(ea, P.gmask) == entry_grp(eb, P.gmask)) emit_cand(P, ea, eb);
+    const uint32_t k = atomicAdd(&matches, 1u);
+    if (k < kMatchMax) match[k] = WordMatch{a, b};
   };
   for (uint32_t i0 = 0; i0 < n; i0 += kJoinCap) {
     const uint32_t m = min(static_cast<uint32_t>(kJoinCap), n - i0);
@@ -940,6 +740,35 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
         }
         s = (s + 1) & smask;
       }
+    }
+    __syncthreads();
+    const uint32_t met = matches;
+    if (met == 0) continue;  // uniform
+    if (met <= kMatchMax) {
+      for (uint32_t k = tid >> 6; k < met; k += BLOCK / 64) {  // uniform over a wave
+        const WordMatch w = match[k];
+        MatchPair r;
+        if (match_pair(P.src, pb, w.a, w.b, &r) && may_be_equal(P, r.x, r.y) && lane_id() == 0) emit_match(P, w.a, w.b, r);
+      }
+    } else {
+      // Each entry of the chunk against those before it, each later one against all.
+      for (uint32_t i = i0 + tid; i < n; i += BLOCK) {
+        const uint64_t g = src[i];
+        const uint32_t h = static_cast<uint32_t>(g >> pb);
+        uint32_t s = h & smask;
+        for (uint32_t v = table[s]; v != kEmpty; s = (s + 1) & smask, v = table[s]) {
+          const uint32_t o = i0 + (v & kIdxMask);
+          if (((v ^ h) & ~kIdxMask) != 0 || o >= i) continue;
+          const uint64_t f = src[o];
+          MatchPair r;
+          if ((f >> pb) == (g >> pb) && match_pair(P.src, pb, g, f, &r)) emit_match(P, g, f, r);
+        }
+      }
+    }
+    __syncthreads();
+    if (tid == 0) {
+      atomicAdd(&P.flags[kFlagWordMatch], met);
+      matches = 0;
     }
     __syncthreads();
   }
@@ -1039,7 +868,8 @@ struct VerifyParams {
   int batch;
   uint32_t kinds;
   uint32_t third_off;  // the third condition compares rad(m + third_off), rad(n + third_off) (2 in use)
-  uint64_t fp_mask;
+  uint64_t fp_mask;  // fingerprint bits every candidate's entries hold
+  int compact;
   OutPair* out;
   uint32_t out_cap;
   uint32_t* flags;
@@ -1121,9 +951,15 @@ __global__ __launch_bounds__(BLOCK) void k_verify(VerifyParams P) {
       const uint64_t lo_n = rad[2] < rad[3] ? rad[2] : rad[3], hi_n = rad[2] < rad[3] ? rad[3] : rad[2];
       const bool same = (lo_m == lo_n) && (hi_m == hi_n) && m != n &&
                         entry_grp(cd.b, P.batch ? kGrpMask : 0u) == qa_idx;
+      const uint64_t fp_m = key64(lo_m, hi_m, P.batch ? qa_idx : 0u) >> 11;
       if (!same) {
-        atomicAdd(&P.flags[kFlagFalseCand], 1u);  // equal fingerprints, different sets (or queries)
-      } else if (((key64(lo_m, hi_m, P.batch ? qa_idx : 0u) >> 11) & P.fp_mask) != entry_fp(cd.a)) {
+        // Different sets (or queries).  A candidate made from compact words
+        // counts as one only if the whole fingerprints agree.
+        if (P.compact && fp_m != key64(lo_n, hi_n, P.batch ? qa_idx : 0u) >> 11)
+          atomicAdd(&P.flags[kFlagDropped], 1u);
+        else
+          atomicAdd(&P.flags[kFlagFalseCand], 1u);
+      } else if ((fp_m ^ entry_fp(cd.a)) & P.fp_mask) {
         atomicAdd(&P.flags[kFlagVerifyFail], 1u);  // the entry does not hold this set's fingerprint
       } else {
         // Kind 1 iff rad(m) = rad(n) (Algorithm 2); the third-condition bit

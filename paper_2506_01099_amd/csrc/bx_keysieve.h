@@ -1,0 +1,633 @@
+// The key sieve of the searches: Algorithm 1 as far as the join needs it.
+//
+// The join takes only the integers x that pass the member test, almost all of
+// them with x and x + 1 non-squarefree (10.7%), so rad(x) is needed for few x.
+// k_sieve_keys therefore keeps, per integer, one bit (x is a multiple of the
+// square of a prime) and the product of the larger prime powers' factors (the
+// cell E), finds the kept x from the bits, and computes rad(x) and rad(x + 1)
+// by one division each for those alone:
+//
+//   e(x) = x / rad(x) = 2^(a-1) * s(x) * E(x)
+//     2^(a-1)  from the trailing zeros of x,
+//     s(x)     one factor 3, 5, 7 for 9, 25, 49 | x, from x's residues,
+//     E(x)     one factor p for every other odd power p^k | x, k >= 2.
+//
+// A wave sieves a subtile of 1024 integers on its own: its cells, bits and
+// kept list are private to it, so no barrier falls inside a subtile (LDS
+// accesses of one wave execute in order).  The words of the kept x leave
+// through per-bucket queues in LDS, from which any wave writes out a run as
+// soon as the run is claimed, without a barrier too (KeyQueue).  The workgroup
+// meets only to list the hits of the powers above 361: per chunk of 2^18
+// integers those of the powers above 2^16, per block of 2^17 all of them.
+#pragma once
+#include "bx_kernels.h"
+
+namespace bx {
+
+constexpr int kSub = 1024;               // integers of a subtile
+constexpr int kPerLane = kSub / 64;      // consecutive integers of a lane
+constexpr int kKeyBlock = 1024;          // threads of a workgroup
+constexpr int kKeyWaves = kKeyBlock / 64;
+constexpr uint32_t kRow = kSub * kKeyWaves;  // integers of a row of subtiles
+constexpr uint32_t kKeyChunk = 1u << 18;
+constexpr uint32_t kKeyLen = 1u << 17;
+constexpr uint32_t kKeySubs = kKeyLen / kSub;
+constexpr uint32_t kMidMax = 1u << 16;    // powers up to here are hit through static slots
+constexpr int kMidPer = 2;                // of them per thread (1974 slots at kKeyLen)
+constexpr uint32_t kHitMax = 2304;        // hits of a block held in LDS (about 2030 at 2^42)
+constexpr uint32_t kSparseMax = 512;      // hits of a chunk by powers above kMidMax (about 200)
+constexpr uint32_t kKeySpill = 1u << 15;  // per workgroup in device memory: hits past kSparseMax, then past kHitMax
+constexpr uint32_t kRecMax = 128;         // kept integers a wave turns into words at once
+constexpr int kCellPitch = kSub + 4;      // cells 0 .. kSub of a subtile
+constexpr int kBitPitch = kSub / 32 + 2;  // bits 0 .. kSub
+constexpr uint32_t kQueueSlots = 8192;    // words in the bucket queues, together
+constexpr int kRunMaxLog = 6;             // the longest run a queue writes out: 64 words
+
+// The powers with a static slot per multiple in a subtile (73 slots, in two
+// rounds); 27 stands for 27, 81, 243 and 729 (lut3).  Every odd power up to
+// kFixedQMax, and 729, has its slot here or is in s(x).
+constexpr uint32_t kFixedQMax = 361;
+constexpr int kFixed = 7, kFixedSlots = 73, kFixedPer = 2;
+__device__ constexpr uint16_t kFixedQ[kFixed] = {27, 125, 343, 121, 169, 289, 361};
+__device__ constexpr uint8_t kFixedP[kFixed] = {3, 5, 7, 11, 13, 17, 19};
+
+// A multiple of a power kFixedQMax < q <= kMidMax: jq = j * q past the power's
+// first multiple in a block.  (Slots that stand for nothing have jq = 2^31.)
+struct MidSlot {
+  double q, invq;
+  uint32_t jq, p;
+};
+// A power above kMidMax; the table ends in entries with q = infinity.  invq is
+// 1 / q less 2^-46 of it, so that ceil(S * invq) is the number of the first
+// multiple at or after S for every S < 2^42, also when q divides S.
+struct SparsePow {
+  double q, invq;
+};
+
+struct KeyParams {
+  const Query* queries;
+  const uint64_t* seg_prefix;  // n_queries + 1: first segment of each query
+  uint32_t n_queries;
+  uint64_t n_segs;
+  uint32_t seg_len;
+  const MidSlot* mid;
+  const SparsePow* sp;
+  const uint32_t* sp_p;  // their primes
+  uint64_t* spill;       // kKeySpill words per workgroup
+  uint32_t* flags;
+  int batch;
+  uint32_t prune;    // drop x that cannot be a member of any pair (may_pair)
+  uint32_t pfilter;  // keep x only when pass_hash(key) is in [ph_lo, ph_hi)
+  uint64_t ph_lo, ph_hi;
+  uint32_t b1bits;   // first-level bucket = low b1bits bits of key64
+  uint32_t li_bits;  // words: L1Word
+  uint64_t kl_mask;
+  uint64_t* l1;    // region (b, w) of bucket b written by workgroup w: l1 + (b * gridDim.x + w) * cap1
+  uint64_t cap1;   // words per region (a multiple of 64)
+  uint32_t* cnt1;  // B1 x gridDim.x fill counts, written at the end of the kernel
+};
+
+// LDS of the workgroup.  The queues: bucket b has the 2^(13 - b1bits) slots
+// from b << (13 - b1bits); an empty slot holds kNoWord.
+struct KeySh {
+  __align__(16) uint32_t cell[kKeyWaves * kCellPitch];
+  uint64_t queue[kQueueSlots];
+  __align__(16) double2 small_f[64];  // s(x), s(x + 1) by 9 | x, 9 | x + 1, 25 | x, ...
+  uint64_t sparse[kSparseMax];        // position in the chunk | p << 19
+  uint32_t bits[kKeyWaves * kBitPitch], cbits[kKeyWaves * kBitPitch];
+  uint32_t hits[kHitMax];             // position in the subtile | p << 11, by subtile
+  uint32_t hcnt[kKeySubs + 1];        // hits per subtile, then their first index
+  uint32_t cur[kB1Max];               // words claimed per bucket
+  uint32_t sparse_n, spill_n;
+  uint16_t rec[kKeyWaves * kRecMax];  // kept integers of each wave's subtile
+  // By x mod 729, for 27 | x: 3^(v-2), v = min(v_3(x), 6).  By x mod 225 and
+  // x mod 49: the bits of small_f.  (Long enough to need no reduction.)
+  uint8_t lut3[729 + kSub + 3], lut225[225 + kSub + 3], lut49[49 + kSub + 3];
+};
+static_assert(sizeof(KeySh) <= 160 * 1024, "LDS of a CU");
+
+// (-S) mod q for S < 2^42 as a double: the offset of the first multiple at or
+// after S (invq as in SparsePow).
+__device__ __forceinline__ double first_multiple(double S, double q, double invq) {
+  return __builtin_fma(__builtin_ceil(S * invq), q, -S);
+}
+__device__ __forceinline__ uint32_t first_multiple_small(double S, uint32_t q) {
+  const double qd = static_cast<double>(q);
+  return static_cast<uint32_t>(first_multiple(S, qd, (1.0 / qd) * (1.0 - 0x1p-46)));
+}
+
+// This thread's index, not to be hoisted: addresses made from it are made where
+// they are used, so that they take no registers in the rows.
+__device__ __forceinline__ uint32_t thread_here() {
+  uint32_t t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Waits until this wave's loads and stores are done (vmcnt 0).
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// a * b, or 0 (which stays 0) once the product passes 32 bits.
+__device__ __forceinline__ uint32_t mul_or_zero(uint32_t a, uint32_t b) { return __umulhi(a, b) ? 0u : a * b; }
+
+// Multiplies a cell of this wave by v.  Two lanes may hit one cell at once:
+// each exchange leaves the product of the cell and of the values in the lanes'
+// hands unchanged, and a lane is done when it got 1 back.  Returns the value
+// it left: the last lane to finish leaves the whole product.
+__device__ __forceinline__ uint32_t mul_cell(uint32_t* cell, uint32_t v) {
+  uint32_t old = atomicExch(cell, v);
+  while (old != 1u) {
+    v = mul_or_zero(old, atomicExch(cell, 1u));
+    old = atomicExch(cell, v);
+  }
+  return v;
+}
+
+// The rare x whose cell passed 32 bits: then rad(x) < 2^10 * 2 * 105, every
+// prime of E(x) is at most x / E(x) < 2^10, and dividing out the primes below
+// 2^10 leaves 1 or a product of primes dividing x once.
+__device__ __attribute__((noinline)) uint64_t rad_by_division(uint64_t x) {
+  uint64_t r = 1;
+  if ((x & 1) == 0) {
+    r = 2;
+    x >>= __builtin_ctzll(x);
+  }
+  for (uint32_t d = 3; d < 1024; d += 2) {
+    if (x % d) continue;
+    r *= d;
+    while (x % d == 0) x /= d;
+  }
+  return r * x;
+}
+
+// Hands the words of this wave's lanes (those with `keep`) to their buckets.
+//
+// A word claims the next place `pos` of its bucket, which is its index in this
+// workgroup's region as well, and goes into the queue's slot pos mod slots.
+// Whoever claims the last place of a run (half a queue, at most 64 words)
+// writes the run out: one lane per slot takes the slot's word and stores it,
+// so the stores of a run are consecutive and, runs being aligned, full lines
+// or halves of them.  A slot passes from word to word by compare-and-swap
+// (empty -> word) and exchange (word -> empty).  A lane that finds its slot
+// still taken, or not yet filled, tries again; each round of the loop tries
+// all of them, and the oldest run's words never wait for anything, so the loop
+// ends.  (A word may be taken with a neighbouring run of its bucket: the
+// region is an unordered list.)
+__device__ __forceinline__ void put_words(KeySh& sh, const KeyParams& P, bool keep, uint32_t bk, uint64_t word) {
+  const uint32_t lane = lane_id();
+  const uint32_t slog = 13 - P.b1bits, smask = (1u << slog) - 1u;
+  const uint32_t hlog = min(slog - 1u, static_cast<uint32_t>(kRunMaxLog)), hmask = (1u << hlog) - 1u;
+  uint32_t pos = 0;
+  if (P.b1bits == 0) {  // one bucket: claimed for the wave at once
+    const uint64_t m = __ballot(keep);
+    uint32_t base = 0;
+    if (lane == 0) base = atomicAdd(&sh.cur[0], static_cast<uint32_t>(__popcll(m)));
+    pos = __builtin_amdgcn_readfirstlane(base) + static_cast<uint32_t>(__popcll(m & ((1ull << lane) - 1ull)));
+  } else if (keep) {
+    pos = atomicAdd(&sh.cur[bk], 1u);
+  }
+  unsigned long long* const queue = reinterpret_cast<unsigned long long*>(sh.queue);
+  unsigned long long* const mine = queue + ((bk << slog) + (pos & smask));
+  uint64_t runs = __ballot(keep && (pos & hmask) == hmask);  // lanes with a run to write out
+  bool put = keep, take = false;
+  unsigned long long* from = queue;
+  uint64_t* to = P.l1;
+  bool fits = true;
+  for (;;) {
+    if (put) put = atomicCAS(mine, kNoWord, word) != kNoWord;
+    if (runs && !__any(take)) {  // the next 64 >> hlog runs, one lane per word
+      const uint32_t rank = static_cast<uint32_t>(__popcll(runs & ((1ull << lane) - 1ull)));
+      const uint32_t n = min(static_cast<uint32_t>(__popcll(runs)), 64u >> hlog);
+      const bool give = (runs >> lane) & 1ull && rank < n;
+      // Lane `rank` gets the run's bucket and place, then the run's lanes do.
+      // (The others push to lane 63, which no run with more than one word is
+      // read from: n <= 32.)
+      const int dst = give ? static_cast<int>(rank) * 4 : 63 * 4;
+      const int gp = __builtin_amdgcn_ds_permute(dst, static_cast<int>(pos));
+      const int gb = __builtin_amdgcn_ds_permute(dst, static_cast<int>(bk));
+      const int src = static_cast<int>(lane >> hlog) * 4;
+      const uint32_t rp = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, gp)) - hmask + (lane & hmask);
+      const uint32_t rb = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, gb));
+      runs = __ballot((runs >> lane) & 1ull && rank >= n);
+      take = (lane >> hlog) < n;
+      from = queue + (take ? (rb << slog) + (rp & smask) : 0u);
+      fits = !take || rp < P.cap1;
+      to = P.l1 + (static_cast<uint64_t>(rb) * gridDim.x + blockIdx.x) * P.cap1 + rp;
+      if (__any(!fits) && lane == 0) atomicOr(&P.flags[kFlagL1Overflow], 1u);
+    }
+    if (take) {
+      const unsigned long long w = atomicExch(from, kNoWord);
+      take = w == kNoWord;
+      if (!take && fits) *to = w;
+    }
+    if (!__any(put || take) && !runs) break;
+  }
+}
+
+// One workgroup per CU walks its segments (s mod gridDim.x).
+__global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
+  __shared__ KeySh sh;
+  const uint32_t lane = lane_id();
+  const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t* cell = sh.cell + wid * kCellPitch;
+  uint32_t* bits = sh.bits + wid * kBitPitch;
+  uint32_t* cbits = sh.cbits + wid * kBitPitch;
+  uint16_t* rec = sh.rec + wid * kRecMax;
+  {
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t i = tid; i < kKeyWaves * kCellPitch; i += kKeyBlock) sh.cell[i] = 1u;
+    for (uint32_t i = tid; i < kQueueSlots; i += kKeyBlock) sh.queue[i] = kNoWord;
+    for (uint32_t i = tid; i < kKeyWaves * kBitPitch; i += kKeyBlock) sh.bits[i] = sh.cbits[i] = 0u;
+    for (uint32_t i = tid; i < sizeof(sh.lut3); i += kKeyBlock) {
+      const uint32_t t = i % 729;
+      sh.lut3[i] = t == 0 ? 81 : t % 243 == 0 ? 27 : t % 81 == 0 ? 9 : 3;
+    }
+    for (uint32_t i = tid; i < sizeof(sh.lut225); i += kKeyBlock)
+      sh.lut225[i] = (i % 9 == 0 ? 1 : 0) | (i % 9 == 8 ? 2 : 0) | (i % 25 == 0 ? 4 : 0) | (i % 25 == 24 ? 8 : 0);
+    for (uint32_t i = tid; i < sizeof(sh.lut49); i += kKeyBlock)
+      sh.lut49[i] = (i % 49 == 0 ? 16 : 0) | (i % 49 == 48 ? 32 : 0);
+    if (tid < 64) {
+      const uint32_t b = tid;
+      sh.small_f[b].x = (b & 1 ? 3.0 : 1.0) * (b & 4 ? 5.0 : 1.0) * (b & 16 ? 7.0 : 1.0);
+      sh.small_f[b].y = (b & 2 ? 3.0 : 1.0) * (b & 8 ? 5.0 : 1.0) * (b & 32 ? 7.0 : 1.0);
+    }
+    for (uint32_t b = tid; b < kB1Max; b += kKeyBlock) sh.cur[b] = 0;
+  }
+  // This lane's static slots: a power's multiple slot_jq past its first one in
+  // the subtile.
+  uint32_t slot_q[kFixedPer], slot_jq[kFixedPer], slot_p[kFixedPer], slot_adv[kFixedPer];
+#pragma unroll
+  for (int u = 0; u < kFixedPer; ++u) {
+    slot_q[u] = slot_jq[u] = slot_adv[u] = 0;
+    slot_p[u] = 1;
+    uint32_t first = 0;
+    const uint32_t t = lane + 64 * u;
+#pragma unroll
+    for (int k = 0; k < kFixed; ++k) {
+      const uint32_t q = kFixedQ[k], n = kSub / q + 1;
+      if (t >= first && t < first + n) {
+        slot_q[u] = q;
+        slot_jq[u] = (t - first) * q;
+        slot_p[u] = kFixedP[k];
+        slot_adv[u] = kRow % q;
+      }
+      first += n;
+    }
+  }
+  constexpr uint32_t kFree = 64 * kFixedPer - kFixedSlots;  // lanes of the last round left for listed hits
+  uint64_t* spill = P.spill + static_cast<uint64_t>(blockIdx.x) * kKeySpill;
+  constexpr uint32_t kSpillHalf = kKeySpill / 2;
+
+  uint64_t li0 = 0;  // index of the segment's first integer in this workgroup's sequence
+  for (uint64_t s = blockIdx.x; s < P.n_segs; s += gridDim.x, li0 += P.seg_len) {
+    // Segment s -> its query: the prefix is searched 64 entries at a time.
+    uint32_t qlo = 0, qn = P.n_queries;
+    while (qn > 1) {
+      const uint32_t step = (qn + 63) / 64;
+      const uint32_t at = lane * step;
+      const uint64_t m = __ballot(at < qn && P.seg_prefix[qlo + (at < qn ? at : 0u)] <= s);
+      const uint32_t k = static_cast<uint32_t>(__popcll(m)) - 1;  // lane 0 always holds
+      qlo += k * step;
+      qn = min(step, qn - k * step);
+    }
+    const uint32_t qi = __builtin_amdgcn_readfirstlane(qlo);
+    const uint64_t qa = P.queries[qi].a, qb = P.queries[qi].b;
+    const uint64_t seg0 = qa + (s - P.seg_prefix[qi]) * static_cast<uint64_t>(P.seg_len);
+    const uint64_t seg1 = min(seg0 + P.seg_len, qb);
+    const uint32_t grp = P.batch ? qi : 0u;
+
+    for (uint64_t start = seg0; start < seg1; start += kKeyLen) {
+      const uint32_t tid = thread_here();
+      const uint32_t len = static_cast<uint32_t>(min(static_cast<uint64_t>(kKeyLen), seg1 - start));
+      const uint32_t nsub = (len + kSub - 1) / kSub;
+      const double S = static_cast<double>(start);
+      // 1. Every second block begins a chunk: the hits of the powers above
+      // kMidMax on its positions 0 .. chunk length, one multiple each (up to
+      // four of the smallest).  Each round's powers are read while the round
+      // before is at work.
+      const uint32_t c0 = static_cast<uint32_t>((start - seg0) % kKeyChunk);  // the block's place in the chunk
+      MidSlot m[kMidPer];
+#pragma unroll
+      for (int u = 0; u < kMidPer; ++u) m[u] = P.mid[tid + u * kKeyBlock];
+      if (tid < kKeySubs) sh.hcnt[tid] = 0;
+      if (c0 == 0) {
+        if (tid == 0) sh.sparse_n = 0;
+        __syncthreads();
+        const double Lc = static_cast<double>(min(static_cast<uint64_t>(kKeyChunk), seg1 - start)), Vd = S + Lc;
+        SparsePow wn[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) wn[u] = P.sp[tid + u * kKeyBlock];
+        for (uint32_t i0 = tid;; i0 += 4 * kKeyBlock) {
+          SparsePow w[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) w[u] = wn[u];
+          if (__all(w[0].q > Vd)) break;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) wn[u] = P.sp[i0 + (4 + u) * kKeyBlock];
+          double j[4];
+          bool any = false;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            j[u] = first_multiple(S, w[u].q, w[u].invq);  // not a number for q = infinity
+            any |= j[u] <= Lc;
+          }
+          if (any) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              for (; j[u] <= Lc; j[u] += w[u].q) {
+                const uint64_t e = static_cast<uint32_t>(j[u]) | (static_cast<uint64_t>(P.sp_p[i0 + u * kKeyBlock]) << 19);
+                const uint32_t k = atomicAdd(&sh.sparse_n, 1u);
+                if (k < kSparseMax)
+                  sh.sparse[k] = e;
+                else if (k - kSparseMax < kSpillHalf)
+                  spill[k - kSparseMax] = e;
+                else
+                  atomicOr(&P.flags[kFlagSpillOverflow], 1u);
+              }
+            }
+          }
+        }
+      }
+      if (tid == 0) sh.spill_n = 0;
+      __syncthreads();
+      // 2. The block's hits by subtile: positions 0 .. len of the multiples of
+      // the powers above kFixedQMax (but 729), counted, then placed.  A hit on
+      // the first integer of a subtile also belongs to the subtile before (as
+      // its last value, x + 1 of its last x).
+      const uint32_t nsp = min(sh.sparse_n, kSparseMax + kSpillHalf);
+      auto sparse_at = [&](uint32_t k, uint32_t* pos, uint32_t* p) {  // whether hit k falls in the block
+        const uint64_t e = k < kSparseMax ? sh.sparse[k] : spill[k - kSparseMax];
+        *pos = (static_cast<uint32_t>(e) & 0x7FFFFu) - c0;
+        *p = static_cast<uint32_t>(e >> 19);
+        return *pos <= len;  // (a hit before the block wraps around)
+      };
+      constexpr int kOwn = kMidPer + 1;  // this thread's slots, and one listed hit
+      uint32_t hpos[kOwn], hp[kOwn], hrank[kOwn], hdup[kOwn];
+#pragma unroll
+      for (int u = 0; u < kMidPer; ++u) {
+        const uint32_t pos = static_cast<uint32_t>(first_multiple(S, m[u].q, m[u].invq)) + m[u].jq;
+        hpos[u] = pos <= len ? pos : ~0u;
+        hp[u] = m[u].p;
+      }
+      hpos[kMidPer] = ~0u;
+      if (tid < nsp && !sparse_at(tid, &hpos[kMidPer], &hp[kMidPer])) hpos[kMidPer] = ~0u;
+      auto count = [&](uint32_t pos, uint32_t* rank, uint32_t* dup) {
+        const uint32_t sub = pos / kSub;
+        if (sub < nsub) *rank = atomicAdd(&sh.hcnt[sub], 1u);
+        if (pos % kSub == 0 && pos) *dup = atomicAdd(&sh.hcnt[sub - 1], 1u);
+      };
+#pragma unroll
+      for (int u = 0; u < kOwn; ++u)
+        if (hpos[u] != ~0u) count(hpos[u], &hrank[u], &hdup[u]);
+      __syncthreads();
+      if (wid == 0) {
+        static_assert(kKeySubs == 128, "two counts per lane");
+        const uint32_t n0 = sh.hcnt[2 * lane], n1 = sh.hcnt[2 * lane + 1];
+        const uint32_t end = wave_inclusive_scan(n0 + n1);
+        sh.hcnt[2 * lane] = end - n0 - n1;
+        sh.hcnt[2 * lane + 1] = end - n1;
+        if (lane == 63) sh.hcnt[kKeySubs] = end;
+      }
+      __syncthreads();
+      // Hits past kHitMax go to the second half of the spill, which every
+      // subtile then reads: position in the subtile | subtile << 11 | p << 21.
+      auto put_spill = [&](uint32_t sub, uint32_t at, uint32_t p) {
+        const uint32_t o = atomicAdd(&sh.spill_n, 1u);
+        if (o < kSpillHalf)
+          spill[kSpillHalf + o] = at | (sub << 11) | (static_cast<uint64_t>(p) << 21);
+        else
+          atomicOr(&P.flags[kFlagSpillOverflow], 1u);
+      };
+      auto place = [&](uint32_t pos, uint32_t p, uint32_t rank, uint32_t dup) {
+        auto put = [&](uint32_t sub, uint32_t at, uint32_t o) {
+          if (o < kHitMax)
+            sh.hits[o] = at | (p << 11);
+          else
+            put_spill(sub, at, p);
+        };
+        const uint32_t sub = pos / kSub;
+        if (sub < nsub) put(sub, pos % kSub, sh.hcnt[sub] + rank);
+        if (pos % kSub == 0 && pos) put(sub - 1, kSub, sh.hcnt[sub - 1] + dup);
+      };
+#pragma unroll
+      for (int u = 0; u < kOwn; ++u)
+        if (hpos[u] != ~0u) place(hpos[u], hp[u], hrank[u], hdup[u]);
+      for (uint32_t k = tid + kKeyBlock; k < nsp; k += kKeyBlock) {  // a chunk with more hits than threads
+        uint32_t pos, p;
+        if (!sparse_at(k, &pos, &p)) continue;
+        if (pos / kSub < nsub) put_spill(pos / kSub, pos % kSub, p);
+        if (pos % kSub == 0 && pos) put_spill(pos / kSub - 1, kSub, p);
+      }
+      __syncthreads();
+      const uint32_t nspill = min(sh.spill_n, kSpillHalf);
+      // Nothing the rows need is in flight: said here, so that no wait for
+      // memory (for the stores of words, then) falls inside the rows.
+      wait_loads();
+
+      // 3. The wave's residues at its first subtile, then advanced by a row.
+      const double Sw = S + static_cast<double>(wid * kSub);
+      uint32_t f[kFixedPer];
+#pragma unroll
+      for (int u = 0; u < kFixedPer; ++u) f[u] = slot_q[u] ? first_multiple_small(Sw, slot_q[u]) : 0u;
+      const double Sl = Sw + static_cast<double>(kPerLane * lane);
+      uint32_t r9 = first_multiple_small(Sl, 9), r25 = first_multiple_small(Sl, 25), r49 = first_multiple_small(Sl, 49);
+      auto residue = [&](uint32_t q) {
+        return __builtin_amdgcn_readfirstlane((q - first_multiple_small(Sw, q)) % q);
+      };
+      uint32_t o729 = residue(729), o225 = residue(225), o49 = residue(49);
+      const uint32_t c4 = 0x11111u << ((4u - (static_cast<uint32_t>(start) & 3u)) & 3u);
+      for (uint32_t sub = wid; sub < nsub; sub += kKeyWaves) {
+        const uint64_t x0 = start + static_cast<uint64_t>(sub) * kSub;
+        const double x0d = S + static_cast<double>(sub * kSub);
+        const uint32_t cntv = min(static_cast<uint32_t>(kSub), len - sub * kSub);
+        const bool lower = P.prune && (x0 <= 3 || x0 <= (qb >> 1));
+        // Below b / 2 a squarefree y of {x, x + 1} with y * M <= b is kept
+        // too, M = max(2, rad(z) - 1) of its neighbour z: then e(z) >= ethr.
+        // With ethr small every x with a non-squarefree neighbour is looked
+        // at; else those next to a z with 105 * 2^(a-1) * E(z) >= ethr, marked
+        // in cbits.
+        float ethr = 0.f;
+        uint32_t look = 0;  // 0: the bits decide, 1: all, 2: one non-squarefree, 3: marked
+        if (!P.prune) look = 1;
+        if (lower) {
+          const double bd = static_cast<double>(qb);
+          ethr = static_cast<float>(0.99 * x0d / (bd / x0d + 1.0));
+          look = x0d * x0d <= bd + 8 ? 1 : ethr < 16384.f ? 2 : 3;
+        }
+        auto hit = [&](uint32_t pos, uint32_t v) {
+          const uint32_t e = mul_cell(&cell[pos], v);
+          atomicOr(&bits[pos >> 5], 1u << (pos & 31u));
+          if (look == 3) {
+            const uint64_t z = x0 + pos;
+            const int a1 = (z & 1) ? 0 : __builtin_ctzll(z) - 1;
+            if (e == 0 || static_cast<float>(e) * 105.f * __builtin_ldexpf(1.f, a1) >= ethr)
+              atomicOr(&cbits[pos >> 5], 1u << (pos & 31u));
+          }
+        };
+        {
+          const uint32_t h0 = min(sh.hcnt[sub], kHitMax), h1 = min(sh.hcnt[sub + 1], kHitMax);
+          // Two rounds: the static slots, then the listed hits in the lanes
+          // that have none.
+          uint32_t pos[kFixedPer], v[kFixedPer];
+          bool on[kFixedPer];
+#pragma unroll
+          for (int u = 0; u < kFixedPer; ++u) {
+            pos[u] = f[u] + slot_jq[u];
+            v[u] = slot_p[u];
+            on[u] = pos[u] <= kSub;
+            if (slot_p[u] == 3) v[u] = sh.lut3[min(pos[u] + o729, 728u + kSub)];
+          }
+          {
+            constexpr int u = kFixedPer - 1;
+            if (lane >= 64 - kFree) {
+              const uint32_t hi = h0 + lane - (64 - kFree);
+              on[u] = hi < h1;
+              const uint32_t e = sh.hits[on[u] ? hi : 0u];
+              pos[u] = e & 2047u;
+              v[u] = e >> 11;
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < kFixedPer; ++u)
+            if (on[u]) hit(pos[u], v[u]);
+          for (uint32_t h = h0 + kFree + lane; __any(h < h1); h += 64) {
+            if (h < h1) {
+              const uint32_t e = sh.hits[h];
+              hit(e & 2047u, e >> 11);
+            }
+          }
+          if (nspill) {
+            for (uint32_t h = lane; h < nspill; h += 64) {
+              const uint64_t e = spill[kSpillHalf + h];
+              if ((static_cast<uint32_t>(e >> 11) & 0x3FFu) == sub)
+                hit(static_cast<uint32_t>(e) & 0x7FFu, static_cast<uint32_t>(e >> 21));
+            }
+            wait_loads();
+          }
+        }
+        wave_sync();
+        // Kept bits of this lane's integers X .. X + kPerLane - 1.
+        constexpr uint32_t kLaneMask = (1u << kPerLane) - 1u;
+        const uint16_t* bb = reinterpret_cast<const uint16_t*>(bits);
+        static_assert(kPerLane == 16, "one halfword of bits per lane");
+        const uint32_t ns = bb[lane] | (static_cast<uint32_t>(bb[lane + 1]) << 16) | c4 | (0x201u << r9) | (1u << r25) |
+                            (1u << min(r49, 31u));
+        uint32_t K = ns & (ns >> 1);
+        if (look) {  // uniform
+          if (look == 1) {
+            K = kLaneMask;
+          } else if (look == 2) {
+            K = ns | (ns >> 1);
+          } else {
+            const uint16_t* cb = reinterpret_cast<const uint16_t*>(cbits);
+            uint32_t C = cb[lane] | (static_cast<uint32_t>(cb[lane + 1]) << 16);
+            // Powers of two alone: z = 0 mod 8 with 105 * 2^(a-1) >= ethr.
+            const uint64_t X = x0 + kPerLane * lane;
+            for (uint32_t k = static_cast<uint32_t>(-static_cast<int64_t>(X)) & 7u; k <= kPerLane; k += 8)
+              if (105.f * __builtin_ldexpf(1.f, __builtin_ctzll(X + k) - 1) >= ethr) C |= 1u << k;
+            K |= C | (C >> 1);
+          }
+        }
+        const uint32_t left = cntv > kPerLane * lane ? cntv - kPerLane * lane : 0u;
+        K &= left >= kPerLane ? kLaneMask : (1u << left) - 1u;
+        const uint32_t pc = __popc(K);
+        const uint32_t inc = wave_inclusive_scan(pc);
+        const uint32_t total = __builtin_amdgcn_readlane(inc, 63);
+        const uint64_t li = li0 + (x0 - seg0);
+        for (uint32_t rb = 0; rb < total; rb += kRecMax) {
+          {
+            uint32_t kt = K, slot = inc - pc - rb;
+            if (total <= kRecMax) {
+              while (kt) {
+                rec[slot++] = static_cast<uint16_t>(kPerLane * lane + __builtin_ctz(kt));
+                kt &= kt - 1;
+              }
+            } else {
+              for (; kt; ++slot, kt &= kt - 1)
+                if (slot < kRecMax) rec[slot] = static_cast<uint16_t>(kPerLane * lane + __builtin_ctz(kt));
+            }
+          }
+          wave_sync();
+          const uint32_t nrec = min(total - rb, kRecMax);
+          for (uint32_t q0 = 0; q0 < nrec; q0 += 64) {
+            bool keep = q0 + lane < nrec;
+            const uint32_t i = rec[keep ? q0 + lane : 0u];
+            const uint32_t E0 = cell[i], E1 = cell[i + 1];
+            const double2 sf = sh.small_f[sh.lut225[i + o225] | sh.lut49[i + o49]];
+            const uint64_t x = x0 + i;
+            const double xd = x0d + static_cast<double>(i);
+            // The even one of x, x + 1 gets its factor 2^(a-1).
+            const uint32_t odd = static_cast<uint32_t>(x) & 1u;
+            const uint64_t ev = x + odd;
+            const int a1 = (static_cast<uint32_t>(ev) ? __builtin_ctz(static_cast<uint32_t>(ev))
+                                                      : 32 + __builtin_ctz(static_cast<uint32_t>(ev >> 32))) - 1;
+            double d0 = static_cast<double>(E0) * sf.x, d1 = static_cast<double>(E1) * sf.y;
+            d0 = __builtin_ldexp(d0, odd ? 0 : a1);
+            d1 = __builtin_ldexp(d1, odd ? a1 : 0);
+            // rad = x / e, an integer below 2^42: one Newton step on the
+            // hardware's reciprocal (2^-46 relative), rounded to the integer
+            // by adding 2^52.
+            double i0 = __builtin_amdgcn_rcp(d0), i1 = __builtin_amdgcn_rcp(d1);
+            i0 = __builtin_fma(i0, __builtin_fma(-d0, i0, 1.0), i0);
+            i1 = __builtin_fma(i1, __builtin_fma(-d1, i1, 1.0), i1);
+            const double q0d = __builtin_fma(xd, i0, 0x1p52), q1d = __builtin_fma(xd + 1.0, i1, 0x1p52);
+            constexpr uint64_t kMant = (1ull << 52) - 1;
+            uint64_t r0 = __builtin_bit_cast(uint64_t, q0d) & kMant, r1 = __builtin_bit_cast(uint64_t, q1d) & kMant;
+            if (keep && (E0 == 0 || E1 == 0)) {
+              if (E0 == 0) r0 = rad_by_division(x);
+              if (E1 == 0) r1 = rad_by_division(x + 1);
+            }
+            const uint64_t klo = r0 < r1 ? r0 : r1, khi = r0 < r1 ? r1 : r0;
+            if (lower) keep = keep && may_pair(x, r0, r1, qb);
+            if (P.pfilter) {
+              const uint64_t ph = pass_hash(klo, khi, grp);
+              keep = keep && ph >= P.ph_lo && ph < P.ph_hi;
+            }
+            const uint64_t h = key64(klo, khi, grp);
+            put_words(sh, P, keep, static_cast<uint32_t>(h) & ((1u << P.b1bits) - 1u),
+                      l1_word(h, P.kl_mask, P.li_bits, li + i));
+          }
+          wave_sync();
+        }
+        // The cells and bits for the next subtile, the residues a row on.
+        for (uint32_t c = lane; c < kCellPitch / 4; c += 64)
+          reinterpret_cast<uint4*>(cell)[c] = make_uint4(1u, 1u, 1u, 1u);
+        if (lane < kBitPitch) bits[lane] = 0u;
+        if (look == 3 && lane < kBitPitch) cbits[lane] = 0u;
+        wave_sync();
+        auto step = [](uint32_t r, uint32_t c, uint32_t q) {
+          const uint32_t t = r - c;
+          return min(t, t + q);
+        };
+#pragma unroll
+        for (int u = 0; u < kFixedPer; ++u) f[u] = step(f[u], slot_adv[u], slot_q[u]);
+        r9 = step(r9, kRow % 9u, 9u);
+        r25 = step(r25, kRow % 25u, 25u);
+        r49 = step(r49, kRow % 49u, 49u);
+        auto sstep = [](uint32_t r, uint32_t c, uint32_t q) { return r + c >= q ? r + c - q : r + c; };
+        o729 = sstep(o729, kRow % 729u, 729u);
+        o225 = sstep(o225, kRow % 225u, 225u);
+        o49 = sstep(o49, kRow % 49u, 49u);
+      }
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  // What the queues still hold: each bucket's last, unfinished run.
+  const uint32_t slog = 13 - P.b1bits, smask = (1u << slog) - 1u;
+  const uint32_t hmask = (1u << min(slog - 1u, static_cast<uint32_t>(kRunMaxLog))) - 1u;
+  for (uint32_t i = threadIdx.x; i < kQueueSlots; i += kKeyBlock) {
+    const uint32_t b = i >> slog, n = sh.cur[b];
+    const uint32_t first = n & ~hmask;  // places of the run: [first, n)
+    const uint32_t k = first + ((i - first) & smask);
+    if (k >= n) continue;
+    if (k < P.cap1)
+      P.l1[(static_cast<uint64_t>(b) * gridDim.x + blockIdx.x) * P.cap1 + k] = sh.queue[i];
+    else
+      atomicOr(&P.flags[kFlagL1Overflow], 1u);
+  }
+  for (uint32_t b = threadIdx.x; b < (1u << P.b1bits); b += kKeyBlock)
+    P.cnt1[static_cast<uint64_t>(b) * gridDim.x + blockIdx.x] = sh.cur[b];
+}
+
+}  // namespace bx

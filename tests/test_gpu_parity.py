@@ -592,6 +592,38 @@ def test_compact_candidates_exact_batched(ctx):
     assert st["candidates"] == st["pairs"] and st["false_candidates"] == 0
 
 
+@pytest.mark.parametrize("a,length", [
+    (1, 1023), (1, 1024), (2, 1025), (5, 16385), (36, (1 << 17) + 1), (1 << 20, (1 << 17) - 1),
+    (3**26 - 5000, 9999),  # cells past 32 bits: 3^26, 11^12
+    (11**12 - 1025, 2050),
+    ((1 << 32) - 777, 2001),  # a multiple of 2^32 inside
+    ((1 << 40) + 3, (1 << 18) + 1), ((1 << 42) - 70002, 70000)])
+def test_key_sieve_edges(ctx, a, length):
+    """The searches' sieve at the edges of its lanes, subtiles, rows, blocks and chunks
+    and at special integers, counted exactly: the entries are the kept integers of the
+    range, and with few fingerprint bits kept the candidates are the pairs of equal keys
+    among them (every integer's key counts), both from the oracle's radicals."""
+    b = a + length
+    say(f"key sieve [{a}, {b})")
+    rad = oracle.radicals(a, b + 1)
+    ctx.set_option("small_max", 0)
+    try:
+        assert ctx.search_range(a, b) == oracle.search_range(a, b)
+        entries = ctx.stats()["entries"]
+        ctx.set_option("fp_bits", 12)
+        ctx.set_option("prune", 0)
+        assert ctx.search_range(a, b) == oracle.search_range(a, b)
+        st = ctx.stats()
+    finally:
+        ctx.set_option("small_max", 8192)
+        ctx.set_option("fp_bits", 0)
+        ctx.set_option("prune", 1)
+    assert entries == join_model.group_keys(rad, a, b, 0, 0, 1, 12)[1]
+    keys, n = join_model.group_keys(rad, a, b, 0, st["b1_bits"], 1, 12, prune=False)
+    assert st["entries"] == st["joined"] == n == length
+    assert st["candidates"] == join_model.candidates(keys)
+
+
 @pytest.mark.parametrize("passes", [1, 2, 3, 5, 7, 16, 64])
 def test_pass_count_invariance(ctx, passes):
     ctx.set_option("passes", passes)
