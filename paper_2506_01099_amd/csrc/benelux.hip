@@ -424,7 +424,11 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
     p.b2bits = b2;
     p.cap2 = static_cast<uint32_t>(
         round_up(static_cast<uint64_t>(std::ceil(bucket * 1.03 / std::ldexp(1.0, static_cast<int>(b2)) * 1.1)) + 128, 16));
-    if (p.cap1 > 0xF0000000ull || p.cap2 > 0xF0000000ull) continue;
+    // The sieve addresses a workgroup's regions, and a bucket's runs, in 32 bits.
+    if ((p.cap1 << b1) >= (1ull << 29) || (p.cap1 >> run_log(b1)) >= (1ull << 22) || p.cap2 > 0xF0000000ull) {
+      if (c->force_passes > 0) return fail(BX_ENOMEM, "forced pass count leaves regions too large");
+      continue;
+    }
     const uint64_t nb1 = 1ull << b1, nb2 = 1ull << b2;
     uint32_t G = c->force_group > 0 ? static_cast<uint32_t>(c->force_group) : 8u;
     if (G > nb1) G = static_cast<uint32_t>(nb1);
@@ -852,11 +856,12 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
   P.pfilter = !(ph_lo == 0 && ph_hi == (1ull << 32));
   P.ph_lo = ph_lo;
   P.ph_hi = ph_hi;
+  P.W = j.sieve_grid;
   P.b1bits = plan.b1bits;
   P.li_bits = j.li_bits;
   P.kl_mask = j.kl_mask;
   P.l1 = static_cast<uint64_t*>(c->l1.p);
-  P.cap1 = plan.cap1;
+  P.cap1 = static_cast<uint32_t>(plan.cap1);
   P.cnt1 = static_cast<uint32_t*>(c->cnt1.p);
   {
     LaunchTimer t(c, K_SIEVE, st);
@@ -880,6 +885,7 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
     Q.cap1 = plan.cap1;
     Q.cnt1 = static_cast<const uint32_t*>(c->cnt1.p);
     Q.W = j.sieve_grid;
+    Q.B1 = j.B1;
     Q.first = first;
     Q.G = j.G;
     Q.chunks_per_region = j.cpr;

@@ -358,8 +358,8 @@ __device__ __forceinline__ uint64_t word_pos43(const WordSource& S, uint32_t w, 
 struct PartParams {
   const uint64_t* l1;
   uint64_t cap1;          // words per first-level region
-  const uint32_t* cnt1;   // B1 x W region fill counts
-  uint32_t W;             // regions per bucket (sieve workgroups)
+  const uint32_t* cnt1;   // W x B1 region fill counts
+  uint32_t W, B1;         // regions per bucket (sieve workgroups), buckets
   uint32_t first;  // first first-level bucket of this group
   uint32_t G;      // buckets in the group: 1, 2, 4 or 8
   uint32_t chunks_per_region;
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(BLOCK) void k_partition(PartParams P) {
   auto bucket_of = [&](uint32_t i) -> uint32_t { return sbk[i]; };
   // Chunk ci of the bucket: entries [s0, s0 + n) of region ci / cpr.
   auto chunk = [&](uint64_t ci, const uint64_t** src) -> uint32_t {  // ci < n_chunks
-    const uint64_t region = static_cast<uint64_t>(b1) * P.W + ci / cpr;
+    const uint64_t region = (ci / cpr) * P.B1 + b1;
     const uint64_t n1 = min(static_cast<uint64_t>(P.cnt1[region]), P.cap1);
     const uint64_t s0 = (ci % cpr) * static_cast<uint64_t>(kPartChunk);
     *src = P.l1 + region * P.cap1 + s0;

@@ -41,7 +41,6 @@ constexpr uint32_t kRecMax = 128;         // kept integers a wave turns into wor
 constexpr int kCellPitch = kSub + 4;      // cells 0 .. kSub of a subtile
 constexpr int kBitPitch = kSub / 32 + 2;  // bits 0 .. kSub
 constexpr uint32_t kQueueSlots = 8192;    // words in the bucket queues, together
-constexpr int kRunMaxLog = 6;             // the longest run a queue writes out: 64 words
 
 // The powers with a static slot per multiple in a subtile (73 slots, in two
 // rounds); 27 stands for 27, 81, 243 and 729 (lut3).  Every odd power up to
@@ -82,10 +81,14 @@ struct KeyParams {
   uint32_t b1bits;   // first-level bucket = low b1bits bits of key64
   uint32_t li_bits;  // words: L1Word
   uint64_t kl_mask;
-  uint64_t* l1;    // region (b, w) of bucket b written by workgroup w: l1 + (b * gridDim.x + w) * cap1
-  uint64_t cap1;   // words per region (a multiple of 64)
-  uint32_t* cnt1;  // B1 x gridDim.x fill counts, written at the end of the kernel
+  uint32_t W;      // workgroups
+  uint64_t* l1;    // region (w, b) of bucket b written by workgroup w: l1 + (w * B1 + b) * cap1
+  uint32_t cap1;   // words per region (a multiple of 64; B1 * cap1 < 2^29)
+  uint32_t* cnt1;  // W x B1 fill counts, written at the end of the kernel
 };
+
+// A queue writes out runs of 2^run_log words: half its slots, at most 64.
+__host__ __device__ constexpr uint32_t run_log(uint32_t b1bits) { return b1bits > 6 ? 12 - b1bits : 6; }
 
 // LDS of the workgroup.  The queues: bucket b has the 2^(13 - b1bits) slots
 // from b << (13 - b1bits); an empty slot holds kNoWord.
@@ -124,23 +127,40 @@ __device__ __forceinline__ uint32_t thread_here() {
   return t;
 }
 
+__device__ __forceinline__ void set_priority(uint32_t p) {  // uniform
+  if (p == 0)
+    __builtin_amdgcn_s_setprio(0);
+  else if (p == 1)
+    __builtin_amdgcn_s_setprio(1);
+  else if (p == 2)
+    __builtin_amdgcn_s_setprio(2);
+  else
+    __builtin_amdgcn_s_setprio(3);
+}
+
 // Waits until this wave's loads and stores are done (vmcnt 0).
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // a * b, or 0 (which stays 0) once the product passes 32 bits.
 __device__ __forceinline__ uint32_t mul_or_zero(uint32_t a, uint32_t b) { return __umulhi(a, b) ? 0u : a * b; }
 
-// Multiplies a cell of this wave by v.  Two lanes may hit one cell at once:
-// each exchange leaves the product of the cell and of the values in the lanes'
-// hands unchanged, and a lane is done when it got 1 back.  Returns the value
-// it left: the last lane to finish leaves the whole product.
-__device__ __forceinline__ uint32_t mul_cell(uint32_t* cell, uint32_t v) {
-  uint32_t old = atomicExch(cell, v);
-  while (old != 1u) {
-    v = mul_or_zero(old, atomicExch(cell, 1u));
-    old = atomicExch(cell, v);
+// Multiplies cells of this wave: cell[pos[u]] by v[u] where on[u].  Two lanes
+// may hit one cell at once: each exchange leaves the product of the cell and
+// of the values in the lanes' hands unchanged, and a lane is done when it got
+// 1 back.  v[u] becomes the value left: the last to finish on a cell leaves the
+// whole product.
+template <int N>
+__device__ __forceinline__ void mul_cells(uint32_t* cell, const uint32_t (&pos)[N], uint32_t (&v)[N], const bool (&on)[N]) {
+  uint32_t old[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) old[u] = on[u] ? atomicExch(&cell[pos[u]], v[u]) : 1u;
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    while (old[u] != 1u) {
+      v[u] = mul_or_zero(old[u], atomicExch(&cell[pos[u]], 1u));
+      old[u] = atomicExch(&cell[pos[u]], v[u]);
+    }
   }
-  return v;
 }
 
 // The rare x whose cell passed 32 bits: then rad(x) < 2^10 * 2 * 105, every
@@ -160,6 +180,13 @@ __device__ __attribute__((noinline)) uint64_t rad_by_division(uint64_t x) {
   return r * x;
 }
 
+__device__ __forceinline__ bool any_lane(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
+
+// Lanes below this one that are in m.
+__device__ __forceinline__ uint32_t rank_in(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+}
+
 // Hands the words of this wave's lanes (those with `keep`) to their buckets.
 //
 // A word claims the next place `pos` of its bucket, which is its index in this
@@ -176,55 +203,50 @@ __device__ __attribute__((noinline)) uint64_t rad_by_division(uint64_t x) {
 __device__ __forceinline__ void put_words(KeySh& sh, const KeyParams& P, bool keep, uint32_t bk, uint64_t word) {
   const uint32_t lane = lane_id();
   const uint32_t slog = 13 - P.b1bits, smask = (1u << slog) - 1u;
-  const uint32_t hlog = min(slog - 1u, static_cast<uint32_t>(kRunMaxLog)), hmask = (1u << hlog) - 1u;
+  const uint32_t hlog = run_log(P.b1bits), hmask = (1u << hlog) - 1u, most = 64u >> hlog;
+  unsigned long long* const queue = reinterpret_cast<unsigned long long*>(sh.queue);
   uint32_t pos = 0;
   if (P.b1bits == 0) {  // one bucket: claimed for the wave at once
-    const uint64_t m = __ballot(keep);
+    const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
     uint32_t base = 0;
     if (lane == 0) base = atomicAdd(&sh.cur[0], static_cast<uint32_t>(__popcll(m)));
-    pos = __builtin_amdgcn_readfirstlane(base) + static_cast<uint32_t>(__popcll(m & ((1ull << lane) - 1ull)));
+    pos = __builtin_amdgcn_readfirstlane(base) + rank_in(m);
   } else if (keep) {
     pos = atomicAdd(&sh.cur[bk], 1u);
   }
-  unsigned long long* const queue = reinterpret_cast<unsigned long long*>(sh.queue);
-  unsigned long long* const mine = queue + ((bk << slog) + (pos & smask));
-  uint64_t runs = __ballot(keep && (pos & hmask) == hmask);  // lanes with a run to write out
+  unsigned long long* const slot = queue + ((bk << slog) + (pos & smask));
+  uint64_t runs = __builtin_amdgcn_ballot_w64(keep && (pos & hmask) == hmask);  // lanes with a run to write out
   bool put = keep, take = false;
   unsigned long long* from = queue;
-  uint64_t* to = P.l1;
-  bool fits = true;
+  uint32_t to = ~0u;
+  uint64_t* const mine = P.l1 + blockIdx.x * (static_cast<uint64_t>(P.cap1) << P.b1bits);
   for (;;) {
-    if (put) put = atomicCAS(mine, kNoWord, word) != kNoWord;
-    if (runs && !__any(take)) {  // the next 64 >> hlog runs, one lane per word
-      const uint32_t rank = static_cast<uint32_t>(__popcll(runs & ((1ull << lane) - 1ull)));
-      const uint32_t n = min(static_cast<uint32_t>(__popcll(runs)), 64u >> hlog);
-      const bool give = (runs >> lane) & 1ull && rank < n;
-      // Lane `rank` gets the run's bucket and place, then the run's lanes do.
-      // (The others push to lane 63, which no run with more than one word is
-      // read from: n <= 32.)
-      const int dst = give ? static_cast<int>(rank) * 4 : 63 * 4;
-      const int gp = __builtin_amdgcn_ds_permute(dst, static_cast<int>(pos));
-      const int gb = __builtin_amdgcn_ds_permute(dst, static_cast<int>(bk));
-      const int src = static_cast<int>(lane >> hlog) * 4;
-      const uint32_t rp = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, gp)) - hmask + (lane & hmask);
-      const uint32_t rb = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, gb));
-      runs = __ballot((runs >> lane) & 1ull && rank >= n);
-      take = (lane >> hlog) < n;
+    if (put) put = atomicCAS(slot, kNoWord, word) != kNoWord;
+    if (runs && !any_lane(take)) {
+      // The next 64 >> hlog runs, one lane per word: lane k gets the k-th
+      // run's bucket and place, then the run's lanes do.  (Lanes without a run
+      // push to lane 63, which is not read from: a run has two words or more.)
+      const uint32_t rank = rank_in(runs);
+      const bool has = (runs >> lane) & 1ull, give = has && rank < most;
+      const int pushed = __builtin_amdgcn_ds_permute(give ? static_cast<int>(rank * 4) : 63 * 4,
+                                                     static_cast<int>(((pos >> hlog) << 10) | bk));
+      const uint32_t run = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(static_cast<int>(lane >> hlog) * 4, pushed));
+      const uint32_t rb = run & 1023u, rp = ((run >> 10) << hlog) + (lane & hmask);
+      take = (lane >> hlog) < static_cast<uint32_t>(__popcll(runs));
+      runs = __builtin_amdgcn_ballot_w64(has && !give);
       from = queue + (take ? (rb << slog) + (rp & smask) : 0u);
-      fits = !take || rp < P.cap1;
-      to = P.l1 + (static_cast<uint64_t>(rb) * gridDim.x + blockIdx.x) * P.cap1 + rp;
-      if (__any(!fits) && lane == 0) atomicOr(&P.flags[kFlagL1Overflow], 1u);
+      to = rp < P.cap1 ? rb * P.cap1 + rp : ~0u;
     }
     if (take) {
       const unsigned long long w = atomicExch(from, kNoWord);
       take = w == kNoWord;
-      if (!take && fits) *to = w;
+      if (!take && to != ~0u) mine[to] = w;  // (a region that overflows is reported at the end)
     }
-    if (!__any(put || take) && !runs) break;
+    if (!any_lane(put || take) && !runs) break;
   }
 }
 
-// One workgroup per CU walks its segments (s mod gridDim.x).
+// One workgroup per CU walks its segments (s mod W).
 __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
   __shared__ KeySh sh;
   const uint32_t lane = lane_id();
@@ -279,7 +301,7 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
   constexpr uint32_t kSpillHalf = kKeySpill / 2;
 
   uint64_t li0 = 0;  // index of the segment's first integer in this workgroup's sequence
-  for (uint64_t s = blockIdx.x; s < P.n_segs; s += gridDim.x, li0 += P.seg_len) {
+  for (uint64_t s = blockIdx.x; s < P.n_segs; s += P.W, li0 += P.seg_len) {
     // Segment s -> its query: the prefix is searched 64 entries at a time.
     uint32_t qlo = 0, qn = P.n_queries;
     while (qn > 1) {
@@ -314,16 +336,20 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
         if (tid == 0) sh.sparse_n = 0;
         __syncthreads();
         const double Lc = static_cast<double>(min(static_cast<uint64_t>(kKeyChunk), seg1 - start)), Vd = S + Lc;
+        // (Read by 32-bit byte offsets from the table's start.)
+        auto power = [&](uint32_t i) {
+          return *reinterpret_cast<const SparsePow*>(reinterpret_cast<const uint8_t*>(P.sp) + i * static_cast<uint32_t>(sizeof(SparsePow)));
+        };
         SparsePow wn[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) wn[u] = P.sp[tid + u * kKeyBlock];
+        for (int u = 0; u < 4; ++u) wn[u] = power(tid + u * kKeyBlock);
         for (uint32_t i0 = tid;; i0 += 4 * kKeyBlock) {
           SparsePow w[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) w[u] = wn[u];
           if (__all(w[0].q > Vd)) break;
 #pragma unroll
-          for (int u = 0; u < 4; ++u) wn[u] = P.sp[i0 + (4 + u) * kKeyBlock];
+          for (int u = 0; u < 4; ++u) wn[u] = power(i0 + (4 + u) * kKeyBlock);
           double j[4];
           bool any = false;
 #pragma unroll
@@ -437,6 +463,10 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
       uint32_t o729 = residue(729), o225 = residue(225), o49 = residue(49);
       const uint32_t c4 = 0x11111u << ((4u - (static_cast<uint32_t>(start) & 3u)) & 3u);
       for (uint32_t sub = wid; sub < nsub; sub += kKeyWaves) {
+        // The SIMD's four waves (wid / 4) take the highest priority in turn:
+        // by age alone the oldest runs ahead, and the block's end waits for
+        // the youngest, which then has the SIMD to itself.
+        set_priority((sub / kKeyWaves + wid / 4) & 3u);
         const uint64_t x0 = start + static_cast<uint64_t>(sub) * kSub;
         const double x0d = S + static_cast<double>(sub * kSub);
         const uint32_t cntv = min(static_cast<uint32_t>(kSub), len - sub * kSub);
@@ -454,8 +484,7 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
           ethr = static_cast<float>(0.99 * x0d / (bd / x0d + 1.0));
           look = x0d * x0d <= bd + 8 ? 1 : ethr < 16384.f ? 2 : 3;
         }
-        auto hit = [&](uint32_t pos, uint32_t v) {
-          const uint32_t e = mul_cell(&cell[pos], v);
+        auto mark = [&](uint32_t pos, uint32_t e) {
           atomicOr(&bits[pos >> 5], 1u << (pos & 31u));
           if (look == 3) {
             const uint64_t z = x0 + pos;
@@ -487,9 +516,17 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
               v[u] = e >> 11;
             }
           }
+          mul_cells(cell, pos, v, on);
 #pragma unroll
           for (int u = 0; u < kFixedPer; ++u)
-            if (on[u]) hit(pos[u], v[u]);
+            if (on[u]) mark(pos[u], v[u]);
+          auto hit = [&](uint32_t at, uint32_t p) {
+            const uint32_t one_pos[1] = {at};
+            uint32_t one_v[1] = {p};
+            const bool one_on[1] = {true};
+            mul_cells(cell, one_pos, one_v, one_on);
+            mark(at, one_v[0]);
+          };
           for (uint32_t h = h0 + kFree + lane; __any(h < h1); h += 64) {
             if (h < h1) {
               const uint32_t e = sh.hits[h];
@@ -534,6 +571,8 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
         const uint32_t inc = wave_inclusive_scan(pc);
         const uint32_t total = __builtin_amdgcn_readlane(inc, 63);
         const uint64_t li = li0 + (x0 - seg0);
+        const uint32_t x0odd = static_cast<uint32_t>(x0) & 1u;
+        const bool wraps = static_cast<uint32_t>(x0) - 1u > 0xFFFFFFFFu - kSub - 1u;  // a multiple of 2^32 near the subtile
         for (uint32_t rb = 0; rb < total; rb += kRecMax) {
           {
             uint32_t kt = K, slot = inc - pc - rb;
@@ -556,42 +595,44 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
             const double2 sf = sh.small_f[sh.lut225[i + o225] | sh.lut49[i + o49]];
             const uint64_t x = x0 + i;
             const double xd = x0d + static_cast<double>(i);
-            // The even one of x, x + 1 gets its factor 2^(a-1).
-            const uint32_t odd = static_cast<uint32_t>(x) & 1u;
-            const uint64_t ev = x + odd;
-            const int a1 = (static_cast<uint32_t>(ev) ? __builtin_ctz(static_cast<uint32_t>(ev))
-                                                      : 32 + __builtin_ctz(static_cast<uint32_t>(ev >> 32))) - 1;
-            double d0 = static_cast<double>(E0) * sf.x, d1 = static_cast<double>(E1) * sf.y;
-            d0 = __builtin_ldexp(d0, odd ? 0 : a1);
-            d1 = __builtin_ldexp(d1, odd ? a1 : 0);
+            // The even one of x, x + 1 has the factor 2^(a-1), half its lowest
+            // set bit (in the low word, but for multiples of 2^32).
+            const uint32_t odd = i & 1u ^ x0odd, ev = static_cast<uint32_t>(x) + odd;
+            double low = static_cast<double>(ev & (0u - ev));
+            if (wraps && ev == 0) low = 0x1p32 * static_cast<double>((x + odd) >> 32 & (0 - ((x + odd) >> 32)));
+            low *= 0.5;
+            const double d0 = static_cast<double>(E0) * sf.x * (odd ? 1.0 : low);
+            const double d1 = static_cast<double>(E1) * sf.y * (odd ? low : 1.0);
             // rad = x / e, an integer below 2^42: one Newton step on the
-            // hardware's reciprocal (2^-46 relative), rounded to the integer
-            // by adding 2^52.
-            double i0 = __builtin_amdgcn_rcp(d0), i1 = __builtin_amdgcn_rcp(d1);
-            i0 = __builtin_fma(i0, __builtin_fma(-d0, i0, 1.0), i0);
-            i1 = __builtin_fma(i1, __builtin_fma(-d1, i1, 1.0), i1);
-            const double q0d = __builtin_fma(xd, i0, 0x1p52), q1d = __builtin_fma(xd + 1.0, i1, 0x1p52);
-            constexpr uint64_t kMant = (1ull << 52) - 1;
-            uint64_t r0 = __builtin_bit_cast(uint64_t, q0d) & kMant, r1 = __builtin_bit_cast(uint64_t, q1d) & kMant;
+            // hardware's reciprocal of both e's product (2^-46 relative),
+            // rounded to the integer by adding 2^52.
+            const double dd = d0 * d1;
+            double ri = __builtin_amdgcn_rcp(dd);
+            ri = __builtin_fma(ri, __builtin_fma(-dd, ri, 1.0), ri);
+            double q0d = __builtin_fma(xd, ri * d1, 0x1p52), q1d = __builtin_fma(xd + 1.0, ri * d0, 0x1p52);
             if (keep && (E0 == 0 || E1 == 0)) {
-              if (E0 == 0) r0 = rad_by_division(x);
-              if (E1 == 0) r1 = rad_by_division(x + 1);
+              q0d = 0x1p52 + static_cast<double>(E0 ? static_cast<uint64_t>(xd / d0) : rad_by_division(x));
+              q1d = 0x1p52 + static_cast<double>(E1 ? static_cast<uint64_t>((xd + 1.0) / d1) : rad_by_division(x + 1));
             }
-            const uint64_t klo = r0 < r1 ? r0 : r1, khi = r0 < r1 ? r1 : r0;
-            if (lower) keep = keep && may_pair(x, r0, r1, qb);
+            constexpr uint64_t kMant = (1ull << 52) - 1;
+            const uint64_t klo = __builtin_bit_cast(uint64_t, __builtin_fmin(q0d, q1d)) & kMant;
+            const uint64_t khi = __builtin_bit_cast(uint64_t, __builtin_fmax(q0d, q1d)) & kMant;
+            if (lower)
+              keep = keep && may_pair(x, __builtin_bit_cast(uint64_t, q0d) & kMant, __builtin_bit_cast(uint64_t, q1d) & kMant, qb);
             if (P.pfilter) {
               const uint64_t ph = pass_hash(klo, khi, grp);
               keep = keep && ph >= P.ph_lo && ph < P.ph_hi;
             }
             const uint64_t h = key64(klo, khi, grp);
-            put_words(sh, P, keep, static_cast<uint32_t>(h) & ((1u << P.b1bits) - 1u),
-                      l1_word(h, P.kl_mask, P.li_bits, li + i));
+            put_words(sh, P, keep, static_cast<uint32_t>(h) & ((1u << P.b1bits) - 1u), l1_word(h, P.kl_mask, P.li_bits, li + i));
           }
           wave_sync();
         }
         // The cells and bits for the next subtile, the residues a row on.
-        for (uint32_t c = lane; c < kCellPitch / 4; c += 64)
-          reinterpret_cast<uint4*>(cell)[c] = make_uint4(1u, 1u, 1u, 1u);
+        static_assert(kCellPitch == 4 * 256 + 4, "four stores per lane and one");
+#pragma unroll
+        for (uint32_t c = 0; c < 4; ++c) reinterpret_cast<uint4*>(cell)[64 * c + lane] = make_uint4(1u, 1u, 1u, 1u);
+        if (lane == 0) reinterpret_cast<uint4*>(cell)[256] = make_uint4(1u, 1u, 1u, 1u);
         if (lane < kBitPitch) bits[lane] = 0u;
         if (look == 3 && lane < kBitPitch) cbits[lane] = 0u;
         wave_sync();
@@ -609,25 +650,25 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
         o225 = sstep(o225, kRow % 225u, 225u);
         o49 = sstep(o49, kRow % 49u, 49u);
       }
+      __builtin_amdgcn_s_setprio(0);
       __syncthreads();
     }
   }
   __syncthreads();
   // What the queues still hold: each bucket's last, unfinished run.
-  const uint32_t slog = 13 - P.b1bits, smask = (1u << slog) - 1u;
-  const uint32_t hmask = (1u << min(slog - 1u, static_cast<uint32_t>(kRunMaxLog))) - 1u;
+  const uint32_t slog = 13 - P.b1bits, smask = (1u << slog) - 1u, hmask = (1u << run_log(P.b1bits)) - 1u;
+  uint64_t* const mine = P.l1 + blockIdx.x * (static_cast<uint64_t>(P.cap1) << P.b1bits);
   for (uint32_t i = threadIdx.x; i < kQueueSlots; i += kKeyBlock) {
     const uint32_t b = i >> slog, n = sh.cur[b];
     const uint32_t first = n & ~hmask;  // places of the run: [first, n)
     const uint32_t k = first + ((i - first) & smask);
-    if (k >= n) continue;
-    if (k < P.cap1)
-      P.l1[(static_cast<uint64_t>(b) * gridDim.x + blockIdx.x) * P.cap1 + k] = sh.queue[i];
-    else
-      atomicOr(&P.flags[kFlagL1Overflow], 1u);
+    if (k < n && k < P.cap1) mine[b * P.cap1 + k] = sh.queue[i];
   }
-  for (uint32_t b = threadIdx.x; b < (1u << P.b1bits); b += kKeyBlock)
-    P.cnt1[static_cast<uint64_t>(b) * gridDim.x + blockIdx.x] = sh.cur[b];
+  for (uint32_t b = threadIdx.x; b < (1u << P.b1bits); b += kKeyBlock) {
+    const uint32_t n = sh.cur[b];
+    P.cnt1[(static_cast<uint64_t>(blockIdx.x) << P.b1bits) + b] = n;
+    if (n > P.cap1) atomicOr(&P.flags[kFlagL1Overflow], 1u);
+  }
 }
 
 }  // namespace bx
