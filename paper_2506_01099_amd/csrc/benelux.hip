@@ -142,7 +142,7 @@ struct bx_ctx {
   hipGraphExec_t graph_exec = nullptr;
   std::string graph_key;
   uint32_t graph_launches[6] = {0, 0, 0, 0, 0, 0};  // kernel launches the graph holds, per kernel
-  uint32_t seg_len = kDefaultSegLen;
+  uint32_t seg_len = kDefaultSegLen;  // the longest segment (fit_seg_len)
   bx_stats stats{};
   std::mutex mu;
   std::vector<hipEvent_t> ev_free;
@@ -261,6 +261,9 @@ int fill_u32(bx_ctx* c, void* p, uint64_t n, uint32_t v, hipStream_t s) {
   return BX_OK;
 }
 
+// 1/q a little low: ceil(S * invq) is then exact for every S < 2^42 (first_multiple).
+double low_inverse(double q) { return 1.0 / q * (1.0 - std::ldexp(1.0, -46)); }
+
 // Prime tables: primes <= isqrt(hi_max) (for verification) and every odd prime
 // power p^k <= hi_max, k >= 2 (Algorithm 1 sieves with exactly these), sorted
 // by q, plus the dense schedules for the powers <= each tile size.
@@ -279,7 +282,8 @@ int build_tables(bx_ctx* c) {
     const uint32_t pinv = inv32_host(p);
     uint64_t q = static_cast<uint64_t>(p) * p;
     while (q <= c->hi_max) {
-      c->pp.push_back(PrimePow{q, 1.0 / static_cast<double>(q), p, pinv});
+      const double qd = static_cast<double>(q);
+      c->pp.push_back(PrimePow{qd, low_inverse(qd), p, pinv});
       if (q > c->hi_max / p) break;
       q *= p;
     }
@@ -314,18 +318,15 @@ int build_tables(bx_ctx* c) {
     BX_HIP(hipMemcpy(c->d_dense[which], &dt, sizeof(DenseTab), hipMemcpyHostToDevice));
   }
   {
-    // 1/q a little low: ceil(S * invq) is then exact for every S < 2^42.
-    auto inv = [](double q) { return 1.0 / q * (1.0 - std::ldexp(1.0, -46)); };
     std::vector<MidSlot> mid;
     std::vector<SparsePow> sp;
     std::vector<uint32_t> sp_p;
     for (const auto& w : c->pp) {
-      const double q = static_cast<double>(w.q);
       if (w.q <= kFixedQMax || w.q == 729) continue;  // the subtile's own slots
       if (w.q <= kMidMax) {
-        for (uint64_t jq = 0; jq <= kKeyLen; jq += w.q) mid.push_back(MidSlot{q, inv(q), static_cast<uint32_t>(jq), w.p});
+        for (uint32_t jq = 0; jq <= kKeyLen; jq += static_cast<uint32_t>(w.q)) mid.push_back(MidSlot{w.q, w.invq, jq, w.p});
       } else {
-        sp.push_back(SparsePow{q, inv(q)});
+        sp.push_back(SparsePow{w.q, w.invq});
         sp_p.push_back(w.p);
       }
     }
@@ -335,7 +336,7 @@ int build_tables(bx_ctx* c) {
     sp.resize(sp.size() + 8 * kKeyBlock, SparsePow{HUGE_VAL, 0.0});
     sp_p.resize(sp.size(), 0);
     // The rest of the slots lie past any block: q = 1 gives offset 0.
-    mid.resize(static_cast<size_t>(kMidPer) * kKeyBlock, MidSlot{1.0, inv(1.0), 1u << 31, 1});
+    mid.resize(static_cast<size_t>(kMidPer) * kKeyBlock, MidSlot{1.0, low_inverse(1.0), 1u << 31, 1});
     BX_HIP(hipMalloc(&c->d_mid, mid.size() * sizeof(MidSlot)));
     BX_HIP(hipMalloc(&c->d_sp, sp.size() * sizeof(SparsePow)));
     BX_HIP(hipMalloc(&c->d_sp_p, sp_p.size() * sizeof(uint32_t)));
@@ -394,6 +395,7 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
   const uint64_t fixed = fixed_bytes(sieve_grid);
   const uint32_t p_first = c->force_passes > 0 ? static_cast<uint32_t>(c->force_passes) : 1;
   const uint32_t p_last = c->force_passes > 0 ? p_first : 4096;
+  const double W = static_cast<double>(sieve_grid);
   for (uint32_t P = p_first; P <= p_last; ++P) {
     Plan p;
     p.passes = P;
@@ -405,6 +407,11 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
     // runs per bucket.
     const double n_pass = std::max(1.0, std::ceil(static_cast<double>(std::min(n_expect, n_keys)) / P));
     uint32_t b1 = std::min<uint32_t>(10, ceil_log2(n_pass * 1.03 / (7600.0 * 2048.0)));
+    // From 2048 entries per region on, at least eight buckets, so that each is
+    // one XCD's and its partitions' lines fill in that XCD's L2: 2.9e7 entries
+    // partition in 0.160 ms with 2^3 x 2^9 against 0.296 with 2 x 2^11.  With
+    // fewer (1.1e5 entries: 18 against 36 us) the regions are too short.
+    if (n_pass >= 8.0 * 2048.0 * W) b1 = std::max(b1, 3u);
     if (c->force_b1 >= 0) b1 = static_cast<uint32_t>(c->force_b1);
     p.b1bits = b1;
     const double bucket = n_pass / std::ldexp(1.0, static_cast<int>(b1));
@@ -415,7 +422,11 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
     // Partitions of at most ~7.6k entries on average: with the bucket-to-bucket
     // spread (3%) and the partition-to-partition spread (a few sigma of ~90)
     // they stay within one LDS join chunk (8192 entries).
+    // A short range splits further, into up to 2^8 partitions of 512 or more:
+    // one workgroup joins a partition, and 16 of them took 11 us for 1.1e5
+    // entries.
     uint32_t b2 = bucket * 1.03 > 7600.0 ? ceil_log2(bucket * 1.03 / 7600.0) : 0;
+    while (b2 < 8 && bucket > 1024.0 * std::ldexp(1.0, static_cast<int>(b2))) ++b2;
     if (c->force_b2 >= 0) b2 = static_cast<uint32_t>(c->force_b2);
     if (b2 > 11 || b1 + b2 > 32) {
       if (c->force_passes > 0) return fail(BX_ENOMEM, "forced pass count leaves partitions too large");
@@ -446,7 +457,26 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
   return fail(BX_ENOMEM, "HBM budget too small for the search");
 }
 
+// Segment length for n integers over `wgs` workgroups: as many equal rounds of
+// all workgroups as segments of at most `longest` need, in multiples of `unit`.
+// Segments of 2^18 left the chip idle on short ranges (2^20 integers at 2^40 on
+// 4 of 256 CUs: sieve 81 us) and ran a last round for a few of them; a short
+// segment repeats the hit list's look at every large power (about 9 us at 2^40),
+// so those of a range run side by side.
+uint32_t fit_seg_len(uint64_t n, uint64_t wgs, uint32_t longest, uint32_t unit) {
+  const uint64_t rounds = std::max<uint64_t>(1, (n + wgs * longest - 1) / (wgs * longest));
+  const uint64_t len = round_up(std::max<uint64_t>(1, (n + wgs * rounds - 1) / (wgs * rounds)), unit);
+  return static_cast<uint32_t>(std::min<uint64_t>(len, longest));
+}
+constexpr uint32_t kKeySegUnit = 4 * kSub;  // a wave per SIMD at work at least
+
+// Radical-sieve segments of a range: two workgroups per CU and tile shape.
+uint32_t rad_seg_len(const bx_ctx* c, uint64_t n) {
+  return fit_seg_len(n, 2ull * static_cast<uint64_t>(std::max(1, c->n_cu)), c->seg_len, kTileLarge);
+}
+
 struct Segs {
+  uint32_t seg_len = 0;
   std::vector<Query> q;
   std::vector<uint64_t> prefix;
   std::vector<uint32_t> small;  // queries served by the small-query class (no segments)
@@ -542,7 +572,7 @@ uint64_t max_share(const bx_ctx* c, const Segs& s, uint32_t W) {
   if (W == 0) return 0;
   std::vector<double> diff(W + 1, 0.0);
   std::vector<double> extra(W, 0.0);  // the shorter last segment of each query
-  const uint64_t L = c->seg_len;
+  const uint64_t L = s.seg_len;
   for (size_t i = 0; i < s.q.size(); ++i) {
     const Query& q = s.q[i];
     const uint64_t len = q.b > q.a ? q.b - q.a : 0;
@@ -601,8 +631,12 @@ void make_segs(const bx_ctx* c, Segs* s, bool small_class) {
   s->prefix.assign(s->q.size() + 1, 0);
   s->small.clear();
   s->n_ints = 0;
-  uint64_t acc = 0;
+  uint64_t acc = 0, n = 0;
   double keys = 0.0, expect = 0.0;
+  for (const Query& q : s->q)
+    if (q.b > q.a && !(small_class && is_small(c, q))) n += q.b - q.a;
+  s->seg_len = small_class ? fit_seg_len(n, static_cast<uint64_t>(std::max(1, c->n_cu)), c->seg_len, kKeySegUnit)
+                           : rad_seg_len(c, n);
   for (size_t i = 0; i < s->q.size(); ++i) {
     s->prefix[i] = acc;
     const uint64_t L = s->q[i].b > s->q[i].a ? s->q[i].b - s->q[i].a : 0;
@@ -611,7 +645,7 @@ void make_segs(const bx_ctx* c, Segs* s, bool small_class) {
       s->n_ints += L;
       continue;
     }
-    acc += (L + c->seg_len - 1) / c->seg_len;
+    acc += (L + s->seg_len - 1) / s->seg_len;
     keys += kept_bound(c, s->q[i], s->q[i].a, s->q[i].b);
     expect += kept_expected(c, s->q[i]);
     s->n_ints += L;
@@ -669,7 +703,7 @@ SieveParams base_sieve_params(bx_ctx* c, const Segs& s) {
   P.seg_prefix = static_cast<const uint64_t*>(c->segpref.p);
   P.n_queries = static_cast<uint32_t>(s.q.size());
   P.n_segs = s.n_segs;
-  P.seg_len = c->seg_len;
+  P.seg_len = s.seg_len;
   P.pp = c->d_pp;
   P.n_pp = static_cast<uint32_t>(c->pp.size());
   const int which = c->tile == kTileLarge ? 1 : 0;
@@ -760,7 +794,7 @@ int plan_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, Job* j, JobBufs* nb)
     // Indices run up to segments per workgroup * seg_len - 1; the bit length
     // of that product keeps the all-ones index free.
     const uint64_t W = std::max<uint64_t>(1, j->sieve_grid);
-    j->li_bits = std::max(1u, bits_of((s.n_segs + W - 1) / W * c->seg_len));
+    j->li_bits = std::max(1u, bits_of((s.n_segs + W - 1) / W * s.seg_len));
     const uint32_t kl = std::min<uint32_t>(42, 53 - j->li_bits);  // li_bits <= 43: x < 2^42
     j->kl_mask = (1ull << kl) - 1;
     j->wl_bits = j->li_bits + bits_of(W - 1);
@@ -820,7 +854,7 @@ int prepare_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, hipStream_t st, J
   c->stats.b1_bits = plan.b1bits;
   c->stats.b2_bits = plan.b2bits;
   c->stats.l2_entry_bytes = j->compact ? 8u : 12u;
-  c->stats.seg_len = c->seg_len;
+  c->stats.seg_len = s.seg_len;
   c->stats.tile = static_cast<uint32_t>(c->tile);
   return BX_OK;
 }
@@ -845,7 +879,7 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
   P.seg_prefix = static_cast<const uint64_t*>(c->segpref.p);
   P.n_queries = static_cast<uint32_t>(j.s->q.size());
   P.n_segs = j.s->n_segs;
-  P.seg_len = c->seg_len;
+  P.seg_len = j.s->seg_len;
   P.mid = c->d_mid;
   P.sp = c->d_sp;
   P.sp_p = c->d_sp_p;
@@ -875,7 +909,7 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
   src.queries = P.queries;
   src.seg_prefix = P.seg_prefix;
   src.n_queries = P.n_queries;
-  src.seg_len = c->seg_len;
+  src.seg_len = j.s->seg_len;
   src.W = j.sieve_grid;
   src.li_bits = j.li_bits;
   src.batch = j.batch;
@@ -1124,7 +1158,7 @@ int run_passes_graph(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* re
                 "%u %llu %u %u %u %u %llu %u %d %u %u %d %u %d %d %llx %u %d %zu %d %u %llx %p %p %p %p %p %p %p %p %p %p %p %p %p %p",
                 j.plan.passes, static_cast<unsigned long long>(j.plan.cap1), j.plan.cap2, j.plan.b1bits, j.plan.b2bits,
                 j.G, static_cast<unsigned long long>(j.s->n_segs), static_cast<uint32_t>(j.s->q.size()), j.batch,
-                j.kinds, c->third_off, c->tile, c->seg_len, c->prune, c->join_sort,
+                j.kinds, c->third_off, c->tile, j.s->seg_len, c->prune, c->join_sort,
                 static_cast<unsigned long long>(c->fp_mask), c->small_max, c->small_block, j.s->small.size(),
                 static_cast<int>(j.compact), j.wl_bits, static_cast<unsigned long long>(j.low_mask), c->l1.p,
                 c->l2.p, c->spill.p, c->cnt1.p, c->cnt2.p, c->cand.p, c->out.p, c->flags.p, c->acc.p, c->queries.p,
@@ -1882,7 +1916,7 @@ int bx_radical_segment_dev_noalloc(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t
   const int which = c->tile == kTileLarge ? 1 : 0;
   const uint32_t first_sparse = c->n_dense[which];
   const size_t top = static_cast<size_t>(
-      std::upper_bound(c->pp.begin(), c->pp.end(), hi, [](uint64_t v, const PrimePow& w) { return v < w.q; }) -
+      std::upper_bound(c->pp.begin(), c->pp.end(), static_cast<double>(hi), [](double v, const PrimePow& w) { return v < w.q; }) -
       c->pp.begin());
   const double expect = static_cast<double>(c->seg_len) *
                         (c->cum_inv_q[std::max<size_t>(top, first_sparse)] - c->cum_inv_q[first_sparse]);
@@ -1900,7 +1934,8 @@ int bx_radical_segment_dev_noalloc(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t
   uint32_t* flags = reinterpret_cast<uint32_t*>(na->ptr);
   Query* q = reinterpret_cast<Query*>(na->ptr + kNaQueryOff);
   uint64_t* pref = reinterpret_cast<uint64_t*>(na->ptr + kNaPrefOff);
-  const uint64_t n_segs = (hi - lo + c->seg_len - 1) / c->seg_len;
+  const uint32_t seg_len = rad_seg_len(c, hi - lo);
+  const uint64_t n_segs = (hi - lo + seg_len - 1) / seg_len;
   const uint32_t grid = static_cast<uint32_t>(
       std::min<uint64_t>({n_segs, kNaGrid, 2ull * sieve_wg_per_cu(c) * static_cast<uint64_t>(c->n_cu)}));
   // The counters start at zero (a fill kernel), the query table is written
@@ -1914,7 +1949,7 @@ int bx_radical_segment_dev_noalloc(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t
   P.seg_prefix = pref;
   P.n_queries = 1;
   P.n_segs = n_segs;
-  P.seg_len = c->seg_len;
+  P.seg_len = seg_len;
   P.pp = c->d_pp;
   P.n_pp = static_cast<uint32_t>(c->pp.size());
   P.n_dense = first_sparse;

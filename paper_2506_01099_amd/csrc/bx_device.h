@@ -28,8 +28,8 @@ struct Entry {
 // Odd prime power q = p^k (k >= 2) with its reciprocal (for q | x tests and the
 // first-multiple offset) and p^{-1} mod 2^32 (for the exact division by p).
 struct PrimePow {
-  uint64_t q;
-  double invq;
+  double q;
+  double invq;  // first_multiple
   uint32_t p;
   uint32_t pinv;
 };
@@ -121,16 +121,11 @@ __device__ __forceinline__ uint32_t inv32(uint32_t p) {
   return x;
 }
 
-// S mod q for S < 2^53 and 2 <= q < 2^53 with floor(S/q) < 2^31, from a
-// double-precision quotient estimate that is off by at most one.
-__device__ __forceinline__ uint64_t mod_fp64(uint64_t S, uint64_t q, double invq) {
-  const double f = floor(static_cast<double>(S) * invq);
-  int64_t r = static_cast<int64_t>(S) - static_cast<int64_t>(f) * static_cast<int64_t>(q);
-  if (r < 0)
-    r += static_cast<int64_t>(q);
-  else if (r >= static_cast<int64_t>(q))
-    r -= static_cast<int64_t>(q);
-  return static_cast<uint64_t>(r);
+// (-S) mod q for S < 2^42 as a double: the offset of the first multiple at or
+// after S.  invq is 1 / q less 2^-46 of it, so that ceil(S * invq) is the number
+// of that multiple also when q divides S.
+__device__ __forceinline__ double first_multiple(double S, double q, double invq) {
+  return __builtin_fma(__builtin_ceil(S * invq), q, -S);
 }
 
 // Divide the LDS cell by p (p divides it).  Different prime powers can hit the

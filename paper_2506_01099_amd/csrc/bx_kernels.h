@@ -158,8 +158,9 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// (Two workgroups of 1024 threads share a CU: 64 registers at most.)
 template <int T, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_sieve(SieveParams P) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void k_sieve(SieveParams P) {
   constexpr uint32_t kHitCap = hit_cap<T>();
   static_assert(T % BLOCK == 0 && T <= 65536, "tile shape");
   constexpr int ITER = T / BLOCK;                                     // keys per thread per tile
@@ -210,11 +211,12 @@ __global__ __launch_bounds__(BLOCK) void k_sieve(SieveParams P) {
     const uint64_t start = qa + (s - P.seg_prefix[qi]) * static_cast<uint64_t>(P.seg_len);
     const uint32_t len = static_cast<uint32_t>(min(static_cast<uint64_t>(P.seg_len), qb - start));
     const uint64_t V = start + len;  // largest value sieved in this segment
+    const double startd = static_cast<double>(start), lend = static_cast<double>(len), Vd = static_cast<double>(V);
     if (tid == 0) {
       uint32_t l = P.n_dense, h = P.n_pp;
       while (l < h) {
         const uint32_t m = (l + h) >> 1;
-        if (P.pp[m].q <= V)
+        if (P.pp[m].q <= Vd)
           l = m + 1;
         else
           h = m;
@@ -242,10 +244,9 @@ __global__ __launch_bounds__(BLOCK) void k_sieve(SieveParams P) {
 #pragma unroll
       for (int u = 0; u < kA; ++u) {
         if (idx0 + u * BLOCK >= n_act) break;
-        const uint64_t r = mod_fp64(start, pw[u].q, pw[u].invq);
-        for (uint64_t j = r ? pw[u].q - r : 0; j <= len; j += pw[u].q) {
+        for (double j = first_multiple(startd, pw[u].q, pw[u].invq); j <= lend; j += pw[u].q) {
           const uint32_t k = atomicAdd(&sh.hit_n, 1u);
-          const uint64_t e = (j << 32) | pw[u].p;
+          const uint64_t e = (static_cast<uint64_t>(static_cast<uint32_t>(j)) << 32) | pw[u].p;
           if (k < kHitCap)
             sh.hits[k] = e;
           else if (k - kHitCap < P.spill_cap)

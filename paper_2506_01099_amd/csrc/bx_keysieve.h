@@ -56,9 +56,7 @@ struct MidSlot {
   double q, invq;
   uint32_t jq, p;
 };
-// A power above kMidMax; the table ends in entries with q = infinity.  invq is
-// 1 / q less 2^-46 of it, so that ceil(S * invq) is the number of the first
-// multiple at or after S for every S < 2^42, also when q divides S.
+// A power above kMidMax; the table ends in entries with q = infinity.
 struct SparsePow {
   double q, invq;
 };
@@ -109,11 +107,7 @@ struct KeySh {
 };
 static_assert(sizeof(KeySh) <= 160 * 1024, "LDS of a CU");
 
-// (-S) mod q for S < 2^42 as a double: the offset of the first multiple at or
-// after S (invq as in SparsePow).
-__device__ __forceinline__ double first_multiple(double S, double q, double invq) {
-  return __builtin_fma(__builtin_ceil(S * invq), q, -S);
-}
+// first_multiple for a small q.
 __device__ __forceinline__ uint32_t first_multiple_small(double S, uint32_t q) {
   const double qd = static_cast<double>(q);
   return static_cast<uint32_t>(first_multiple(S, qd, (1.0 / qd) * (1.0 - 0x1p-46)));

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(BLOCK) void k_small(SmallParams P) {
     uint32_t l = P.n_dense, h = P.n_pp;
     while (l < h) {
       const uint32_t m = (l + h) >> 1;
-      if (P.pp[m].q <= qb)
+      if (P.pp[m].q <= static_cast<double>(qb))
         l = m + 1;
       else
         h = m;
@@ -83,8 +83,8 @@ __global__ __launch_bounds__(BLOCK) void k_small(SmallParams P) {
   const uint32_t n_act = n_act_s;
   for (uint32_t idx = P.n_dense + tid; idx < n_act; idx += BLOCK) {
     const PrimePow pw = P.pp[idx];
-    const uint64_t r = mod_fp64(qa, pw.q, pw.invq);
-    if (r == 0 || pw.q - r <= L) lds_div(&tile[r ? pw.q - r : 0], pw.p, pw.pinv);
+    const double j = first_multiple(static_cast<double>(qa), pw.q, pw.invq);
+    if (j <= static_cast<double>(L)) lds_div(&tile[static_cast<uint32_t>(j)], pw.p, pw.pinv);
   }
   __syncthreads();
   // Member test and fingerprints (kept in registers until every thread has
