@@ -120,7 +120,7 @@ struct bx_ctx {
   SparsePow* d_sp = nullptr;
   uint32_t* d_sp_p = nullptr;
   DenseTab* d_dense[2] = {nullptr, nullptr};
-  DevBuf l1, l2, cnt1, cnt2, cand, out, flags, spill, queries, segpref, rad, acc, a3tab, smallq;
+  DevBuf l1, l2, cnt1, cnt2, cand, out, counters, spill, queries, segpref, rad, a3tab, smallq;
   DevBuf a2k[2], a2v[2], a2hist, a2offs, a2tot;  // Algorithm 2: list (double-buffered), sort counts
   int force_passes = 0, timing = 1, force_b1 = -1, force_b2 = -1, force_group = 0;
   int prune = 1;            // drop x that cannot be a pair member before the join
@@ -147,14 +147,16 @@ struct bx_ctx {
   std::mutex mu;
   std::vector<hipEvent_t> ev_free;
   std::vector<TimedLaunch> timed;
+  std::vector<hipEvent_t> used;  // events of `timed`, each once
+  hipEvent_t last_ev = nullptr;  // recorded behind the last timed launch, if nothing was queued since
   hipEvent_t last_done = nullptr;    // recorded after the last call's work
   hipStream_t last_stream = nullptr;  // stream that work ran on
   void* na = nullptr;  // this device's no-allocation scratch (NaDevice)
-  // Pinned host staging of the query tables (uploads need no wait for the host
-  // vectors) and the event after their last upload (the next upload waits for it).
+  // Pinned host memory that kernels read and write: the staged query tables of
+  // a batch (rewritten only by calls that drained their stream), the report.
   void* pin = nullptr;
   size_t pin_bytes = 0;
-  hipEvent_t pin_ev = nullptr;
+  Report* report = nullptr;
   // serving
   struct Server;
   std::unique_ptr<Server> server;
@@ -198,6 +200,9 @@ hipEvent_t get_event(bx_ctx* c) {
   return e;
 }
 
+// Times one launch by the events around it; a launch right behind another
+// timed one starts at that one's end event (an event costs both the host and
+// the queue some microseconds).
 struct LaunchTimer {
   bx_ctx* c;
   int kind;
@@ -206,36 +211,41 @@ struct LaunchTimer {
   LaunchTimer(bx_ctx* ctx, int k, hipStream_t st) : c(ctx), kind(k), s(st) {
     c->stats.launches[k]++;
     if (c->timing && !c->capturing) {
-      a = get_event(c);
-      b = get_event(c);
-      if (a) (void)hipEventRecord(a, s);
+      a = c->last_ev;
+      if (!a && (a = get_event(c))) {
+        c->used.push_back(a);
+        (void)hipEventRecord(a, s);
+      }
+      if ((b = get_event(c))) c->used.push_back(b);
     }
   }
   ~LaunchTimer() {
     if (a && b) {
       (void)hipEventRecord(b, s);
       c->timed.push_back({kind, a, b});
+      c->last_ev = b;
     }
   }
 };
+
+void free_timings(bx_ctx* c) {
+  c->ev_free.insert(c->ev_free.end(), c->used.begin(), c->used.end());
+  c->used.clear();
+  c->timed.clear();
+  c->last_ev = nullptr;
+}
 
 // Called after the stream has drained: fold the recorded launches into stats.
 void collect_timings(bx_ctx* c) {
   for (auto& t : c->timed) {
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, t.a, t.b) == hipSuccess) c->stats.kernel_ms[t.kind] += ms;
-    c->ev_free.push_back(t.a);
-    c->ev_free.push_back(t.b);
   }
-  c->timed.clear();
+  free_timings(c);
 }
 
 void reset_stats(bx_ctx* c) {
-  for (auto& t : c->timed) {
-    c->ev_free.push_back(t.a);
-    c->ev_free.push_back(t.b);
-  }
-  c->timed.clear();
+  free_timings(c);
   c->stats = bx_stats{};
 }
 
@@ -253,8 +263,12 @@ int mark_done(bx_ctx* c, hipStream_t st) {
   return BX_OK;
 }
 
+uint32_t* flags_of(const bx_ctx* c) { return static_cast<Counters*>(c->counters.p)->flags; }
+unsigned long long* acc_of(const bx_ctx* c) { return static_cast<Counters*>(c->counters.p)->acc; }
+
 int fill_u32(bx_ctx* c, void* p, uint64_t n, uint32_t v, hipStream_t s) {
   if (n == 0) return BX_OK;
+  c->last_ev = nullptr;
   const uint64_t blocks = std::min<uint64_t>((n + 255) / 256, 4096);
   hipLaunchKernelGGL(k_fill_u32, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, static_cast<uint32_t*>(p), n, v);
   BX_HIP(hipGetLastError());
@@ -656,22 +670,18 @@ void make_segs(const bx_ctx* c, Segs* s, bool small_class) {
   s->n_expect = static_cast<uint64_t>(std::ceil(expect));
 }
 
-// Uploads the query table, the segment prefix and the small-query list through
-// the context's pinned staging buffer: the copies are queued on st and the
-// call returns at once (the next upload waits for these copies first).  The
-// device tables are rewritten only once the kernels queued before on st,
-// which may read them, have finished: a small copy from pinned memory may be
-// carried out by the host at once rather than in stream order.
-int upload_segs(bx_ctx* c, const Segs& s, hipStream_t st) {
+// Device room for the query tables; a batch's tables are staged in pinned host
+// memory, from where k_begin copies them (one launch instead of three copies;
+// a single query travels in its arguments).  No kernel that reads the staging
+// buffer is in flight here: calls with more than one query drain their stream.
+int stage_segs(bx_ctx* c, const Segs& s) {
   int rc;
   if ((rc = ensure(c, c->queries, s.q.size() * sizeof(Query))) != BX_OK) return rc;
   if ((rc = ensure(c, c->segpref, s.prefix.size() * sizeof(uint64_t))) != BX_OK) return rc;
-  if (!s.small.empty() && (rc = ensure(c, c->smallq, s.small.size() * sizeof(uint32_t))) != BX_OK) return rc;
+  if ((rc = ensure(c, c->smallq, s.small.size() * sizeof(uint32_t))) != BX_OK) return rc;
+  if (s.q.size() <= 1) return BX_OK;
   const size_t nq = s.q.size() * sizeof(Query), np = s.prefix.size() * sizeof(uint64_t),
-               ns = s.small.size() * sizeof(uint32_t);
-  const size_t op = (nq + 63) & ~size_t(63), os = op + ((np + 63) & ~size_t(63)), need = os + ns;
-  if (c->pin_ev) BX_HIP(hipEventSynchronize(c->pin_ev));  // the previous upload has left the buffer
-  BX_HIP(hipStreamSynchronize(st));  // earlier kernels are done with the tables
+               ns = s.small.size() * sizeof(uint32_t), need = nq + np + ns;
   if (need > c->pin_bytes) {
     if (c->pin) BX_HIP(hipHostFree(c->pin));
     c->pin = nullptr;
@@ -684,15 +694,37 @@ int upload_segs(bx_ctx* c, const Segs& s, hipStream_t st) {
     }
     c->pin_bytes = bytes;
   }
-  if (!c->pin_ev) BX_HIP(hipEventCreateWithFlags(&c->pin_ev, hipEventDisableTiming));
   uint8_t* h = static_cast<uint8_t*>(c->pin);
   std::memcpy(h, s.q.data(), nq);
-  std::memcpy(h + op, s.prefix.data(), np);
-  if (ns) std::memcpy(h + os, s.small.data(), ns);
-  BX_HIP(hipMemcpyAsync(c->queries.p, h, nq, hipMemcpyHostToDevice, st));
-  BX_HIP(hipMemcpyAsync(c->segpref.p, h + op, np, hipMemcpyHostToDevice, st));
-  if (ns) BX_HIP(hipMemcpyAsync(c->smallq.p, h + os, ns, hipMemcpyHostToDevice, st));
-  if (!c->capturing) BX_HIP(hipEventRecord(c->pin_ev, st));
+  std::memcpy(h + nq, s.prefix.data(), np);
+  if (ns) std::memcpy(h + nq + np, s.small.data(), ns);
+  return BX_OK;
+}
+
+// The first launch of a call: counters (with `clear`), n_cnt2 group cursors, query tables.
+int enqueue_begin(bx_ctx* c, const Segs& s, uint64_t n_cnt2, hipStream_t st, bool clear = true) {
+  BeginParams P;
+  std::memset(&P, 0, sizeof(P));
+  P.n = clear ? static_cast<Counters*>(c->counters.p) : nullptr;
+  P.cnt2 = static_cast<uint32_t*>(c->cnt2.p);
+  P.n_cnt2 = static_cast<uint32_t>(n_cnt2);
+  P.queries = static_cast<Query*>(c->queries.p);
+  P.seg_prefix = static_cast<uint64_t*>(c->segpref.p);
+  P.small = static_cast<uint32_t*>(c->smallq.p);
+  P.n_queries = static_cast<uint32_t>(s.q.size());
+  P.n_small = static_cast<uint32_t>(s.small.size());
+  P.one = s.q[0];
+  P.n_segs = s.n_segs;
+  if (s.q.size() > 1) {
+    const uint8_t* h = static_cast<const uint8_t*>(c->pin);
+    P.staged_queries = reinterpret_cast<const uint64_t*>(h);
+    P.staged_prefix = reinterpret_cast<const uint64_t*>(h + s.q.size() * sizeof(Query));
+    P.staged_small = reinterpret_cast<const uint32_t*>(h + s.q.size() * sizeof(Query) + s.prefix.size() * sizeof(uint64_t));
+  }
+  c->last_ev = nullptr;
+  const uint64_t words = std::max<uint64_t>(n_cnt2, 2 * s.q.size());
+  hipLaunchKernelGGL(k_begin, dim3(static_cast<uint32_t>(std::min<uint64_t>((words + 255) / 256, 64))), dim3(256), 0, st, P);
+  BX_HIP(hipGetLastError());
   return BX_OK;
 }
 
@@ -711,7 +743,7 @@ SieveParams base_sieve_params(bx_ctx* c, const Segs& s) {
   P.dense = c->d_dense[which];
   P.spill = static_cast<uint64_t*>(c->spill.p);
   P.spill_cap = spill_cap_of(c);
-  P.flags = static_cast<uint32_t*>(c->flags.p);
+  P.flags = flags_of(c);
   return P;
 }
 
@@ -757,7 +789,7 @@ struct Job {
 
 // Bytes of every workspace buffer a job needs.
 struct JobBufs {
-  size_t l1, l2, cnt1, cnt2, cand, out, flags, acc, spill, queries, segpref, smallq;
+  size_t l1, l2, cnt1, cnt2, cand, out, counters, spill, queries, segpref, smallq;
 };
 
 // The plan and launch shapes of one search over `s` and the workspace it
@@ -811,8 +843,7 @@ int plan_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, Job* j, JobBufs* nb)
   nb->cnt2 = j->ngsub * 4ull;
   nb->cand = kCandCap * sizeof(Cand);
   nb->out = kCandCap * sizeof(OutPair);
-  nb->flags = kFlagCount * 4;
-  nb->acc = kAccCount * sizeof(unsigned long long);
+  nb->counters = sizeof(Counters);
   nb->spill = static_cast<size_t>(j->sieve_grid) * kKeySpill * 8;
   nb->queries = s.q.size() * sizeof(Query);
   nb->segpref = s.prefix.size() * sizeof(uint64_t);
@@ -827,7 +858,7 @@ uint64_t bytes_after(const bx_ctx* c, const JobBufs& nb, bool released) {
   const std::pair<const DevBuf*, size_t> v[] = {{&c->l1, nb.l1},       {&c->l2, nb.l2},
                                                 {&c->cnt1, nb.cnt1},   {&c->cnt2, nb.cnt2},
                                                 {&c->cand, nb.cand},   {&c->out, nb.out},
-                                                {&c->flags, nb.flags}, {&c->acc, nb.acc},
+                                                {&c->counters, nb.counters},
                                                 {&c->spill, nb.spill}, {&c->queries, nb.queries},
                                                 {&c->segpref, nb.segpref}, {&c->smallq, nb.smallq},
                                                 {&c->rad, 0}};
@@ -836,7 +867,7 @@ uint64_t bytes_after(const bx_ctx* c, const JobBufs& nb, bool released) {
   return t;
 }
 
-int prepare_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, hipStream_t st, Job* j) {
+int prepare_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, Job* j) {
   int rc;
   JobBufs nb;
   if ((rc = plan_job(c, s, batch, kinds, j, &nb)) != BX_OK) return rc;
@@ -846,10 +877,9 @@ int prepare_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, hipStream_t st, J
   if ((rc = ensure(c, c->cnt2, nb.cnt2)) != BX_OK) return rc;
   if ((rc = ensure(c, c->cand, nb.cand)) != BX_OK) return rc;
   if ((rc = ensure(c, c->out, nb.out)) != BX_OK) return rc;
-  if ((rc = ensure(c, c->flags, nb.flags)) != BX_OK) return rc;
-  if ((rc = ensure(c, c->acc, nb.acc)) != BX_OK) return rc;
+  if ((rc = ensure(c, c->counters, nb.counters)) != BX_OK) return rc;
   if ((rc = ensure(c, c->spill, nb.spill)) != BX_OK) return rc;
-  if ((rc = upload_segs(c, s, st)) != BX_OK) return rc;
+  if ((rc = stage_segs(c, s)) != BX_OK) return rc;
   const Plan& plan = j->plan;
   c->stats.b1_bits = plan.b1bits;
   c->stats.b2_bits = plan.b2bits;
@@ -859,21 +889,12 @@ int prepare_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, hipStream_t st, J
   return BX_OK;
 }
 
-// Counters start at zero; the join kernel clears every group cursor it reads.
-int enqueue_init(bx_ctx* c, const Job& j, hipStream_t st) {
-  int rc;
-  if ((rc = fill_u32(c, c->flags.p, kFlagCount, 0, st)) != BX_OK) return rc;
-  if ((rc = fill_u32(c, c->cnt2.p, j.ngsub, 0, st)) != BX_OK) return rc;
-  if ((rc = fill_u32(c, c->acc.p, 2 * kAccCount, 0, st)) != BX_OK) return rc;
-  return BX_OK;
-}
-
 // One pass: keep the keys whose pass hash lies in [ph_lo, ph_hi).  The sieve
 // writes them to first-level regions, then each group of G buckets is split
 // into partitions and joined.
 int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStream_t st) {
   const Plan& plan = j.plan;
-  uint32_t* d_flags = static_cast<uint32_t*>(c->flags.p);
+  uint32_t* d_flags = flags_of(c);
   KeyParams P;
   P.queries = static_cast<const Query*>(c->queries.p);
   P.seg_prefix = static_cast<const uint64_t*>(c->segpref.p);
@@ -897,13 +918,11 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
   P.l1 = static_cast<uint64_t*>(c->l1.p);
   P.cap1 = static_cast<uint32_t>(plan.cap1);
   P.cnt1 = static_cast<uint32_t*>(c->cnt1.p);
+  P.entries = acc_of(c) + kAccEntries;
   {
     LaunchTimer t(c, K_SIEVE, st);
     hipLaunchKernelGGL(k_sieve_keys, dim3(j.sieve_grid), dim3(kKeyBlock), 0, st, P);
   }
-  BX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_sum_counts, dim3(64), dim3(256), 0, st, static_cast<const uint32_t*>(c->cnt1.p), j.n_regions,
-                     static_cast<unsigned long long*>(c->acc.p) + kAccEntries);
   BX_HIP(hipGetLastError());
   WordSource src;
   src.queries = P.queries;
@@ -952,7 +971,7 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
     J.cand = static_cast<Cand*>(c->cand.p);
     J.cand_cap = kCandCap;
     J.flags = d_flags;
-    J.joined = static_cast<unsigned long long*>(c->acc.p) + kAccJoined;
+    J.joined = acc_of(c) + kAccJoined;
     J.l2c = static_cast<const uint64_t*>(c->l2.p);
     J.wl_bits = j.wl_bits;
     J.low_mask = j.low_mask;
@@ -993,8 +1012,8 @@ int enqueue_small(bx_ctx* c, const Job& j, hipStream_t st) {
   P.fp_mask = c->fp_mask;
   P.cand = static_cast<Cand*>(c->cand.p);
   P.cand_cap = kCandCap;
-  P.flags = static_cast<uint32_t*>(c->flags.p);
-  P.acc = static_cast<unsigned long long*>(c->acc.p);
+  P.flags = flags_of(c);
+  P.acc = acc_of(c);
   for (uint32_t qi : s.small) {
     const Query& q = s.q[qi];
     if (q.b - q.a < 2 || q.b - q.a > (big ? kTileLarge : kTileSmall))
@@ -1025,10 +1044,19 @@ int enqueue_small(bx_ctx* c, const Job& j, hipStream_t st) {
   return BX_OK;
 }
 
+// Verifies the candidates found so far and writes the report.
 int enqueue_verify(bx_ctx* c, const Job& j, uint32_t grid, hipStream_t st) {
+  if (!c->report) {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, sizeof(Report), hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(BX_ENOMEM, "pinned host allocation of the report failed");
+    }
+    c->report = static_cast<Report*>(p);
+  }
   VerifyParams V;
   V.cand = static_cast<const Cand*>(c->cand.p);
-  V.n_cand = static_cast<const uint32_t*>(c->flags.p) + kFlagCand;
+  V.n_cand = flags_of(c) + kFlagCand;
   V.cand_cap = kCandCap;
   V.primes = c->d_primes;
   V.pinv = c->d_pinv;
@@ -1041,7 +1069,8 @@ int enqueue_verify(bx_ctx* c, const Job& j, uint32_t grid, hipStream_t st) {
   V.compact = j.compact;
   V.out = static_cast<OutPair*>(c->out.p);
   V.out_cap = kCandCap;
-  V.flags = static_cast<uint32_t*>(c->flags.p);
+  V.flags = flags_of(c);
+  V.report = c->report;
   {
     LaunchTimer t(c, K_VERIFY, st);
     hipLaunchKernelGGL((k_verify<kVerifyBlock>), dim3(grid), dim3(kVerifyBlock), 0, st, V);
@@ -1050,32 +1079,34 @@ int enqueue_verify(bx_ctx* c, const Job& j, uint32_t grid, hipStream_t st) {
   return BX_OK;
 }
 
-// The flag words and the 64-bit counters, read with one wait.
-int read_flags_acc(bx_ctx* c, uint32_t* fl, unsigned long long* acc, hipStream_t st) {
-  BX_HIP(hipMemcpyAsync(fl, c->flags.p, kFlagCount * 4, hipMemcpyDeviceToHost, st));
-  BX_HIP(hipMemcpyAsync(acc, c->acc.p, kAccCount * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
+// The counters, once everything queued has run.
+int read_counters(bx_ctx* c, Counters* n, hipStream_t st) {
+  BX_HIP(hipMemcpyAsync(n, c->counters.p, sizeof(Counters), hipMemcpyDeviceToHost, st));
   BX_HIP(hipStreamSynchronize(st));
   return BX_OK;
 }
 
-// Read the verified pairs (flags and counters already read after the last kernel).
-int collect_pairs(bx_ctx* c, const uint32_t* fl, const unsigned long long* acc, hipStream_t st,
-                  std::vector<OutPair>* result) {
+// The verified pairs and the call's statistics, from the counters after the
+// last verification (whose report holds the first pairs).
+int collect_pairs(bx_ctx* c, const Counters& n, uint64_t candidates, hipStream_t st, std::vector<OutPair>* result) {
+  const uint32_t* fl = n.flags;
   if (fl[kFlagSpillOverflow]) return fail(BX_EINTERNAL, "sparse-hit spill buffer overflow");
   if (fl[kFlagVerifyFail])
     return fail(BX_EINTERNAL, std::to_string(fl[kFlagVerifyFail]) + " candidate pairs failed exact verification");
-  c->stats.candidates = fl[kFlagCand] - fl[kFlagDropped];
+  c->stats.candidates = candidates - fl[kFlagDropped];
   c->stats.false_candidates = fl[kFlagFalseCand];
   c->stats.word_matches = fl[kFlagWordMatch];
   const uint32_t n_out = std::min(fl[kFlagOut], kCandCap);
   c->stats.pairs = n_out;
   result->resize(n_out);
-  if (n_out) {
+  if (n_out && n_out <= kReportPairs) {
+    std::memcpy(result->data(), c->report->pairs, n_out * sizeof(OutPair));
+  } else if (n_out) {
     BX_HIP(hipMemcpyAsync(result->data(), c->out.p, n_out * sizeof(OutPair), hipMemcpyDeviceToHost, st));
     BX_HIP(hipStreamSynchronize(st));
   }
-  c->stats.entries = acc[kAccEntries];
-  c->stats.joined = acc[kAccJoined];
+  c->stats.entries = n.acc[kAccEntries];
+  c->stats.joined = n.acc[kAccJoined];
   std::sort(result->begin(), result->end(), [](const OutPair& x, const OutPair& y) {
     if (x.query != y.query) return x.query < y.query;
     if (x.m != y.m) return x.m < y.m;
@@ -1084,64 +1115,59 @@ int collect_pairs(bx_ctx* c, const uint32_t* fl, const unsigned long long* acc, 
   return BX_OK;
 }
 
-// Passes run one at a time with a check after each: a pass whose buckets
-// overflow is discarded and run again split in two (one more pass-hash range
-// split), so the result never depends on the bucket sizes.
+// Passes run one at a time, each with its verification behind it and one wait:
+// the report says how it went.  A pass whose buckets overflowed is discarded
+// (the counters go back to what they were) and run again split in two (one
+// more pass-hash range split), so the result never depends on the bucket sizes.
 int run_passes_checked(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* result) {
   int rc;
-  if ((rc = enqueue_init(c, j, st)) != BX_OK) return rc;
+  if ((rc = enqueue_begin(c, *j.s, j.ngsub, st)) != BX_OK) return rc;
   if ((rc = enqueue_small(c, j, st)) != BX_OK) return rc;
   std::deque<std::pair<uint64_t, uint64_t>> pending;
   for (uint64_t v = 0; v < j.plan.passes; ++v)
     pending.emplace_back((v << 32) / j.plan.passes, ((v + 1) << 32) / j.plan.passes);
-  // Candidates are verified after every pass, so the buffer holds one pass's.
-  uint32_t cand_before = 0;  // of the small class, not yet verified
   uint64_t cand_total = 0;
-  unsigned long long acc_before[kAccCount] = {0, 0}, acc[kAccCount] = {0, 0};
-  uint32_t fl[kFlagCount] = {};
-  auto verify_found = [&]() -> int {
-    const uint32_t n = fl[kFlagCand];
-    if (n == 0) return BX_OK;
-    if (n > kCandCap) return fail(BX_EINTERNAL, "candidate buffer overflow");
-    cand_total += n;
-    int r = enqueue_verify(c, j, std::min<uint32_t>(n, kVerifyGrid), st);
-    if (r == BX_OK) r = fill_u32(c, static_cast<uint32_t*>(c->flags.p) + kFlagCand, 1, 0, st);
-    return r;
+  Counters before, now;
+  std::memset(&before, 0, sizeof(before));
+  auto verify = [&]() -> int {
+    int v = enqueue_verify(c, j, kVerifyGrid, st);
+    if (v != BX_OK) return v;
+    BX_HIP(hipStreamSynchronize(st));
+    c->last_ev = nullptr;
+    now = c->report->n;
+    return BX_OK;
   };
-  if (!j.s->small.empty()) {  // a split pass rolls back to what the small class left
-    if ((rc = read_flags_acc(c, fl, acc, st)) != BX_OK) return rc;
-    cand_before = fl[kFlagCand];
-    std::memcpy(acc_before, acc, sizeof(acc));
+  auto accept = [&]() -> int {
+    if (now.flags[kFlagCand] > kCandCap) return fail(BX_EINTERNAL, "candidate buffer overflow");
+    cand_total += now.flags[kFlagCand];
+    before = now;
+    before.flags[kFlagCand] = before.flags[kFlagDone] = 0;
+    return BX_OK;
+  };
+  if (!j.s->small.empty()) {  // the small class first: a discarded pass must not take its pairs along
+    if ((rc = verify()) != BX_OK || (rc = accept()) != BX_OK) return rc;
   }
   while (!pending.empty()) {
     const uint64_t ph_lo = pending.front().first, ph_hi = pending.front().second;
     pending.pop_front();
     if ((rc = enqueue_pass(c, j, ph_lo, ph_hi, st)) != BX_OK) return rc;
-    if ((rc = read_flags_acc(c, fl, acc, st)) != BX_OK) return rc;
+    if ((rc = verify()) != BX_OK) return rc;
     c->stats.passes++;
-    if (fl[kFlagSpillOverflow]) return fail(BX_EINTERNAL, "sparse-hit spill buffer overflow");
-    if (fl[kFlagL1Overflow] || fl[kFlagL2Overflow]) {
+    if (now.flags[kFlagSpillOverflow]) return fail(BX_EINTERNAL, "sparse-hit spill buffer overflow");
+    if (now.flags[kFlagL1Overflow] || now.flags[kFlagL2Overflow]) {
       c->stats.retries++;
       if (ph_hi - ph_lo < 2) return fail(BX_EINTERNAL, "bucket overflow on a single pass-hash value");
-      uint32_t* d_flags = static_cast<uint32_t*>(c->flags.p);
-      uint32_t z[2] = {0, 0};
-      BX_HIP(hipMemcpyAsync(d_flags + kFlagL1Overflow, z, sizeof(z), hipMemcpyHostToDevice, st));
-      BX_HIP(hipMemcpyAsync(d_flags + kFlagCand, &cand_before, 4, hipMemcpyHostToDevice, st));
-      BX_HIP(hipMemcpyAsync(c->acc.p, acc_before, sizeof(acc_before), hipMemcpyHostToDevice, st));
+      BX_HIP(hipMemcpyAsync(c->counters.p, &before, sizeof(before), hipMemcpyHostToDevice, st));
       BX_HIP(hipStreamSynchronize(st));
+      c->last_ev = nullptr;
       const uint64_t mid = ph_lo + (ph_hi - ph_lo) / 2;
       pending.emplace_front(mid, ph_hi);
       pending.emplace_front(ph_lo, mid);
       continue;
     }
-    std::memcpy(acc_before, acc, sizeof(acc));
-    if ((rc = verify_found()) != BX_OK) return rc;
-    cand_before = 0;
+    if ((rc = accept()) != BX_OK) return rc;
   }
-  if (j.plan.passes == 0 && (rc = verify_found()) != BX_OK) return rc;  // small-class queries only
-  if (cand_total && (rc = read_flags_acc(c, fl, acc, st)) != BX_OK) return rc;  // otherwise the last read is current
-  fl[kFlagCand] = static_cast<uint32_t>(cand_total);
-  return collect_pairs(c, fl, acc, st, result);
+  return collect_pairs(c, now, cand_total, st, result);
 }
 
 // All passes and the verification captured into one HIP graph and launched
@@ -1161,7 +1187,7 @@ int run_passes_graph(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* re
                 j.kinds, c->third_off, c->tile, j.s->seg_len, c->prune, c->join_sort,
                 static_cast<unsigned long long>(c->fp_mask), c->small_max, c->small_block, j.s->small.size(),
                 static_cast<int>(j.compact), j.wl_bits, static_cast<unsigned long long>(j.low_mask), c->l1.p,
-                c->l2.p, c->spill.p, c->cnt1.p, c->cnt2.p, c->cand.p, c->out.p, c->flags.p, c->acc.p, c->queries.p,
+                c->l2.p, c->spill.p, c->cnt1.p, c->cnt2.p, c->cand.p, c->out.p, c->counters.p, c->pin, c->queries.p,
                 c->segpref.p, c->smallq.p, static_cast<void*>(c->d_pp), static_cast<void*>(c->d_primes));
   if (!c->graph_exec || c->graph_key != key) {
     if (c->graph_exec) {
@@ -1172,7 +1198,7 @@ int run_passes_graph(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* re
     std::memcpy(before, c->stats.launches, sizeof(before));
     BX_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
     c->capturing = true;
-    rc = enqueue_init(c, j, st);
+    rc = enqueue_begin(c, *j.s, j.ngsub, st);
     if (rc == BX_OK) rc = enqueue_small(c, j, st);
     for (uint64_t v = 0; rc == BX_OK && v < j.plan.passes; ++v)
       rc = enqueue_pass(c, j, (v << 32) / j.plan.passes, ((v + 1) << 32) / j.plan.passes, st);
@@ -1197,9 +1223,9 @@ int run_passes_graph(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* re
   if (a) BX_HIP(hipEventRecord(a, st));
   BX_HIP(hipGraphLaunch(c->graph_exec, st));
   if (b) BX_HIP(hipEventRecord(b, st));
-  uint32_t fl[kFlagCount];
-  unsigned long long acc[kAccCount] = {0, 0};
-  if ((rc = read_flags_acc(c, fl, acc, st)) != BX_OK) return rc;
+  BX_HIP(hipStreamSynchronize(st));
+  const Counters n = c->report->n;
+  const uint32_t* fl = n.flags;
   if (a && b) {
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, a, b) == hipSuccess) c->stats.graph_ms += ms;
@@ -1212,7 +1238,7 @@ int run_passes_graph(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* re
     return BX_OK;
   }
   if (fl[kFlagCand] > kCandCap) return fail(BX_EINTERNAL, "candidate buffer overflow");
-  return collect_pairs(c, fl, acc, st, result);
+  return collect_pairs(c, n, fl[kFlagCand], st, result);
 }
 
 // The hash-partitioned exact join over all queries of `s`.
@@ -1221,12 +1247,10 @@ int run_search(bx_ctx* c, Segs& s, int batch, uint32_t kinds, std::vector<OutPai
   result->clear();
   int rc = order_after_last(c, st);
   if (rc != BX_OK) return rc;
-  rc = mark_done(c, st);  // host-synchronous from here on: the call drains st
-  if (rc != BX_OK) return rc;
-  make_segs(c, &s, true);
+  make_segs(c, &s, true);  // (the call drains st: no later call has to wait for it)
   if (s.n_segs == 0 && s.small.empty()) return BX_OK;
   Job j;
-  if ((rc = prepare_job(c, s, batch, kinds, st, &j)) != BX_OK) return rc;
+  if ((rc = prepare_job(c, s, batch, kinds, &j)) != BX_OK) return rc;
   c->stats.integers = s.n_ints;
   if (use_graph) {
     int redo = 0;
@@ -1254,11 +1278,11 @@ int radicals_into(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t* dev_out, hipStr
   make_segs(c, &s, false);
   if (s.n_segs == 0) return BX_OK;
   int rc;
-  if ((rc = upload_segs(c, s, st)) != BX_OK) return rc;
-  if ((rc = ensure(c, c->flags, kFlagCount * 4)) != BX_OK) return rc;
+  if ((rc = stage_segs(c, s)) != BX_OK) return rc;
+  if ((rc = ensure(c, c->counters, sizeof(Counters))) != BX_OK) return rc;
   const uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>(s.n_segs, 2ull * sieve_wg_per_cu(c) * c->n_cu));
   if ((rc = ensure(c, c->spill, static_cast<size_t>(grid) * spill_cap_of(c) * 8)) != BX_OK) return rc;
-  if (clear_flags && (rc = fill_u32(c, c->flags.p, kFlagCount, 0, st)) != BX_OK) return rc;
+  if ((rc = enqueue_begin(c, s, 0, st, clear_flags)) != BX_OK) return rc;
   SieveParams P = base_sieve_params(c, s);
   P.rad_out = dev_out;
   P.rad_lo = lo;
@@ -1289,10 +1313,8 @@ int run_alg3(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
   if ((rc = ensure(c, c->rad, (s + 1) * sizeof(uint64_t))) != BX_OK) return rc;
   if ((rc = ensure(c, c->cand, kCandCap * sizeof(Cand))) != BX_OK) return rc;
   if ((rc = ensure(c, c->out, kCandCap * sizeof(OutPair))) != BX_OK) return rc;
-  if ((rc = ensure(c, c->flags, kFlagCount * 4)) != BX_OK) return rc;
-  if ((rc = ensure(c, c->acc, kAccCount * sizeof(unsigned long long))) != BX_OK) return rc;
-  if ((rc = fill_u32(c, c->flags.p, kFlagCount, 0, st)) != BX_OK) return rc;
-  if ((rc = fill_u32(c, c->acc.p, 2 * kAccCount, 0, st)) != BX_OK) return rc;
+  if ((rc = ensure(c, c->counters, sizeof(Counters))) != BX_OK) return rc;
+  if ((rc = fill_u32(c, c->counters.p, sizeof(Counters) / 4, 0, st)) != BX_OK) return rc;
   uint64_t* rad = static_cast<uint64_t*>(c->rad.p);
   A3Params P;
   P.rad = rad;
@@ -1300,10 +1322,11 @@ int run_alg3(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
   P.tmask = slots - 1;
   P.cand = static_cast<Cand*>(c->cand.p);
   P.cand_cap = kCandCap;
-  P.flags = static_cast<uint32_t*>(c->flags.p);
+  P.flags = flags_of(c);
   auto grid_for = [&](uint64_t n) { return static_cast<uint32_t>(std::min<uint64_t>((n + 255) / 256, 8192)); };
   for (uint64_t i = 0; i < n_chunks; ++i) {
     const uint64_t ci = a + i * step, cnt_i = std::min(step, b - ci);  // entries n in [ci, ci + cnt_i)
+    c->last_ev = nullptr;
     hipLaunchKernelGGL(k_fill_u64, dim3(4096), dim3(256), 0, st, P.table, slots, kA3Empty);
     BX_HIP(hipGetLastError());
     if ((rc = radicals_into(c, ci, ci + cnt_i + 1, rad, st, false)) != BX_OK) return rc;
@@ -1330,9 +1353,10 @@ int run_alg3(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
     c->stats.passes++;
   }
   c->stats.integers = b - a;
-  uint32_t fl[kFlagCount];
-  unsigned long long acc_f[kAccCount] = {0, 0};
-  if ((rc = read_flags_acc(c, fl, acc_f, st)) != BX_OK) return rc;
+  Counters n_f;
+  if ((rc = read_counters(c, &n_f, st)) != BX_OK) return rc;
+  const uint32_t* fl = n_f.flags;
+  const uint32_t found = fl[kFlagCand];
   if (fl[kFlagSpillOverflow]) return fail(BX_EINTERNAL, "sparse-hit overflow in the radical sieve");
   if (fl[kFlagCand] > kCandCap) return fail(BX_EINTERNAL, "candidate buffer overflow");
   if (fl[kFlagCand] > 0) {
@@ -1340,10 +1364,10 @@ int run_alg3(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
     j.batch = 0;
     j.kinds = kinds;
     j.cand_fp_mask = c->fp_mask;
-    if ((rc = enqueue_verify(c, j, std::min<uint32_t>(fl[kFlagCand], kVerifyGrid), st)) != BX_OK) return rc;
-    if ((rc = read_flags_acc(c, fl, acc_f, st)) != BX_OK) return rc;
+    if ((rc = enqueue_verify(c, j, std::min<uint32_t>(found, kVerifyGrid), st)) != BX_OK) return rc;
+    if ((rc = read_counters(c, &n_f, st)) != BX_OK) return rc;
   }
-  return collect_pairs(c, fl, acc_f, st, result);
+  return collect_pairs(c, n_f, found, st, result);
 }
 
 // Algorithm 2 over [a, b): radicals in chunks, one list entry (fingerprint of
@@ -1378,10 +1402,8 @@ int run_alg2(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
   if ((rc = ensure(c, c->rad, (std::min(chunk, b - a) + 1) * sizeof(uint64_t))) != BX_OK) return rc;
   if ((rc = ensure(c, c->cand, kCandCap * sizeof(Cand))) != BX_OK) return rc;
   if ((rc = ensure(c, c->out, kCandCap * sizeof(OutPair))) != BX_OK) return rc;
-  if ((rc = ensure(c, c->flags, kFlagCount * 4)) != BX_OK) return rc;
-  if ((rc = ensure(c, c->acc, kAccCount * sizeof(unsigned long long))) != BX_OK) return rc;
-  if ((rc = fill_u32(c, c->flags.p, kFlagCount, 0, st)) != BX_OK) return rc;
-  if ((rc = fill_u32(c, c->acc.p, 2 * kAccCount, 0, st)) != BX_OK) return rc;
+  if ((rc = ensure(c, c->counters, sizeof(Counters))) != BX_OK) return rc;
+  if ((rc = fill_u32(c, c->counters.p, sizeof(Counters) / 4, 0, st)) != BX_OK) return rc;
   uint64_t* rad = static_cast<uint64_t*>(c->rad.p);
   A2KeyParams K;
   K.rad = rad;
@@ -1391,8 +1413,8 @@ int run_alg2(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
   K.keys = static_cast<uint64_t*>(c->a2k[0].p);
   K.vals = static_cast<uint64_t*>(c->a2v[0].p);
   K.cap = cap;
-  K.n_out = static_cast<unsigned long long*>(c->acc.p) + kAccEntries;
-  K.flags = static_cast<uint32_t*>(c->flags.p);
+  K.n_out = acc_of(c) + kAccEntries;
+  K.flags = flags_of(c);
   for (uint64_t c0 = a; c0 < b; c0 += chunk) {
     const uint64_t cnt = std::min(chunk, b - c0);
     if ((rc = radicals_into(c, c0, c0 + cnt + 1, rad, st, false)) != BX_OK) return rc;
@@ -1407,7 +1429,7 @@ int run_alg2(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
     BX_HIP(hipGetLastError());
   }
   unsigned long long acc[kAccCount] = {0, 0};
-  BX_HIP(hipMemcpyAsync(acc, c->acc.p, sizeof(acc), hipMemcpyDeviceToHost, st));
+  BX_HIP(hipMemcpyAsync(acc, acc_of(c), sizeof(acc), hipMemcpyDeviceToHost, st));
   BX_HIP(hipStreamSynchronize(st));
   const uint64_t n = acc[kAccEntries];
   if (n > cap) return fail(BX_EINTERNAL, "Algorithm 2: more kept integers than the bound");
@@ -1443,12 +1465,13 @@ int run_alg2(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
     hipLaunchKernelGGL(k_a2_runs, dim3(static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>((n + 255) / 256, 8192)))),
                        dim3(256), 0, st, static_cast<const uint64_t*>(c->a2k[cur].p),
                        static_cast<const uint64_t*>(c->a2v[cur].p), n, static_cast<Cand*>(c->cand.p), kCandCap,
-                       static_cast<uint32_t*>(c->flags.p));
+                       flags_of(c));
   }
   BX_HIP(hipGetLastError());
-  uint32_t fl[kFlagCount];
-  unsigned long long acc_f[kAccCount] = {0, 0};
-  if ((rc = read_flags_acc(c, fl, acc_f, st)) != BX_OK) return rc;
+  Counters n_f;
+  if ((rc = read_counters(c, &n_f, st)) != BX_OK) return rc;
+  const uint32_t* fl = n_f.flags;
+  const uint32_t found = fl[kFlagCand];
   if (fl[kFlagSpillOverflow]) return fail(BX_EINTERNAL, "sparse-hit overflow in the radical sieve");
   if (fl[kFlagL1Overflow]) return fail(BX_EINTERNAL, "Algorithm 2: list overflow");
   if (fl[kFlagCand] > kCandCap) return fail(BX_EINTERNAL, "candidate buffer overflow");
@@ -1457,10 +1480,10 @@ int run_alg2(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
     j.batch = 0;
     j.kinds = kinds;
     j.cand_fp_mask = c->fp_mask;
-    if ((rc = enqueue_verify(c, j, std::min<uint32_t>(fl[kFlagCand], kVerifyGrid), st)) != BX_OK) return rc;
-    if ((rc = read_flags_acc(c, fl, acc_f, st)) != BX_OK) return rc;
+    if ((rc = enqueue_verify(c, j, std::min<uint32_t>(found, kVerifyGrid), st)) != BX_OK) return rc;
+    if ((rc = read_counters(c, &n_f, st)) != BX_OK) return rc;
   }
-  rc = collect_pairs(c, fl, acc_f, st, result);
+  rc = collect_pairs(c, n_f, found, st, result);
   c->stats.joined = n;
   return rc;
 }
@@ -1474,7 +1497,7 @@ constexpr uint32_t kNaGrid = 512;   // sieve workgroups of one call at most
 constexpr uint32_t kNaSpill = 4096; // spilled sparse hits per workgroup (beyond the LDS list)
 constexpr size_t kNaQueryOff = 256, kNaPrefOff = 512, kNaSpillOff = 1024;
 constexpr size_t kNaBytes = kNaSpillOff + static_cast<size_t>(kNaGrid) * kNaSpill * sizeof(uint64_t);
-static_assert(kFlagCount * sizeof(uint32_t) <= kNaQueryOff && sizeof(Query) <= kNaPrefOff - kNaQueryOff,
+static_assert(sizeof(Counters) <= kNaQueryOff && sizeof(Query) <= kNaPrefOff - kNaQueryOff,
               "scratch layout");
 static __device__ __align__(256) uint8_t scratch[kNaBytes];
 
@@ -1559,8 +1582,8 @@ namespace {
 
 uint64_t workspace_bytes(const bx_ctx* c) {
   uint64_t t = 0;
-  for (const DevBuf* b : {&c->l1, &c->l2, &c->cnt1, &c->cnt2, &c->cand, &c->out, &c->flags, &c->spill, &c->queries,
-                          &c->segpref, &c->rad, &c->acc, &c->smallq})
+  for (const DevBuf* b : {&c->l1, &c->l2, &c->cnt1, &c->cnt2, &c->cand, &c->out, &c->counters, &c->spill, &c->queries,
+                          &c->segpref, &c->rad, &c->smallq})
     t += b->bytes;
   return t;
 }
@@ -1569,8 +1592,8 @@ void release_workspace(bx_ctx* c) {
   std::lock_guard<std::mutex> lk(c->mu);
   (void)hipSetDevice(c->device);
   (void)hipStreamSynchronize(c->stream);
-  for (DevBuf* b : {&c->l1, &c->l2, &c->cnt1, &c->cnt2, &c->cand, &c->out, &c->flags, &c->spill, &c->queries,
-                    &c->segpref, &c->rad, &c->acc, &c->smallq})
+  for (DevBuf* b : {&c->l1, &c->l2, &c->cnt1, &c->cnt2, &c->cand, &c->out, &c->counters, &c->spill, &c->queries,
+                    &c->segpref, &c->rad, &c->smallq})
     free_buf(*b);
   if (c->graph_exec) {
     (void)hipGraphExecDestroy(c->graph_exec);
@@ -1754,8 +1777,8 @@ void bx_destroy(bx_ctx* c) {
   bx_serve_stop(c);
   (void)hipSetDevice(c->device);
   if (c->stream) (void)hipStreamSynchronize(c->stream);
-  for (DevBuf* b : {&c->l1, &c->l2, &c->cnt1, &c->cnt2, &c->cand, &c->out, &c->flags, &c->spill, &c->queries,
-                    &c->segpref, &c->rad, &c->acc, &c->a3tab, &c->smallq, &c->a2k[0], &c->a2k[1], &c->a2v[0],
+  for (DevBuf* b : {&c->l1, &c->l2, &c->cnt1, &c->cnt2, &c->cand, &c->out, &c->counters, &c->spill, &c->queries,
+                    &c->segpref, &c->rad, &c->a3tab, &c->smallq, &c->a2k[0], &c->a2k[1], &c->a2v[0],
                     &c->a2v[1], &c->a2hist, &c->a2offs, &c->a2tot})
     free_buf(*b);
   if (c->d_primes) (void)hipFree(c->d_primes);
@@ -1770,8 +1793,8 @@ void bx_destroy(bx_ctx* c) {
   reset_stats(c);
   for (hipEvent_t e : c->ev_free) (void)hipEventDestroy(e);
   if (c->last_done) (void)hipEventDestroy(c->last_done);
-  if (c->pin_ev) (void)hipEventDestroy(c->pin_ev);
   if (c->pin) (void)hipHostFree(c->pin);
+  if (c->report) (void)hipHostFree(c->report);
   if (c->own_stream) (void)hipStreamDestroy(c->own_stream);
   delete c;
 }
@@ -1938,10 +1961,16 @@ int bx_radical_segment_dev_noalloc(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t
   const uint64_t n_segs = (hi - lo + seg_len - 1) / seg_len;
   const uint32_t grid = static_cast<uint32_t>(
       std::min<uint64_t>({n_segs, kNaGrid, 2ull * sieve_wg_per_cu(c) * static_cast<uint64_t>(c->n_cu)}));
-  // The counters start at zero (a fill kernel), the query table is written
-  // from kernel arguments.
-  if ((rc = fill_u32(c, flags, kFlagCount, 0, st)) != BX_OK) return rc;
-  hipLaunchKernelGGL(k_set_query, dim3(1), dim3(64), 0, st, q, pref, lo, hi, n_segs);
+  // The counters start at zero, the query table is written from kernel arguments.
+  BeginParams B;
+  std::memset(&B, 0, sizeof(B));
+  B.n = reinterpret_cast<Counters*>(na->ptr);
+  B.queries = q;
+  B.seg_prefix = pref;
+  B.n_queries = 1;
+  B.one = Query{lo, hi};
+  B.n_segs = n_segs;
+  hipLaunchKernelGGL(k_begin, dim3(1), dim3(256), 0, st, B);
   BX_HIP(hipGetLastError());
   SieveParams P;
   std::memset(&P, 0, sizeof(P));

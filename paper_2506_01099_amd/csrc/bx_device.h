@@ -91,12 +91,28 @@ enum : int {
   kFlagFalseCand = 6,  // equal fingerprints of different sets (dropped)
   kFlagWordMatch = 7,  // compact words with equal kept bits
   kFlagDropped = 8,    // of the candidates made from them, those with different whole fingerprints
-  kFlagCount = 9
+  kFlagDone = 9,       // workgroups of the verification that have finished
+  kFlagCount = 10
 };
 
-// 64-bit per-call counters (acc[]): entries written by the sieve, entries read
-// by the join kernels (one add per partition).
+// 64-bit per-call counters (acc[]): entries written by the sieve (one add per
+// workgroup), entries read by the join kernels (one add per partition).
 enum : int { kAccEntries = 0, kAccJoined = 1, kAccCount = 2 };
+
+// The counters of a call lie together: flag words, then acc[].
+struct Counters {
+  uint32_t flags[16];
+  unsigned long long acc[kAccCount];
+};
+static_assert(kFlagCount <= 16, "flag words");
+
+// What a call reports, written to host memory by the last workgroup of the
+// verification: the counters and the first pairs.
+constexpr uint32_t kReportPairs = 256;
+struct Report {
+  Counters n;
+  OutPair pairs[kReportPairs];
+};
 
 // Exact quotient r / p for an odd prime p dividing r, r < 2^64, from
 // p^{-1} mod 2^32 (division by an invariant integer via its inverse,

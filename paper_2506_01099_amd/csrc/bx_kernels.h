@@ -11,8 +11,9 @@
 //                       the resident primes (equal fingerprints of different
 //                       sets are dropped here), classified (first kind when
 //                       rad(m) = rad(n), Algorithm 2) and filtered by kind.
-//   k_fill_u32          fills a word array (clears counters inside graphs).
-//   k_set_query         writes a one-query table from kernel arguments.
+//   k_fill_u32          fills a word array.
+//   k_begin             starts a call: clears its counters and writes its query
+//                       tables.
 #pragma once
 #include <type_traits>
 
@@ -874,7 +875,32 @@ struct VerifyParams {
   OutPair* out;
   uint32_t out_cap;
   uint32_t* flags;
+  Report* report;  // host memory
 };
+
+// The last workgroup of the verification to finish writes the report, and
+// readies the flags for the candidates of another pass.
+template <int BLOCK>
+__device__ __forceinline__ void report(const VerifyParams& P, uint32_t active) {
+  __shared__ uint32_t last;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __threadfence();
+    last = atomicAdd(&P.flags[kFlagDone], 1u) + 1 == active;
+    __threadfence();
+  }
+  __syncthreads();
+  if (!last) return;
+  static_assert(BLOCK >= static_cast<int>(kReportPairs), "one pair per thread");
+  const volatile uint32_t* flags = P.flags;
+  Counters* n = reinterpret_cast<Counters*>(P.flags);
+  const uint32_t pairs = min(flags[kFlagOut], min(P.out_cap, kReportPairs));
+  if (threadIdx.x < 16) P.report->n.flags[threadIdx.x] = flags[threadIdx.x];
+  if (threadIdx.x < kAccCount) P.report->n.acc[threadIdx.x] = *(const volatile unsigned long long*)&n->acc[threadIdx.x];
+  if (threadIdx.x < pairs) P.report->pairs[threadIdx.x] = P.out[threadIdx.x];
+  __syncthreads();
+  if (threadIdx.x == 0) P.flags[kFlagCand] = P.flags[kFlagDone] = 0;
+}
 
 // One workgroup per candidate pair: rad of m, m+1, n, n+1 by trial division
 // (the definition of the radical), with the cofactor left after dividing out
@@ -885,6 +911,8 @@ __global__ __launch_bounds__(BLOCK) void k_verify(VerifyParams P) {
   __shared__ uint64_t red_r[NV][BLOCK], red_s[NV][BLOCK];
   const int tid = threadIdx.x;
   const uint32_t n_cand = min(*P.n_cand, P.cand_cap);
+  const uint32_t active = max(1u, min(n_cand, gridDim.x));  // workgroups with candidates, or the first
+  if (blockIdx.x >= active) return;
   const bool third = (P.kinds & kKindThird) != 0;
   const int nv = third ? NV : 4;
   for (uint32_t c = blockIdx.x; c < n_cand; c += gridDim.x) {
@@ -982,26 +1010,43 @@ __global__ __launch_bounds__(BLOCK) void k_verify(VerifyParams P) {
       }
     }
   }
+  report<BLOCK>(P, active);
 }
 
-// Sum of n counters into *acc (entries written by a pass).
-__global__ void k_sum_counts(const uint32_t* cnt, uint64_t n, unsigned long long* acc) {
-  uint64_t s = 0;
-  for (uint64_t i = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
-    s += cnt[i];
-  if (s) atomicAdd(acc, static_cast<unsigned long long>(s));
-}
-
-// The one-query table of a single-range sieve, written from kernel arguments
-// (no host copy).
-__global__ void k_set_query(Query* q, uint64_t* seg_prefix, uint64_t a, uint64_t b, uint64_t n_segs) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    q->a = a;
-    q->b = b;
-    seg_prefix[0] = 0;
-    seg_prefix[1] = n_segs;
+// Start of a call: counters and group cursors to zero, and the query tables,
+// from the arguments (one query) or from the host's staging buffer.
+struct BeginParams {
+  Counters* n;
+  uint32_t* cnt2;  // n_cnt2 cursors
+  uint32_t n_cnt2;
+  Query* queries;
+  uint64_t* seg_prefix;
+  uint32_t* small;
+  uint32_t n_queries, n_small;
+  Query one;        // n_queries = 1
+  uint64_t n_segs;
+  const uint64_t* staged_queries;  // host memory: two words per query, n_queries + 1 words, n_small half words
+  const uint64_t* staged_prefix;
+  const uint32_t* staged_small;
+};
+__global__ __launch_bounds__(256) void k_begin(BeginParams P) {
+  const uint32_t t = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
+  if (P.n && t < 16) P.n->flags[t] = 0;
+  if (P.n && t < kAccCount) P.n->acc[t] = 0;
+  for (uint32_t i = t; i < P.n_cnt2; i += step) P.cnt2[i] = 0;
+  if (P.n_queries == 1) {
+    if (t == 0) {
+      P.queries[0] = P.one;
+      P.seg_prefix[0] = 0;
+      P.seg_prefix[1] = P.n_segs;
+      if (P.n_small) P.small[0] = 0;
+    }
+    return;
   }
+  uint64_t* q = reinterpret_cast<uint64_t*>(P.queries);
+  for (uint32_t i = t; i < 2 * P.n_queries; i += step) q[i] = P.staged_queries[i];
+  for (uint32_t i = t; i < P.n_queries + 1; i += step) P.seg_prefix[i] = P.staged_prefix[i];
+  for (uint32_t i = t; i < P.n_small; i += step) P.small[i] = P.staged_small[i];
 }
 
 __global__ void k_fill_u32(uint32_t* p, uint64_t n, uint32_t v) {

@@ -83,6 +83,7 @@ struct KeyParams {
   uint64_t* l1;    // region (w, b) of bucket b written by workgroup w: l1 + (w * B1 + b) * cap1
   uint32_t cap1;   // words per region (a multiple of 64; B1 * cap1 < 2^29)
   uint32_t* cnt1;  // W x B1 fill counts, written at the end of the kernel
+  unsigned long long* entries;  // += words written
 };
 
 // A queue writes out runs of 2^run_log words: half its slots, at most 64.
@@ -591,7 +592,7 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
             const double xd = x0d + static_cast<double>(i);
             // The even one of x, x + 1 has the factor 2^(a-1), half its lowest
             // set bit (in the low word, but for multiples of 2^32).
-            const uint32_t odd = i & 1u ^ x0odd, ev = static_cast<uint32_t>(x) + odd;
+            const uint32_t odd = (i & 1u) ^ x0odd, ev = static_cast<uint32_t>(x) + odd;
             double low = static_cast<double>(ev & (0u - ev));
             if (wraps && ev == 0) low = 0x1p32 * static_cast<double>((x + odd) >> 32 & (0 - ((x + odd) >> 32)));
             low *= 0.5;
@@ -658,11 +659,17 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
     const uint32_t k = first + ((i - first) & smask);
     if (k < n && k < P.cap1) mine[b * P.cap1 + k] = sh.queue[i];
   }
-  for (uint32_t b = threadIdx.x; b < (1u << P.b1bits); b += kKeyBlock) {
+  if (threadIdx.x == 0) sh.sparse_n = 0;
+  __syncthreads();
+  static_assert(kB1Max == kKeyBlock, "one bucket per thread");
+  if (const uint32_t b = threadIdx.x; b < (1u << P.b1bits)) {
     const uint32_t n = sh.cur[b];
     P.cnt1[(static_cast<uint64_t>(blockIdx.x) << P.b1bits) + b] = n;
     if (n > P.cap1) atomicOr(&P.flags[kFlagL1Overflow], 1u);
+    if (n) atomicAdd(&sh.sparse_n, n);
   }
+  __syncthreads();
+  if (threadIdx.x == 0 && sh.sparse_n) atomicAdd(P.entries, static_cast<unsigned long long>(sh.sparse_n));
 }
 
 }  // namespace bx
