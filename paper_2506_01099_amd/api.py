@@ -23,13 +23,19 @@ def _split_by_offsets(flat, offs, q):
     return [flat[b[i]:b[i + 1]] for i in range(q)]
 
 
+_PAIR = np.dtype([("m", np.uint64), ("n", np.uint64), ("kind", np.uint32), ("query", np.uint32)])
+
+
 def _pairs_from(ptr, count):
-    lib = load()
+    """The library's list as [(m, n, kind)], converted in bulk and released."""
+    if not count:
+        return []
     try:
-        return [(int(ptr[i].m), int(ptr[i].n), int(ptr[i].kind)) for i in range(count)]
+        raw = ctypes.cast(ptr, ctypes.POINTER(ctypes.c_char * (count * _PAIR.itemsize))).contents
+        a = np.frombuffer(raw, dtype=_PAIR, count=count)
+        return list(zip(a["m"].tolist(), a["n"].tolist(), a["kind"].tolist()))
     finally:
-        if count:
-            lib.bx_free(ptr)
+        load().bx_free(ptr)
 
 
 class Benelux:

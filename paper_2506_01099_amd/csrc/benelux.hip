@@ -58,8 +58,6 @@ constexpr uint32_t kDefaultSegLen = 1u << 18;
 constexpr uint64_t kMaxQueryLen = 1ull << 28;
 constexpr uint32_t kMaxQueries = kGrpMask + 1;
 
-enum { K_SIEVE = 0, K_PART = 1, K_JOIN = 2, K_VERIFY = 3, K_RAD = 4, K_SMALL = 5 };
-
 // Queries of at most this many integers are served whole by one workgroup
 // (k_small) when the small-query class is on; the class keeps no HBM entries.
 constexpr uint32_t kSmallMaxLen = 8192;
@@ -107,19 +105,24 @@ struct bx_ctx {
   hipStream_t stream = nullptr;
   uint64_t hi_max = 0, budget = 0;
   int n_cu = 256;
+  int clock_khz = 100000;  // of wall_clock64
   std::string arch;
   std::vector<uint32_t> primes;
-  std::vector<PrimePow> pp;
+  struct OddPower {
+    double q, invq;
+    uint32_t p;
+  };
+  std::vector<OddPower> pp;  // every odd prime power, ascending
   std::vector<double> cum_inv_q;  // cum_inv_q[i] = sum of 1/q over pp[0, i)
   uint32_t n_dense[2] = {0, 0};  // per tile shape (small, large)
   uint32_t* d_primes = nullptr;
   PrimeInv* d_pinv = nullptr;  // per prime: p^-1 mod 2^64 and floor((2^64 - 1) / p) (divisibility tests)
-  PrimePow* d_pp = nullptr;
-  // The key sieve's tables: static slots of the powers up to kMidMax, and the powers above.
-  MidSlot* d_mid = nullptr;
-  SparsePow* d_sp = nullptr;
-  uint32_t* d_sp_p = nullptr;
+  PowerTables powers{nullptr, nullptr, nullptr, nullptr};
+  uint32_t sparse_first = 0;  // powers.pw from here on are above kMidMax
+  MidSlot* d_mid = nullptr;   // the key sieve's slots of the powers up to kMidMax
   DenseTab* d_dense[2] = {nullptr, nullptr};
+  MidSlot* d_small[2] = {nullptr, nullptr};  // the same powers' multiples, for the small-query class
+  uint32_t n_small[2] = {0, 0};
   DevBuf l1, l2, cnt1, cnt2, cand, out, counters, spill, queries, segpref, rad, a3tab, smallq;
   DevBuf a2k[2], a2v[2], a2hist, a2offs, a2tot;  // Algorithm 2: list (double-buffered), sort counts
   int force_passes = 0, timing = 1, force_b1 = -1, force_b2 = -1, force_group = 0;
@@ -147,8 +150,6 @@ struct bx_ctx {
   std::mutex mu;
   std::vector<hipEvent_t> ev_free;
   std::vector<TimedLaunch> timed;
-  std::vector<hipEvent_t> used;  // events of `timed`, each once
-  hipEvent_t last_ev = nullptr;  // recorded behind the last timed launch, if nothing was queued since
   hipEvent_t last_done = nullptr;    // recorded after the last call's work
   hipStream_t last_stream = nullptr;  // stream that work ran on
   void* na = nullptr;  // this device's no-allocation scratch (NaDevice)
@@ -200,9 +201,8 @@ hipEvent_t get_event(bx_ctx* c) {
   return e;
 }
 
-// Times one launch by the events around it; a launch right behind another
-// timed one starts at that one's end event (an event costs both the host and
-// the queue some microseconds).
+// Times a launch of the radical sieve or of a baseline by the events around it
+// (the kernels of the passes keep their own clock: note_time).
 struct LaunchTimer {
   bx_ctx* c;
   int kind;
@@ -211,28 +211,25 @@ struct LaunchTimer {
   LaunchTimer(bx_ctx* ctx, int k, hipStream_t st) : c(ctx), kind(k), s(st) {
     c->stats.launches[k]++;
     if (c->timing && !c->capturing) {
-      a = c->last_ev;
-      if (!a && (a = get_event(c))) {
-        c->used.push_back(a);
-        (void)hipEventRecord(a, s);
-      }
-      if ((b = get_event(c))) c->used.push_back(b);
+      a = get_event(c);
+      b = get_event(c);
+      if (a) (void)hipEventRecord(a, s);
     }
   }
   ~LaunchTimer() {
     if (a && b) {
       (void)hipEventRecord(b, s);
       c->timed.push_back({kind, a, b});
-      c->last_ev = b;
     }
   }
 };
 
 void free_timings(bx_ctx* c) {
-  c->ev_free.insert(c->ev_free.end(), c->used.begin(), c->used.end());
-  c->used.clear();
+  for (auto& t : c->timed) {
+    c->ev_free.push_back(t.a);
+    c->ev_free.push_back(t.b);
+  }
   c->timed.clear();
-  c->last_ev = nullptr;
 }
 
 // Called after the stream has drained: fold the recorded launches into stats.
@@ -268,7 +265,6 @@ unsigned long long* acc_of(const bx_ctx* c) { return static_cast<Counters*>(c->c
 
 int fill_u32(bx_ctx* c, void* p, uint64_t n, uint32_t v, hipStream_t s) {
   if (n == 0) return BX_OK;
-  c->last_ev = nullptr;
   const uint64_t blocks = std::min<uint64_t>((n + 255) / 256, 4096);
   hipLaunchKernelGGL(k_fill_u32, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, static_cast<uint32_t*>(p), n, v);
   BX_HIP(hipGetLastError());
@@ -293,16 +289,15 @@ int build_tables(bx_ctx* c) {
   c->pp.clear();
   for (uint32_t p : c->primes) {
     if (p == 2) continue;
-    const uint32_t pinv = inv32_host(p);
     uint64_t q = static_cast<uint64_t>(p) * p;
     while (q <= c->hi_max) {
       const double qd = static_cast<double>(q);
-      c->pp.push_back(PrimePow{qd, low_inverse(qd), p, pinv});
+      c->pp.push_back({qd, low_inverse(qd), p});
       if (q > c->hi_max / p) break;
       q *= p;
     }
   }
-  std::sort(c->pp.begin(), c->pp.end(), [](const PrimePow& a, const PrimePow& b) { return a.q < b.q; });
+  std::sort(c->pp.begin(), c->pp.end(), [](const bx_ctx::OddPower& a, const bx_ctx::OddPower& b) { return a.q < b.q; });
   c->cum_inv_q.assign(c->pp.size() + 1, 0.0);
   for (size_t i = 0; i < c->pp.size(); ++i) c->cum_inv_q[i + 1] = c->cum_inv_q[i] + c->pp[i].invq;
   for (int which = 0; which < 2; ++which) {
@@ -319,7 +314,7 @@ int build_tables(bx_ctx* c) {
         return fail(BX_EINTERNAL, "dense slot table overflow");
       dt.q[nd] = q;
       dt.p[nd] = w.p;
-      dt.pinv[nd] = w.pinv;
+      dt.pinv[nd] = inv32_host(w.p);
       dt.prefix[nd] = slots;
       for (uint32_t k = 0; k < ub; ++k) dt.slot_d[slots + k] = static_cast<uint8_t>(nd);
       slots += ub;
@@ -328,35 +323,55 @@ int build_tables(bx_ctx* c) {
     dt.n = nd;
     dt.nslots = slots;
     c->n_dense[which] = nd;
+    std::vector<MidSlot> ms;
+    for (uint32_t d = 0; d < nd; ++d)
+      for (uint32_t jq = 0; jq <= T; jq += dt.q[d]) ms.push_back(MidSlot{c->pp[d].q, c->pp[d].invq, jq, dt.p[d]});
+    c->n_small[which] = static_cast<uint32_t>(ms.size());
+    ms.resize(std::max<size_t>(1, ms.size()), MidSlot{1.0, low_inverse(1.0), 1u << 31, 1});
+    BX_HIP(hipMalloc(&c->d_small[which], ms.size() * sizeof(MidSlot)));
+    BX_HIP(hipMemcpy(c->d_small[which], ms.data(), ms.size() * sizeof(MidSlot), hipMemcpyHostToDevice));
     BX_HIP(hipMalloc(&c->d_dense[which], sizeof(DenseTab)));
     BX_HIP(hipMemcpy(c->d_dense[which], &dt, sizeof(DenseTab), hipMemcpyHostToDevice));
   }
   {
     std::vector<MidSlot> mid;
-    std::vector<SparsePow> sp;
-    std::vector<uint32_t> sp_p;
+    std::vector<Power> pw;
+    std::vector<uint32_t> pw_p, sq_p;
+    std::vector<float> sq;
+    c->sparse_first = 0;
     for (const auto& w : c->pp) {
-      if (w.q <= kFixedQMax || w.q == 729) continue;  // the subtile's own slots
-      if (w.q <= kMidMax) {
+      if (w.q > kFixedQMax && w.q != 729 && w.q <= kMidMax)  // (the rest have a subtile's own slots)
         for (uint32_t jq = 0; jq <= kKeyLen; jq += static_cast<uint32_t>(w.q)) mid.push_back(MidSlot{w.q, w.invq, jq, w.p});
+      if (w.p > kSquareMin && w.q == static_cast<double>(w.p) * w.p) {
+        sq.push_back(static_cast<float>(1.0 / w.q));
+        sq_p.push_back(w.p);
       } else {
-        sp.push_back(SparsePow{w.q, w.invq});
-        sp_p.push_back(w.p);
+        c->sparse_first += w.q <= kMidMax;
+        pw.push_back(Power{w.q, w.invq});
+        pw_p.push_back(w.p);
       }
     }
     std::sort(mid.begin(), mid.end(), [](const MidSlot& a, const MidSlot& b) { return a.jq < b.jq; });
     if (mid.size() > static_cast<size_t>(kMidPer) * kKeyBlock) return fail(BX_EINTERNAL, "mid slot table overflow");
-    // The sieve reads rounds of 4 * kKeyBlock powers until one starts past its range.
-    sp.resize(sp.size() + 8 * kKeyBlock, SparsePow{HUGE_VAL, 0.0});
-    sp_p.resize(sp.size(), 0);
+    pw.resize(pw.size() + kPowerPad, Power{HUGE_VAL, 0.0});
+    pw_p.resize(pw.size(), 0);
+    sq.resize(sq.size() + kPowerPad, 0.f);
+    sq_p.resize(sq.size(), 1u << 31);  // (t = 0 passes the single-precision test; q > V does not the exact one)
     // The rest of the slots lie past any block: q = 1 gives offset 0.
     mid.resize(static_cast<size_t>(kMidPer) * kKeyBlock, MidSlot{1.0, low_inverse(1.0), 1u << 31, 1});
     BX_HIP(hipMalloc(&c->d_mid, mid.size() * sizeof(MidSlot)));
-    BX_HIP(hipMalloc(&c->d_sp, sp.size() * sizeof(SparsePow)));
-    BX_HIP(hipMalloc(&c->d_sp_p, sp_p.size() * sizeof(uint32_t)));
     BX_HIP(hipMemcpy(c->d_mid, mid.data(), mid.size() * sizeof(MidSlot), hipMemcpyHostToDevice));
-    BX_HIP(hipMemcpy(c->d_sp, sp.data(), sp.size() * sizeof(SparsePow), hipMemcpyHostToDevice));
-    BX_HIP(hipMemcpy(c->d_sp_p, sp_p.data(), sp_p.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+    auto up = [](auto** d, const auto& v) -> int {
+      void* p = nullptr;
+      BX_HIP(hipMalloc(&p, v.size() * sizeof(v[0])));
+      *d = static_cast<std::remove_reference_t<decltype(*d)>>(p);
+      BX_HIP(hipMemcpy(p, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice));
+      return BX_OK;
+    };
+    int rc;
+    if ((rc = up(&c->powers.pw, pw)) != BX_OK || (rc = up(&c->powers.pw_p, pw_p)) != BX_OK ||
+        (rc = up(&c->powers.sq, sq)) != BX_OK || (rc = up(&c->powers.sq_p, sq_p)) != BX_OK)
+      return rc;
   }
   BX_HIP(hipMalloc(&c->d_primes, std::max<size_t>(4, c->primes.size() * sizeof(uint32_t))));
   {
@@ -373,11 +388,8 @@ int build_tables(bx_ctx* c) {
     if (!inv.empty())
       BX_HIP(hipMemcpy(c->d_pinv, inv.data(), inv.size() * sizeof(PrimeInv), hipMemcpyHostToDevice));
   }
-  BX_HIP(hipMalloc(&c->d_pp, std::max<size_t>(sizeof(PrimePow), c->pp.size() * sizeof(PrimePow))));
   if (!c->primes.empty())
     BX_HIP(hipMemcpy(c->d_primes, c->primes.data(), c->primes.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-  if (!c->pp.empty())
-    BX_HIP(hipMemcpy(c->d_pp, c->pp.data(), c->pp.size() * sizeof(PrimePow), hipMemcpyHostToDevice));
   return BX_OK;
 }
 
@@ -721,7 +733,6 @@ int enqueue_begin(bx_ctx* c, const Segs& s, uint64_t n_cnt2, hipStream_t st, boo
     P.staged_prefix = reinterpret_cast<const uint64_t*>(h + s.q.size() * sizeof(Query));
     P.staged_small = reinterpret_cast<const uint32_t*>(h + s.q.size() * sizeof(Query) + s.prefix.size() * sizeof(uint64_t));
   }
-  c->last_ev = nullptr;
   const uint64_t words = std::max<uint64_t>(n_cnt2, 2 * s.q.size());
   hipLaunchKernelGGL(k_begin, dim3(static_cast<uint32_t>(std::min<uint64_t>((words + 255) / 256, 64))), dim3(256), 0, st, P);
   BX_HIP(hipGetLastError());
@@ -736,8 +747,7 @@ SieveParams base_sieve_params(bx_ctx* c, const Segs& s) {
   P.n_queries = static_cast<uint32_t>(s.q.size());
   P.n_segs = s.n_segs;
   P.seg_len = s.seg_len;
-  P.pp = c->d_pp;
-  P.n_pp = static_cast<uint32_t>(c->pp.size());
+  P.powers = c->powers;
   const int which = c->tile == kTileLarge ? 1 : 0;
   P.n_dense = c->n_dense[which];
   P.dense = c->d_dense[which];
@@ -902,8 +912,8 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
   P.n_segs = j.s->n_segs;
   P.seg_len = j.s->seg_len;
   P.mid = c->d_mid;
-  P.sp = c->d_sp;
-  P.sp_p = c->d_sp_p;
+  P.powers = c->powers;
+  P.sparse_first = c->sparse_first;
   P.spill = static_cast<uint64_t*>(c->spill.p);
   P.flags = d_flags;
   P.batch = j.batch;
@@ -920,7 +930,7 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
   P.cnt1 = static_cast<uint32_t*>(c->cnt1.p);
   P.entries = acc_of(c) + kAccEntries;
   {
-    LaunchTimer t(c, K_SIEVE, st);
+    c->stats.launches[K_SIEVE]++;
     hipLaunchKernelGGL(k_sieve_keys, dim3(j.sieve_grid), dim3(kKeyBlock), 0, st, P);
   }
   BX_HIP(hipGetLastError());
@@ -954,7 +964,7 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
     Q.wl_bits = j.wl_bits;
     Q.low_mask = j.low_mask;
     {
-      LaunchTimer t(c, K_PART, st);
+      c->stats.launches[K_PART]++;
       const dim3 pg(static_cast<uint32_t>(j.part_grid));
       if (j.compact)
         hipLaunchKernelGGL((k_partition<kPartBlock, true>), pg, dim3(kPartBlock), 0, st, Q);
@@ -980,7 +990,7 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
     J.pinv = c->d_pinv;
     J.n_primes = static_cast<uint32_t>(c->primes.size());
     {
-      LaunchTimer t(c, K_JOIN, st);
+      c->stats.launches[K_JOIN]++;
       if (j.compact)
         hipLaunchKernelGGL((k_join_c<kJoinBlock>), dim3(static_cast<uint32_t>(j.ngsub)), dim3(kJoinBlock), 0, st, J);
       else if (c->join_sort)
@@ -1004,11 +1014,11 @@ int enqueue_small(bx_ctx* c, const Job& j, hipStream_t st) {
   P.list = static_cast<const uint32_t*>(c->smallq.p);
   P.batch = j.batch;
   P.prune = c->prune;
-  P.pp = c->d_pp;
-  P.n_pp = static_cast<uint32_t>(c->pp.size());
+  P.powers = c->powers;
   const bool big = c->small_max > static_cast<uint32_t>(kTileSmall);
   P.n_dense = c->n_dense[big ? 1 : 0];
-  P.dense = c->d_dense[big ? 1 : 0];
+  P.slots = c->d_small[big ? 1 : 0];
+  P.n_slots = c->n_small[big ? 1 : 0];
   P.fp_mask = c->fp_mask;
   P.cand = static_cast<Cand*>(c->cand.p);
   P.cand_cap = kCandCap;
@@ -1021,7 +1031,7 @@ int enqueue_small(bx_ctx* c, const Job& j, hipStream_t st) {
   }
   const dim3 grid(static_cast<uint32_t>(s.small.size()));
   {
-    LaunchTimer t(c, K_SMALL, st);
+    c->stats.launches[K_SMALL]++;
 #define BX_SMALL_LAUNCH(T, B) hipLaunchKernelGGL((k_small<T, B>), grid, dim3(B), 0, st, P)
     if (big) {
       if (c->small_block == 256)
@@ -1046,14 +1056,6 @@ int enqueue_small(bx_ctx* c, const Job& j, hipStream_t st) {
 
 // Verifies the candidates found so far and writes the report.
 int enqueue_verify(bx_ctx* c, const Job& j, uint32_t grid, hipStream_t st) {
-  if (!c->report) {
-    void* p = nullptr;
-    if (hipHostMalloc(&p, sizeof(Report), hipHostMallocDefault) != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(BX_ENOMEM, "pinned host allocation of the report failed");
-    }
-    c->report = static_cast<Report*>(p);
-  }
   VerifyParams V;
   V.cand = static_cast<const Cand*>(c->cand.p);
   V.n_cand = flags_of(c) + kFlagCand;
@@ -1072,7 +1074,7 @@ int enqueue_verify(bx_ctx* c, const Job& j, uint32_t grid, hipStream_t st) {
   V.flags = flags_of(c);
   V.report = c->report;
   {
-    LaunchTimer t(c, K_VERIFY, st);
+    c->stats.launches[K_VERIFY]++;
     hipLaunchKernelGGL((k_verify<kVerifyBlock>), dim3(grid), dim3(kVerifyBlock), 0, st, V);
   }
   BX_HIP(hipGetLastError());
@@ -1105,6 +1107,8 @@ int collect_pairs(bx_ctx* c, const Counters& n, uint64_t candidates, hipStream_t
     BX_HIP(hipMemcpyAsync(result->data(), c->out.p, n_out * sizeof(OutPair), hipMemcpyDeviceToHost, st));
     BX_HIP(hipStreamSynchronize(st));
   }
+  if (c->timing)
+    for (int k = 0; k < kKernels; ++k) c->stats.kernel_ms[k] += static_cast<double>(n.ticks[k]) / c->clock_khz;
   c->stats.entries = n.acc[kAccEntries];
   c->stats.joined = n.acc[kAccJoined];
   std::sort(result->begin(), result->end(), [](const OutPair& x, const OutPair& y) {
@@ -1133,7 +1137,6 @@ int run_passes_checked(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* 
     int v = enqueue_verify(c, j, kVerifyGrid, st);
     if (v != BX_OK) return v;
     BX_HIP(hipStreamSynchronize(st));
-    c->last_ev = nullptr;
     now = c->report->n;
     return BX_OK;
   };
@@ -1142,6 +1145,7 @@ int run_passes_checked(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* 
     cand_total += now.flags[kFlagCand];
     before = now;
     before.flags[kFlagCand] = before.flags[kFlagDone] = 0;
+    before.since = before.running = 0;
     return BX_OK;
   };
   if (!j.s->small.empty()) {  // the small class first: a discarded pass must not take its pairs along
@@ -1159,7 +1163,6 @@ int run_passes_checked(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* 
       if (ph_hi - ph_lo < 2) return fail(BX_EINTERNAL, "bucket overflow on a single pass-hash value");
       BX_HIP(hipMemcpyAsync(c->counters.p, &before, sizeof(before), hipMemcpyHostToDevice, st));
       BX_HIP(hipStreamSynchronize(st));
-      c->last_ev = nullptr;
       const uint64_t mid = ph_lo + (ph_hi - ph_lo) / 2;
       pending.emplace_front(mid, ph_hi);
       pending.emplace_front(ph_lo, mid);
@@ -1188,7 +1191,7 @@ int run_passes_graph(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* re
                 static_cast<unsigned long long>(c->fp_mask), c->small_max, c->small_block, j.s->small.size(),
                 static_cast<int>(j.compact), j.wl_bits, static_cast<unsigned long long>(j.low_mask), c->l1.p,
                 c->l2.p, c->spill.p, c->cnt1.p, c->cnt2.p, c->cand.p, c->out.p, c->counters.p, c->pin, c->queries.p,
-                c->segpref.p, c->smallq.p, static_cast<void*>(c->d_pp), static_cast<void*>(c->d_primes));
+                c->segpref.p, c->smallq.p, static_cast<const void*>(c->powers.pw), static_cast<void*>(c->d_primes));
   if (!c->graph_exec || c->graph_key != key) {
     if (c->graph_exec) {
       BX_HIP(hipGraphExecDestroy(c->graph_exec));
@@ -1326,7 +1329,6 @@ int run_alg3(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
   auto grid_for = [&](uint64_t n) { return static_cast<uint32_t>(std::min<uint64_t>((n + 255) / 256, 8192)); };
   for (uint64_t i = 0; i < n_chunks; ++i) {
     const uint64_t ci = a + i * step, cnt_i = std::min(step, b - ci);  // entries n in [ci, ci + cnt_i)
-    c->last_ev = nullptr;
     hipLaunchKernelGGL(k_fill_u64, dim3(4096), dim3(256), 0, st, P.table, slots, kA3Empty);
     BX_HIP(hipGetLastError());
     if ((rc = radicals_into(c, ci, ci + cnt_i + 1, rad, st, false)) != BX_OK) return rc;
@@ -1709,7 +1711,9 @@ void serve_worker(bx_ctx::Server* S, int lane) {
       reset_stats(c);
       uint32_t kall = 0;  // every kind any request of the batch asks for
       for (uint32_t k : kinds) kall |= k;
-      rc = run_search(c, s, 1, kall, &res, c->graph_batch != 0);
+      // Batches of a lane are seldom alike: capturing a graph for each costs
+      // more than its few launches.
+      rc = run_search(c, s, 1, kall, &res, false);
       (void)hipStreamSynchronize(c->stream);
       collect_timings(c);
       after = workspace_bytes(c);
@@ -1755,6 +1759,8 @@ int bx_create(bx_ctx** out, int device, uint64_t hi_max, uint64_t hbm_budget_byt
   hipDeviceProp_t prop;
   BX_HIP(hipGetDeviceProperties(&prop, device));
   c->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+  int khz = 0;
+  if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0) c->clock_khz = khz;
   c->arch = prop.gcnArchName;
   const size_t colon = c->arch.find(':');
   if (colon != std::string::npos) c->arch.resize(colon);
@@ -1768,6 +1774,13 @@ int bx_create(bx_ctx** out, int device, uint64_t hi_max, uint64_t hbm_budget_byt
   NaDevice* na = nullptr;
   if ((rc = na_setup(device, &na)) != BX_OK) return rc;
   c->na = na;
+  // Here and not at its first use, which may lie inside a capture.
+  void* report = nullptr;
+  if (hipHostMalloc(&report, sizeof(Report), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(BX_ENOMEM, "pinned host allocation of the report failed");
+  }
+  c->report = static_cast<Report*>(report);
   *out = c.release();
   return BX_OK;
 }
@@ -1783,11 +1796,14 @@ void bx_destroy(bx_ctx* c) {
     free_buf(*b);
   if (c->d_primes) (void)hipFree(c->d_primes);
   if (c->d_pinv) (void)hipFree(c->d_pinv);
-  if (c->d_pp) (void)hipFree(c->d_pp);
+  if (c->powers.pw) (void)hipFree(const_cast<Power*>(c->powers.pw));
+  if (c->powers.pw_p) (void)hipFree(const_cast<uint32_t*>(c->powers.pw_p));
+  if (c->powers.sq) (void)hipFree(const_cast<float*>(c->powers.sq));
+  if (c->powers.sq_p) (void)hipFree(const_cast<uint32_t*>(c->powers.sq_p));
   if (c->d_mid) (void)hipFree(c->d_mid);
-  if (c->d_sp) (void)hipFree(c->d_sp);
-  if (c->d_sp_p) (void)hipFree(c->d_sp_p);
   for (DenseTab* d : c->d_dense)
+    if (d) (void)hipFree(d);
+  for (MidSlot* d : c->d_small)
     if (d) (void)hipFree(d);
   if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
   reset_stats(c);
@@ -1939,7 +1955,7 @@ int bx_radical_segment_dev_noalloc(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t
   const int which = c->tile == kTileLarge ? 1 : 0;
   const uint32_t first_sparse = c->n_dense[which];
   const size_t top = static_cast<size_t>(
-      std::upper_bound(c->pp.begin(), c->pp.end(), static_cast<double>(hi), [](double v, const PrimePow& w) { return v < w.q; }) -
+      std::upper_bound(c->pp.begin(), c->pp.end(), static_cast<double>(hi), [](double v, const bx_ctx::OddPower& w) { return v < w.q; }) -
       c->pp.begin());
   const double expect = static_cast<double>(c->seg_len) *
                         (c->cum_inv_q[std::max<size_t>(top, first_sparse)] - c->cum_inv_q[first_sparse]);
@@ -1979,8 +1995,7 @@ int bx_radical_segment_dev_noalloc(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t
   P.n_queries = 1;
   P.n_segs = n_segs;
   P.seg_len = seg_len;
-  P.pp = c->d_pp;
-  P.n_pp = static_cast<uint32_t>(c->pp.size());
+  P.powers = c->powers;
   P.n_dense = first_sparse;
   P.dense = c->d_dense[which];
   P.spill = reinterpret_cast<uint64_t*>(na->ptr + kNaSpillOff);

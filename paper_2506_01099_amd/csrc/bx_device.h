@@ -25,13 +25,30 @@ struct Entry {
   uint32_t w0, w1, w2;
 };
 
-// Odd prime power q = p^k (k >= 2) with its reciprocal (for q | x tests and the
-// first-multiple offset) and p^{-1} mod 2^32 (for the exact division by p).
-struct PrimePow {
-  double q;
-  double invq;  // first_multiple
-  uint32_t p;
-  uint32_t pinv;
+// An odd prime power q = p^k (k >= 2), with 1 / q less 2^-46 of it
+// (first_multiple).
+struct Power {
+  double q, invq;
+};
+// Every odd prime power up to hi_max, ascending, in two tables that end in
+// entries past every range (the sieves read whole rounds): the rest, and the
+// squares of the primes above kSquareMin, nearly all of them (8.1e4 of the
+// 8.4e4 up to 2^40), as 1 / p^2 in 32 bits.
+struct PowerTables {
+  const Power* pw;
+  const uint32_t* pw_p;  // their primes
+  const float* sq;       // 1 / p^2 for
+  const uint32_t* sq_p;  // these primes
+};
+constexpr uint32_t kSquareMin = 1u << 13;
+constexpr uint32_t kPowerPad = 1u << 15;
+
+// One multiple of a power in a block of integers, with a slot of its own: jq =
+// j * q past the power's first multiple in the block.  (Slots that stand for
+// nothing have jq = 2^31.)
+struct MidSlot {
+  double q, invq;
+  uint32_t jq, p;
 };
 
 // Divisibility by an odd prime without division: p^-1 mod 2^64 and
@@ -99,12 +116,31 @@ enum : int {
 // workgroup), entries read by the join kernels (one add per partition).
 enum : int { kAccEntries = 0, kAccJoined = 1, kAccCount = 2 };
 
-// The counters of a call lie together: flag words, then acc[].
+// Kernels whose device time a call reports (bx_stats).
+enum : int { K_SIEVE = 0, K_PART = 1, K_JOIN = 2, K_VERIFY = 3, K_RAD = 4, K_SMALL = 5, kKernels = 6 };
+
+// The counters of a call lie together: flag words, acc[], and the clock of
+// the call's kernels.
 struct Counters {
   uint32_t flags[16];
   unsigned long long acc[kAccCount];
+  unsigned long long ticks[kKernels];  // device time of each kernel
+  unsigned long long since;            // start of the kernel that runs now
+  unsigned long long running;          // which: its index + 1, or 0
 };
 static_assert(kFlagCount <= 16, "flag words");
+
+// Every kernel of a call notes its start (one thread; they run one after the
+// other), which ends the time of the kernel before it: events between them cost
+// the queue 4 us each.  `flags` is the call's Counters.
+__device__ __forceinline__ void note_time(uint32_t* flags, int kernel) {
+  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+  Counters* n = reinterpret_cast<Counters*>(flags);
+  const unsigned long long now = wall_clock64();
+  if (n->running) n->ticks[n->running - 1] += now - n->since;
+  n->since = now;
+  n->running = static_cast<unsigned long long>(kernel + 1);
+}
 
 // What a call reports, written to host memory by the last workgroup of the
 // verification: the counters and the first pairs.
@@ -142,6 +178,68 @@ __device__ __forceinline__ uint32_t inv32(uint32_t p) {
 // of that multiple also when q divides S.
 __device__ __forceinline__ double first_multiple(double S, double q, double invq) {
   return __builtin_fma(__builtin_ceil(S * invq), q, -S);
+}
+
+// Calls f(j, p) for every multiple S + j, 0 <= j <= len, of the powers of
+// the first table from `first` on and of the second; thread tid of BLOCK threads
+// takes every BLOCK-th power, AHEAD rounds in flight.  S + len < 2^42, len <= 2^24.
+//
+// Every segment looks at every power, and one multiply, ceil, fused multiply-add
+// and compare in double precision each took 25000 cycles for the 8.4e4 of 2^40
+// (double-precision rounding runs at a quarter of the rate).  For q = p^2 > 2^26
+// single precision tells almost always that there is none: t = S / q < 2^16
+// is known to 3 * 2^-24 of itself, so a multiple S + j with 0 <= j <= len needs
+// t within 3 * 2^-24 * t + len / q of an integer.  About 12 of the 8.1e4 pass
+// and are looked at exactly.
+template <int BLOCK, int AHEAD, typename F>
+__device__ __forceinline__ void sparse_hits(const PowerTables& T, uint32_t first, double S, double len, uint32_t tid, F f) {
+  static_assert((2 * AHEAD + 1) * BLOCK <= static_cast<int>(kPowerPad), "rounds read ahead");
+  const double V = S + len;
+  // (Read by 32-bit byte offsets from the tables' starts.)
+  auto power = [&](uint32_t i) {
+    return *reinterpret_cast<const Power*>(reinterpret_cast<const uint8_t*>(T.pw) + i * static_cast<uint32_t>(sizeof(Power)));
+  };
+  auto square = [&](uint32_t i) {
+    return *reinterpret_cast<const float*>(reinterpret_cast<const uint8_t*>(T.sq) + i * static_cast<uint32_t>(sizeof(float)));
+  };
+  float wn[AHEAD];
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) wn[u] = square(tid + u * BLOCK);
+  for (uint32_t i0 = first + tid;; i0 += 2 * BLOCK) {
+    const Power w[2] = {power(i0), power(i0 + BLOCK)};
+    if (__all(w[0].q > V)) break;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      for (double j = first_multiple(S, w[u].q, w[u].invq); j <= len; j += w[u].q)  // (j is no number for q = infinity)
+        f(static_cast<uint32_t>(j), T.pw_p[i0 + u * BLOCK]);
+  }
+  const float Sf = static_cast<float>(S), Vf = static_cast<float>(V);
+  const float near = static_cast<float>((S * 3.01 * 0x1p-24 + len) * 1.001);
+  for (uint32_t i0 = tid;; i0 += AHEAD * BLOCK) {
+    float w[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) w[u] = wn[u];
+    if (__all(w[0] * Vf < 0.999f)) break;  // q > V
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) wn[u] = square(i0 + (AHEAD + u) * BLOCK);
+    bool pass[AHEAD], any = false;
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      const float t = Sf * w[u];
+      pass[u] = __builtin_fabsf(t - __builtin_rintf(t)) <= near * w[u];
+      any |= pass[u];
+    }
+    if (any) {
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        if (!pass[u]) continue;
+        const uint32_t p = T.sq_p[i0 + u * BLOCK];
+        const double q = static_cast<double>(p) * static_cast<double>(p);
+        const double j = __builtin_fma(__builtin_rint(S * static_cast<double>(w[u])), q, -S);
+        if (j >= 0.0 && j <= len) f(static_cast<uint32_t>(j), p);
+      }
+    }
+  }
 }
 
 // Divide the LDS cell by p (p divides it).  Different prime powers can hit the

@@ -40,9 +40,8 @@ struct SieveParams {
   uint32_t n_queries;
   uint64_t n_segs;
   uint32_t seg_len;
-  const PrimePow* pp;  // all odd prime powers <= hi_max, ascending
-  uint32_t n_pp;
-  uint32_t n_dense;  // pp[0, n_dense) are the dense ones (q <= tile)
+  PowerTables powers;
+  uint32_t n_dense;  // powers.pw[0, n_dense) are the dense ones (q <= tile)
   const DenseTab* dense;
   uint64_t* spill;  // per workgroup: spill + blockIdx.x * spill_cap
   uint32_t spill_cap;
@@ -56,7 +55,7 @@ struct SieveSh {
   uint64_t tile[T + 1];
   uint64_t hits[hit_cap<T>()];
   uint32_t dres[kDenseMax], doff[kDenseMax], dq[kDenseMax], dtq[kDenseMax];
-  uint32_t hit_n, n_act;
+  uint32_t hit_n;
 };
 
 // Counting sort of n staged entries (bucket of entry i in sb[i]) into runs per
@@ -211,52 +210,24 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
     const uint64_t qa = P.queries[qi].a, qb = P.queries[qi].b;
     const uint64_t start = qa + (s - P.seg_prefix[qi]) * static_cast<uint64_t>(P.seg_len);
     const uint32_t len = static_cast<uint32_t>(min(static_cast<uint64_t>(P.seg_len), qb - start));
-    const uint64_t V = start + len;  // largest value sieved in this segment
-    const double startd = static_cast<double>(start), lend = static_cast<double>(len), Vd = static_cast<double>(V);
-    if (tid == 0) {
-      uint32_t l = P.n_dense, h = P.n_pp;
-      while (l < h) {
-        const uint32_t m = (l + h) >> 1;
-        if (P.pp[m].q <= Vd)
-          l = m + 1;
-        else
-          h = m;
-      }
-      sh.n_act = l;
-      sh.hit_n = 0;
-    }
+    if (tid == 0) sh.hit_n = 0;
     if (static_cast<uint32_t>(tid) < nd) sh.dres[tid] = static_cast<uint32_t>(start % sh.dq[tid]);
     __syncthreads();
 
     // Sparse prime powers (q > tile): at most one multiple per tile.  Their
     // multiples in [start, V] are listed once per segment (Algorithm 1's
-    // first-multiple offset, start mod q).
-    const uint32_t n_act = sh.n_act;
-    // Four powers per thread and round, their table words loaded together
-    // (a thread past the end loads the last active power and ignores it).
-    constexpr int kA = 4;
-    for (uint32_t idx0 = P.n_dense + tid; idx0 < n_act; idx0 += kA * BLOCK) {
-      PrimePow pw[kA];
-#pragma unroll
-      for (int u = 0; u < kA; ++u) {
-        const uint32_t idx = idx0 + u * BLOCK;
-        pw[u] = P.pp[idx < n_act ? idx : n_act - 1];
-      }
-#pragma unroll
-      for (int u = 0; u < kA; ++u) {
-        if (idx0 + u * BLOCK >= n_act) break;
-        for (double j = first_multiple(startd, pw[u].q, pw[u].invq); j <= lend; j += pw[u].q) {
-          const uint32_t k = atomicAdd(&sh.hit_n, 1u);
-          const uint64_t e = (static_cast<uint64_t>(static_cast<uint32_t>(j)) << 32) | pw[u].p;
-          if (k < kHitCap)
-            sh.hits[k] = e;
-          else if (k - kHitCap < P.spill_cap)
-            spill[k - kHitCap] = e;
-          else
-            atomicOr(&P.flags[kFlagSpillOverflow], 1u);
-        }
-      }
-    }
+    // first-multiple offset, -start mod q).
+    sparse_hits<BLOCK, 8>(P.powers, P.n_dense, static_cast<double>(start), static_cast<double>(len), tid,
+                          [&](uint32_t j, uint32_t p) {
+                            const uint32_t k = atomicAdd(&sh.hit_n, 1u);
+                            const uint64_t e = (static_cast<uint64_t>(j) << 32) | p;
+                            if (k < kHitCap)
+                              sh.hits[k] = e;
+                            else if (k - kHitCap < P.spill_cap)
+                              spill[k - kHitCap] = e;
+                            else
+                              atomicOr(&P.flags[kFlagSpillOverflow], 1u);
+                          });
     __syncthreads();
     const uint32_t nh = min(sh.hit_n, kHitCap + P.spill_cap);
 
@@ -397,6 +368,7 @@ __global__ __launch_bounds__(BLOCK) void k_partition(PartParams P) {
   __shared__ uint16_t sbk[kPartChunk], perm[kPartChunk];
   __shared__ uint32_t cnt[kB2Max], gofs[kB2Max];
   __shared__ uint32_t wsum[BLOCK / 64];
+  note_time(P.flags, K_PART);
   const int tid = threadIdx.x;
   const uint32_t l = blockIdx.x;
   const uint32_t xcd = l & 7u, slot = l >> 3;
@@ -521,6 +493,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
   static_assert(kJoinCap < (1 << kJoinIdxBits), "index field must not reach the empty marker");
   __shared__ __align__(16) uint32_t table[kJoinSlots];
   const int tid = threadIdx.x;
+  note_time(P.flags, K_JOIN);
   const uint64_t sbk = blockIdx.x;
   if (sbk >= P.n_sub) return;
   const uint32_t n = min(P.cnt2[sbk], P.cap2);
@@ -631,20 +604,27 @@ __device__ __forceinline__ void emit_match(const JoinParams& P, uint64_t a, uint
   emit_cand(P, make_entry((r.x - off) | grp, a >> P.wl_bits), make_entry((r.y - off) | grp, b >> P.wl_bits));
 }
 
-// One wave: whether S_x = S_y can hold, from the primes 3 .. 2^13, one per lane.
+// One wave: whether S_x = S_y can hold, from the primes 3 .. 2^11 and some more, one per lane.
 // A prime that divides one of x, x + 1 has to divide the same one of y, y + 1
 // when x and y have the same parity (a pair of the first kind), and the other
 // one else (the second kind; the prime 2 tells).  Different sets seldom pass
 // the first 64 primes.
 __device__ __forceinline__ bool may_be_equal(const JoinParams& P, uint64_t x, uint64_t y) {
   const bool cross = (x ^ y) & 1;
-  for (uint32_t i0 = 1; i0 < P.n_primes; i0 += 64) {
-    const uint32_t i = i0 + lane_id();
-    const PrimeInv v = P.pinv[i < P.n_primes ? i : P.n_primes - 1];
-    const bool a0 = x * v.inv <= v.lim, a1 = (x + 1) * v.inv <= v.lim;
-    const bool b0 = y * v.inv <= v.lim, b1 = (y + 1) * v.inv <= v.lim;
-    if (__any(cross ? a0 != b1 || a1 != b0 : a0 != b0 || a1 != b1)) return false;
-    if (P.primes[i0] >= (1u << 13)) break;
+  for (uint32_t i0 = 1; i0 < P.n_primes; i0 += 256) {
+    PrimeInv v[4];  // four rounds read together
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t i = i0 + 64 * u + lane_id();
+      v[u] = P.pinv[i < P.n_primes ? i : P.n_primes - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool a0 = x * v[u].inv <= v[u].lim, a1 = (x + 1) * v[u].inv <= v[u].lim;
+      const bool b0 = y * v[u].inv <= v[u].lim, b1 = (y + 1) * v[u].inv <= v[u].lim;
+      if (__any(cross ? a0 != b1 || a1 != b0 : a0 != b0 || a1 != b1)) return false;
+    }
+    if (P.primes[i0] >= (1u << 11)) break;
   }
   return true;
 }
@@ -667,6 +647,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
   __shared__ uint32_t matches;  // words of this partition whose kept bits met
   __shared__ WordMatch match[kMatchMax];
   const int tid = threadIdx.x;
+  note_time(P.flags, K_JOIN);
   const uint64_t sbk = blockIdx.x;
   if (sbk >= P.n_sub) return;
   const uint32_t n = min(P.cnt2[sbk], P.cap2);
@@ -789,6 +770,7 @@ __global__ __launch_bounds__(BLOCK) void k_join_sort(JoinParams P) {
   static_assert(kJoinCap <= (1 << kIdx), "index field");
   __shared__ uint64_t key[kJoinCap];
   const int tid = threadIdx.x;
+  note_time(P.flags, K_JOIN);
   const uint64_t sbk = blockIdx.x;
   if (sbk >= P.n_sub) return;
   const uint32_t n = min(P.cnt2[sbk], P.cap2);
@@ -897,6 +879,15 @@ __device__ __forceinline__ void report(const VerifyParams& P, uint32_t active) {
   const uint32_t pairs = min(flags[kFlagOut], min(P.out_cap, kReportPairs));
   if (threadIdx.x < 16) P.report->n.flags[threadIdx.x] = flags[threadIdx.x];
   if (threadIdx.x < kAccCount) P.report->n.acc[threadIdx.x] = *(const volatile unsigned long long*)&n->acc[threadIdx.x];
+  if (threadIdx.x < kKernels) {
+    unsigned long long t = *(const volatile unsigned long long*)&n->ticks[threadIdx.x];
+    if (threadIdx.x == K_VERIFY) {  // up to here
+      t += wall_clock64() - *(const volatile unsigned long long*)&n->since;
+      n->ticks[K_VERIFY] = t;
+      n->running = 0;
+    }
+    P.report->n.ticks[threadIdx.x] = t;
+  }
   if (threadIdx.x < pairs) P.report->pairs[threadIdx.x] = P.out[threadIdx.x];
   __syncthreads();
   if (threadIdx.x == 0) P.flags[kFlagCand] = P.flags[kFlagDone] = 0;
@@ -910,6 +901,7 @@ __global__ __launch_bounds__(BLOCK) void k_verify(VerifyParams P) {
   constexpr int NV = 6;  // m, m+1, n, n+1 and, for the third condition, m+d, n+d (d = 2)
   __shared__ uint64_t red_r[NV][BLOCK], red_s[NV][BLOCK];
   const int tid = threadIdx.x;
+  note_time(P.flags, K_VERIFY);
   const uint32_t n_cand = min(*P.n_cand, P.cand_cap);
   const uint32_t active = max(1u, min(n_cand, gridDim.x));  // workgroups with candidates, or the first
   if (blockIdx.x >= active) return;
@@ -1033,6 +1025,8 @@ __global__ __launch_bounds__(256) void k_begin(BeginParams P) {
   const uint32_t t = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
   if (P.n && t < 16) P.n->flags[t] = 0;
   if (P.n && t < kAccCount) P.n->acc[t] = 0;
+  if (P.n && t < kKernels) P.n->ticks[t] = 0;
+  if (P.n && t == 0) P.n->running = 0;
   for (uint32_t i = t; i < P.n_cnt2; i += step) P.cnt2[i] = 0;
   if (P.n_queries == 1) {
     if (t == 0) {

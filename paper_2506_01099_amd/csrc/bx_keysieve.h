@@ -50,17 +50,6 @@ constexpr int kFixed = 7, kFixedSlots = 73, kFixedPer = 2;
 __device__ constexpr uint16_t kFixedQ[kFixed] = {27, 125, 343, 121, 169, 289, 361};
 __device__ constexpr uint8_t kFixedP[kFixed] = {3, 5, 7, 11, 13, 17, 19};
 
-// A multiple of a power kFixedQMax < q <= kMidMax: jq = j * q past the power's
-// first multiple in a block.  (Slots that stand for nothing have jq = 2^31.)
-struct MidSlot {
-  double q, invq;
-  uint32_t jq, p;
-};
-// A power above kMidMax; the table ends in entries with q = infinity.
-struct SparsePow {
-  double q, invq;
-};
-
 struct KeyParams {
   const Query* queries;
   const uint64_t* seg_prefix;  // n_queries + 1: first segment of each query
@@ -68,8 +57,8 @@ struct KeyParams {
   uint64_t n_segs;
   uint32_t seg_len;
   const MidSlot* mid;
-  const SparsePow* sp;
-  const uint32_t* sp_p;  // their primes
+  PowerTables powers;
+  uint32_t sparse_first;  // powers above kMidMax in powers.pw
   uint64_t* spill;       // kKeySpill words per workgroup
   uint32_t* flags;
   int batch;
@@ -244,6 +233,7 @@ __device__ __forceinline__ void put_words(KeySh& sh, const KeyParams& P, bool ke
 // One workgroup per CU walks its segments (s mod W).
 __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
   __shared__ KeySh sh;
+  note_time(P.flags, K_SIEVE);
   const uint32_t lane = lane_id();
   const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* cell = sh.cell + wid * kCellPitch;
@@ -319,9 +309,7 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
       const uint32_t nsub = (len + kSub - 1) / kSub;
       const double S = static_cast<double>(start);
       // 1. Every second block begins a chunk: the hits of the powers above
-      // kMidMax on its positions 0 .. chunk length, one multiple each (up to
-      // four of the smallest).  Each round's powers are read while the round
-      // before is at work.
+      // kMidMax on its positions 0 .. chunk length.
       const uint32_t c0 = static_cast<uint32_t>((start - seg0) % kKeyChunk);  // the block's place in the chunk
       MidSlot m[kMidPer];
 #pragma unroll
@@ -330,44 +318,17 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
       if (c0 == 0) {
         if (tid == 0) sh.sparse_n = 0;
         __syncthreads();
-        const double Lc = static_cast<double>(min(static_cast<uint64_t>(kKeyChunk), seg1 - start)), Vd = S + Lc;
-        // (Read by 32-bit byte offsets from the table's start.)
-        auto power = [&](uint32_t i) {
-          return *reinterpret_cast<const SparsePow*>(reinterpret_cast<const uint8_t*>(P.sp) + i * static_cast<uint32_t>(sizeof(SparsePow)));
-        };
-        SparsePow wn[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) wn[u] = power(tid + u * kKeyBlock);
-        for (uint32_t i0 = tid;; i0 += 4 * kKeyBlock) {
-          SparsePow w[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) w[u] = wn[u];
-          if (__all(w[0].q > Vd)) break;
-#pragma unroll
-          for (int u = 0; u < 4; ++u) wn[u] = power(i0 + (4 + u) * kKeyBlock);
-          double j[4];
-          bool any = false;
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            j[u] = first_multiple(S, w[u].q, w[u].invq);  // not a number for q = infinity
-            any |= j[u] <= Lc;
-          }
-          if (any) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              for (; j[u] <= Lc; j[u] += w[u].q) {
-                const uint64_t e = static_cast<uint32_t>(j[u]) | (static_cast<uint64_t>(P.sp_p[i0 + u * kKeyBlock]) << 19);
-                const uint32_t k = atomicAdd(&sh.sparse_n, 1u);
-                if (k < kSparseMax)
-                  sh.sparse[k] = e;
-                else if (k - kSparseMax < kSpillHalf)
-                  spill[k - kSparseMax] = e;
-                else
-                  atomicOr(&P.flags[kFlagSpillOverflow], 1u);
-              }
-            }
-          }
-        }
+        const double Lc = static_cast<double>(min(static_cast<uint64_t>(kKeyChunk), seg1 - start));
+        sparse_hits<kKeyBlock, 8>(P.powers, P.sparse_first, S, Lc, tid, [&](uint32_t j, uint32_t p) {
+          const uint64_t e = j | (static_cast<uint64_t>(p) << 19);
+          const uint32_t k = atomicAdd(&sh.sparse_n, 1u);
+          if (k < kSparseMax)
+            sh.sparse[k] = e;
+          else if (k - kSparseMax < kSpillHalf)
+            spill[k - kSparseMax] = e;
+          else
+            atomicOr(&P.flags[kFlagSpillOverflow], 1u);
+        });
       }
       if (tid == 0) sh.spill_n = 0;
       __syncthreads();
