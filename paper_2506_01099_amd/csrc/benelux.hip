@@ -87,6 +87,7 @@ struct DevBuf {
 
 struct Plan {
   uint32_t passes = 1, b1bits = 0, b2bits = 0, group = 1;
+  bool direct = false;  // the first level's buckets are the partitions: no second level
   uint64_t cap1 = 0;
   uint32_t cap2 = 0;
   uint64_t bytes = 0;
@@ -119,6 +120,7 @@ struct bx_ctx {
   PrimeInv* d_pinv = nullptr;  // per prime: p^-1 mod 2^64 and floor((2^64 - 1) / p) (divisibility tests)
   PowerTables powers{nullptr, nullptr, nullptr, nullptr};
   uint32_t sparse_first = 0;  // powers.pw from here on are above kMidMax
+  KeyLuts* d_luts = nullptr;
   MidSlot* d_mid = nullptr;   // the key sieve's slots of the powers up to kMidMax
   DenseTab* d_dense[2] = {nullptr, nullptr};
   MidSlot* d_small[2] = {nullptr, nullptr};  // the same powers' multiples, for the small-query class
@@ -368,7 +370,21 @@ int build_tables(bx_ctx* c) {
       BX_HIP(hipMemcpy(p, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice));
       return BX_OK;
     };
+    std::vector<KeyLuts> luts(1);
+    KeyLuts& t = luts[0];
+    for (uint32_t b = 0; b < 64; ++b) {  // bits 0, 1: 9 | x, 9 | x + 1; then 25 and 49
+      t.small_f[b].x = (b & 1 ? 3.0 : 1.0) * (b & 4 ? 5.0 : 1.0) * (b & 16 ? 7.0 : 1.0);
+      t.small_f[b].y = (b & 2 ? 3.0 : 1.0) * (b & 8 ? 5.0 : 1.0) * (b & 32 ? 7.0 : 1.0);
+    }
+    for (uint32_t i = 0; i < sizeof(t.lut3); ++i) {
+      const uint32_t m = i % 729;
+      t.lut3[i] = m == 0 ? 81 : m % 243 == 0 ? 27 : m % 81 == 0 ? 9 : 3;
+    }
+    for (uint32_t i = 0; i < sizeof(t.lut225); ++i)
+      t.lut225[i] = (i % 9 == 0 ? 1 : 0) | (i % 9 == 8 ? 2 : 0) | (i % 25 == 0 ? 4 : 0) | (i % 25 == 24 ? 8 : 0);
+    for (uint32_t i = 0; i < sizeof(t.lut49); ++i) t.lut49[i] = (i % 49 == 0 ? 16 : 0) | (i % 49 == 48 ? 32 : 0);
     int rc;
+    if ((rc = up(&c->d_luts, luts)) != BX_OK) return rc;
     if ((rc = up(&c->powers.pw, pw)) != BX_OK || (rc = up(&c->powers.pw_p, pw_p)) != BX_OK ||
         (rc = up(&c->powers.sq, sq)) != BX_OK || (rc = up(&c->powers.sq_p, sq_p)) != BX_OK)
       return rc;
@@ -411,6 +427,9 @@ uint64_t fixed_bytes(uint32_t sieve_grid) {
          (64ull << 20);
 }
 
+// Compact words (l1_word) carry the join: full fingerprints and the hash join.
+bool words_ok(const bx_ctx* c) { return c->compact && c->fp_mask == (1ull << kFpBits) - 1 && !c->join_sort; }
+
 // Choose the number of hash passes P (any integer: pass p keeps the keys whose
 // pass hash falls in the p-th of P equal ranges) and the two partition
 // fan-outs.  One pass's words live in the first-level buckets (8 B each);
@@ -438,13 +457,19 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
     // partition in 0.160 ms with 2^3 x 2^9 against 0.296 with 2 x 2^11.  With
     // fewer (1.1e5 entries: 18 against 36 us) the regions are too short.
     if (n_pass >= 8.0 * 2048.0 * W) b1 = std::max(b1, 3u);
+    // A short range needs no second level: up to 2^10 buckets of 512 entries
+    // on average, or up to 4096, are joined as they are.  (1.1e5 entries: 21 us
+    // for partition and join become one launch of 8; beyond 4e6 the regions of
+    // a bucket have too few words each to gather.)
+    p.direct = words_ok(c) && c->force_b1 < 0 && c->force_b2 < 0 && c->force_group == 0 && n_pass <= 4096.0 * 1024.0;
+    if (p.direct) b1 = n_pass <= 4096.0 * 256.0 ? std::min<uint32_t>(8, ceil_log2(n_pass / 512.0)) : ceil_log2(n_pass / 4096.0);
     if (c->force_b1 >= 0) b1 = static_cast<uint32_t>(c->force_b1);
     p.b1bits = b1;
     const double bucket = n_pass / std::ldexp(1.0, static_cast<int>(b1));
     // Each sieve workgroup owns one region per bucket (no atomics); it holds
     // that workgroup's integers of the bucket and pass, plus slack.
     const double region = static_cast<double>(share) / P / std::ldexp(1.0, static_cast<int>(b1));
-    p.cap1 = round_up(static_cast<uint64_t>(std::ceil(region * 1.05)) + 256, 64);
+    p.cap1 = round_up(static_cast<uint64_t>(std::ceil(p.direct ? region + 8.0 * std::sqrt(region) + 24.0 : region * 1.05 + 256.0)), 64);
     // Partitions of at most ~7.6k entries on average: with the bucket-to-bucket
     // spread (3%) and the partition-to-partition spread (a few sigma of ~90)
     // they stay within one LDS join chunk (8192 entries).
@@ -453,6 +478,7 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
     // entries.
     uint32_t b2 = bucket * 1.03 > 7600.0 ? ceil_log2(bucket * 1.03 / 7600.0) : 0;
     while (b2 < 8 && bucket > 1024.0 * std::ldexp(1.0, static_cast<int>(b2))) ++b2;
+    if (p.direct) b2 = 0;
     if (c->force_b2 >= 0) b2 = static_cast<uint32_t>(c->force_b2);
     if (b2 > 11 || b1 + b2 > 32) {
       if (c->force_passes > 0) return fail(BX_ENOMEM, "forced pass count leaves partitions too large");
@@ -468,8 +494,9 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
     }
     const uint64_t nb1 = 1ull << b1, nb2 = 1ull << b2;
     uint32_t G = c->force_group > 0 ? static_cast<uint32_t>(c->force_group) : 8u;
-    if (G > nb1) G = static_cast<uint32_t>(nb1);
+    if (G > nb1 || p.direct) G = static_cast<uint32_t>(nb1);
     p.group = G;
+    if (p.direct) p.cap2 = 0;
     p.bytes = nb1 * sieve_grid * p.cap1 * sizeof(uint64_t) + G * nb2 * p.cap2 * sizeof(Entry) +
               (nb1 * sieve_grid + G * nb2) * 4;
     if (p.bytes + fixed <= c->budget) {
@@ -822,7 +849,7 @@ int plan_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, Job* j, JobBufs* nb)
   const uint64_t chunks = static_cast<uint64_t>(j->sieve_grid) * j->cpr;  // per bucket
   // Persistent partition grid: one workgroup per CU (measured faster than two), a multiple
   // of 8 so that every XCD serves its share of the group's buckets.
-  const uint64_t per = 8 / j->G;
+  const uint64_t per = plan.direct ? 1 : 8 / j->G;
   j->part_grid = 8ull * std::min<uint64_t>(std::max(1, c->n_cu / 8), (chunks + per - 1) / per);
   if (j->part_grid > 0x7FFFFFFFull) return fail(BX_EINTERNAL, "partition grid too large");
   j->gmask = batch ? kGrpMask : 0u;
@@ -843,8 +870,7 @@ int plan_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, Job* j, JobBufs* nb)
     uint32_t keep = std::min(kl, 64 - j->wl_bits);
     if (c->compact_fp_bits) keep = std::min(keep, c->compact_fp_bits);
     j->low_mask = (1ull << keep) - 1;
-    // Compact words need the full fingerprint (no test mask) and the hash join.
-    j->compact = c->compact && c->fp_mask == (1ull << kFpBits) - 1 && !c->join_sort;
+    j->compact = words_ok(c);
     j->cand_fp_mask = j->compact ? j->low_mask : c->fp_mask & (j->kl_mask | (0x7FFull << 42));
     if (s.n_segs == 0) j->cand_fp_mask = c->fp_mask;  // small-class queries only: whole fingerprints
   }
@@ -911,6 +937,7 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
   P.n_queries = static_cast<uint32_t>(j.s->q.size());
   P.n_segs = j.s->n_segs;
   P.seg_len = j.s->seg_len;
+  P.luts = c->d_luts;
   P.mid = c->d_mid;
   P.powers = c->powers;
   P.sparse_first = c->sparse_first;
@@ -963,7 +990,7 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
     Q.l2c = static_cast<uint64_t*>(c->l2.p);
     Q.wl_bits = j.wl_bits;
     Q.low_mask = j.low_mask;
-    {
+    if (!plan.direct) {
       c->stats.launches[K_PART]++;
       const dim3 pg(static_cast<uint32_t>(j.part_grid));
       if (j.compact)
@@ -986,13 +1013,19 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
     J.wl_bits = j.wl_bits;
     J.low_mask = j.low_mask;
     J.src = src;
+    J.l1 = Q.l1;
+    J.cap1 = plan.cap1;
+    J.cnt1 = Q.cnt1;
+    J.kl_mask = j.kl_mask;
     J.primes = c->d_primes;
     J.pinv = c->d_pinv;
     J.n_primes = static_cast<uint32_t>(c->primes.size());
     {
       c->stats.launches[K_JOIN]++;
-      if (j.compact)
-        hipLaunchKernelGGL((k_join_c<kJoinBlock>), dim3(static_cast<uint32_t>(j.ngsub)), dim3(kJoinBlock), 0, st, J);
+      if (plan.direct)
+        hipLaunchKernelGGL((k_join_c<kJoinBlock, true>), dim3(static_cast<uint32_t>(j.ngsub)), dim3(kJoinBlock), 0, st, J);
+      else if (j.compact)
+        hipLaunchKernelGGL((k_join_c<kJoinBlock, false>), dim3(static_cast<uint32_t>(j.ngsub)), dim3(kJoinBlock), 0, st, J);
       else if (c->join_sort)
         hipLaunchKernelGGL((k_join_sort<kJoinBlock>), dim3(static_cast<uint32_t>(j.ngsub)), dim3(kJoinBlock), 0, st, J);
       else
@@ -1184,9 +1217,9 @@ int run_passes_graph(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* re
   // Every launch shape, every option baked into a kernel argument or choice,
   // and every buffer address the graph's kernels use.
   std::snprintf(key, sizeof(key),
-                "%u %llu %u %u %u %u %llu %u %d %u %u %d %u %d %d %llx %u %d %zu %d %u %llx %p %p %p %p %p %p %p %p %p %p %p %p %p %p",
+                "%u %llu %u %u %u %u %d %llu %u %d %u %u %d %u %d %d %llx %u %d %zu %d %u %llx %p %p %p %p %p %p %p %p %p %p %p %p %p %p",
                 j.plan.passes, static_cast<unsigned long long>(j.plan.cap1), j.plan.cap2, j.plan.b1bits, j.plan.b2bits,
-                j.G, static_cast<unsigned long long>(j.s->n_segs), static_cast<uint32_t>(j.s->q.size()), j.batch,
+                j.G, static_cast<int>(j.plan.direct), static_cast<unsigned long long>(j.s->n_segs), static_cast<uint32_t>(j.s->q.size()), j.batch,
                 j.kinds, c->third_off, c->tile, j.s->seg_len, c->prune, c->join_sort,
                 static_cast<unsigned long long>(c->fp_mask), c->small_max, c->small_block, j.s->small.size(),
                 static_cast<int>(j.compact), j.wl_bits, static_cast<unsigned long long>(j.low_mask), c->l1.p,
@@ -1801,6 +1834,7 @@ void bx_destroy(bx_ctx* c) {
   if (c->powers.sq) (void)hipFree(const_cast<float*>(c->powers.sq));
   if (c->powers.sq_p) (void)hipFree(const_cast<uint32_t*>(c->powers.sq_p));
   if (c->d_mid) (void)hipFree(c->d_mid);
+  if (c->d_luts) (void)hipFree(c->d_luts);
   for (DenseTab* d : c->d_dense)
     if (d) (void)hipFree(d);
   for (MidSlot* d : c->d_small)

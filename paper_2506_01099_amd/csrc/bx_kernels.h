@@ -460,6 +460,11 @@ struct JoinParams {
   uint32_t wl_bits;
   uint64_t low_mask;
   WordSource src;
+  // First-level buckets joined as they are (k_join_c<DIRECT>): the regions.
+  const uint64_t* l1;
+  uint64_t cap1;
+  const uint32_t* cnt1;  // W x B1
+  uint64_t kl_mask;
   const uint32_t* primes;  // 2, 3, 5, ...
   const PrimeInv* pinv;
   uint32_t n_primes;
@@ -637,8 +642,12 @@ __device__ __forceinline__ bool may_be_equal(const JoinParams& P, uint64_t x, ui
 // that found it 0.5 ms for an equal pair, a wave about a microsecond.)  A chunk
 // with more matches than the list holds walks its chains once more instead and
 // makes every match a candidate.
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void k_join_c(JoinParams P) {
+//
+// DIRECT: of a short range the first level's buckets are the partitions, and
+// the workgroup gathers its bucket's words from the regions into LDS (2^20
+// integers: a partition launch of 15 us less).
+template <int BLOCK, bool DIRECT>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DIRECT ? 4 : 8))) void k_join_c(JoinParams P) {
   constexpr int EPT = kJoinCap / BLOCK;
   constexpr uint32_t kEmpty = 0xFFFFFFFFu;
   constexpr uint32_t kIdxMask = (1u << kJoinIdxBits) - 1;
@@ -646,18 +655,48 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
   __shared__ __align__(16) uint32_t table[kJoinSlots];
   __shared__ uint32_t matches;  // words of this partition whose kept bits met
   __shared__ WordMatch match[kMatchMax];
+  __shared__ uint64_t gathered[DIRECT ? kJoinCap : 1];
+  __shared__ uint32_t wsum[BLOCK / 64];
   const int tid = threadIdx.x;
   note_time(P.flags, K_JOIN);
   const uint64_t sbk = blockIdx.x;
   if (sbk >= P.n_sub) return;
-  const uint32_t n = min(P.cnt2[sbk], P.cap2);
-  __syncthreads();
-  if (tid == 0) {
-    P.cnt2[sbk] = 0;
-    if (n) atomicAdd(P.joined, static_cast<unsigned long long>(n));
+  uint32_t n;
+  const uint64_t* src;
+  if constexpr (DIRECT) {
+    // Four threads per region, BLOCK / 4 regions at a time (n_sub = B1).
+    n = 0;
+    for (uint32_t w0 = 0; w0 < P.src.W; w0 += BLOCK / 4) {
+      const uint32_t w = w0 + (static_cast<uint32_t>(tid) >> 2), k0 = tid & 3u;
+      const uint64_t region = static_cast<uint64_t>(w) * P.n_sub + sbk;
+      const uint32_t c = w < P.src.W ? min(P.cnt1[region], static_cast<uint32_t>(P.cap1)) : 0u;
+      uint32_t sum;
+      const uint32_t at = n + block_exclusive_scan<BLOCK>(k0 == 0 ? c : 0u, wsum, &sum) - (k0 == 0 ? 0u : c);
+      const uint64_t wl = static_cast<uint64_t>(w) << P.src.li_bits, li_mask = (1ull << P.src.li_bits) - 1;
+      for (uint32_t k = k0; k < c; k += 4) {
+        const uint64_t x = P.l1[region * P.cap1 + k];
+        if (at + k < static_cast<uint32_t>(kJoinCap))
+          gathered[at + k] = ((((x >> P.src.li_bits) & P.kl_mask) & P.low_mask) << P.wl_bits) | wl | (x & li_mask);
+      }
+      n += sum;
+      __syncthreads();
+    }
+    if (n > static_cast<uint32_t>(kJoinCap)) {  // the pass is split
+      if (tid == 0) atomicOr(&P.flags[kFlagL2Overflow], 1u);
+      return;
+    }
+    src = gathered;
+    if (tid == 0 && n) atomicAdd(P.joined, static_cast<unsigned long long>(n));
+  } else {
+    n = min(P.cnt2[sbk], P.cap2);
+    src = P.l2c + sbk * P.cap2;
+    __syncthreads();
+    if (tid == 0) {
+      P.cnt2[sbk] = 0;
+      if (n) atomicAdd(P.joined, static_cast<unsigned long long>(n));
+    }
   }
   if (n < 2) return;
-  const uint64_t* src = P.l2c + sbk * P.cap2;
   const uint32_t pb = P.wl_bits;
   if (tid == 0) matches = 0;  // (barriers follow before the first match)
   auto emit = [&](uint64_t a, uint64_t b) {

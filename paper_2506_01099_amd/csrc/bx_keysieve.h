@@ -50,12 +50,22 @@ constexpr int kFixed = 7, kFixedSlots = 73, kFixedPer = 2;
 __device__ constexpr uint16_t kFixedQ[kFixed] = {27, 125, 343, 121, 169, 289, 361};
 __device__ constexpr uint8_t kFixedP[kFixed] = {3, 5, 7, 11, 13, 17, 19};
 
+// Tables by residues, made on the host and copied into LDS (made there they
+// took 3 of the 19 us of a short range).  By x mod 729, for 27 | x: 3^(v-2),
+// v = min(v_3(x), 6).  By x mod 225 and x mod 49: the bits of small_f.  (Long
+// enough to need no reduction.)
+struct KeyLuts {
+  double2 small_f[64];  // s(x), s(x + 1) by 9 | x, 9 | x + 1, 25 | x, ...
+  uint8_t lut3[729 + kSub + 3], lut225[225 + kSub + 3], lut49[49 + kSub + 3];
+};
+
 struct KeyParams {
   const Query* queries;
   const uint64_t* seg_prefix;  // n_queries + 1: first segment of each query
   uint32_t n_queries;
   uint64_t n_segs;
   uint32_t seg_len;
+  const KeyLuts* luts;
   const MidSlot* mid;
   PowerTables powers;
   uint32_t sparse_first;  // powers above kMidMax in powers.pw
@@ -83,7 +93,7 @@ __host__ __device__ constexpr uint32_t run_log(uint32_t b1bits) { return b1bits 
 struct KeySh {
   __align__(16) uint32_t cell[kKeyWaves * kCellPitch];
   uint64_t queue[kQueueSlots];
-  __align__(16) double2 small_f[64];  // s(x), s(x + 1) by 9 | x, 9 | x + 1, 25 | x, ...
+  __align__(16) KeyLuts lut;
   uint64_t sparse[kSparseMax];        // position in the chunk | p << 19
   uint32_t bits[kKeyWaves * kBitPitch], cbits[kKeyWaves * kBitPitch];
   uint32_t hits[kHitMax];             // position in the subtile | p << 11, by subtile
@@ -91,9 +101,6 @@ struct KeySh {
   uint32_t cur[kB1Max];               // words claimed per bucket
   uint32_t sparse_n, spill_n;
   uint16_t rec[kKeyWaves * kRecMax];  // kept integers of each wave's subtile
-  // By x mod 729, for 27 | x: 3^(v-2), v = min(v_3(x), 6).  By x mod 225 and
-  // x mod 49: the bits of small_f.  (Long enough to need no reduction.)
-  uint8_t lut3[729 + kSub + 3], lut225[225 + kSub + 3], lut49[49 + kSub + 3];
 };
 static_assert(sizeof(KeySh) <= 160 * 1024, "LDS of a CU");
 
@@ -245,19 +252,9 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
     for (uint32_t i = tid; i < kKeyWaves * kCellPitch; i += kKeyBlock) sh.cell[i] = 1u;
     for (uint32_t i = tid; i < kQueueSlots; i += kKeyBlock) sh.queue[i] = kNoWord;
     for (uint32_t i = tid; i < kKeyWaves * kBitPitch; i += kKeyBlock) sh.bits[i] = sh.cbits[i] = 0u;
-    for (uint32_t i = tid; i < sizeof(sh.lut3); i += kKeyBlock) {
-      const uint32_t t = i % 729;
-      sh.lut3[i] = t == 0 ? 81 : t % 243 == 0 ? 27 : t % 81 == 0 ? 9 : 3;
-    }
-    for (uint32_t i = tid; i < sizeof(sh.lut225); i += kKeyBlock)
-      sh.lut225[i] = (i % 9 == 0 ? 1 : 0) | (i % 9 == 8 ? 2 : 0) | (i % 25 == 0 ? 4 : 0) | (i % 25 == 24 ? 8 : 0);
-    for (uint32_t i = tid; i < sizeof(sh.lut49); i += kKeyBlock)
-      sh.lut49[i] = (i % 49 == 0 ? 16 : 0) | (i % 49 == 48 ? 32 : 0);
-    if (tid < 64) {
-      const uint32_t b = tid;
-      sh.small_f[b].x = (b & 1 ? 3.0 : 1.0) * (b & 4 ? 5.0 : 1.0) * (b & 16 ? 7.0 : 1.0);
-      sh.small_f[b].y = (b & 2 ? 3.0 : 1.0) * (b & 8 ? 5.0 : 1.0) * (b & 32 ? 7.0 : 1.0);
-    }
+    static_assert(sizeof(KeyLuts) % 4 == 0, "copied in words");
+    for (uint32_t i = tid; i < sizeof(KeyLuts) / 4; i += kKeyBlock)
+      reinterpret_cast<uint32_t*>(&sh.lut)[i] = reinterpret_cast<const uint32_t*>(P.luts)[i];
     for (uint32_t b = tid; b < kB1Max; b += kKeyBlock) sh.cur[b] = 0;
   }
   // This lane's static slots: a power's multiple slot_jq past its first one in
@@ -460,7 +457,7 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
             pos[u] = f[u] + slot_jq[u];
             v[u] = slot_p[u];
             on[u] = pos[u] <= kSub;
-            if (slot_p[u] == 3) v[u] = sh.lut3[min(pos[u] + o729, 728u + kSub)];
+            if (slot_p[u] == 3) v[u] = sh.lut.lut3[min(pos[u] + o729, 728u + kSub)];
           }
           {
             constexpr int u = kFixedPer - 1;
@@ -521,8 +518,11 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
             K |= C | (C >> 1);
           }
         }
-        const uint32_t left = cntv > kPerLane * lane ? cntv - kPerLane * lane : 0u;
-        K &= left >= kPerLane ? kLaneMask : (1u << left) - 1u;
+        K &= kLaneMask;
+        if (cntv < static_cast<uint32_t>(kSub)) {  // uniform
+          const uint32_t left = cntv > kPerLane * lane ? cntv - kPerLane * lane : 0u;
+          if (left < kPerLane) K &= (1u << left) - 1u;
+        }
         const uint32_t pc = __popc(K);
         const uint32_t inc = wave_inclusive_scan(pc);
         const uint32_t total = __builtin_amdgcn_readlane(inc, 63);
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
             bool keep = q0 + lane < nrec;
             const uint32_t i = rec[keep ? q0 + lane : 0u];
             const uint32_t E0 = cell[i], E1 = cell[i + 1];
-            const double2 sf = sh.small_f[sh.lut225[i + o225] | sh.lut49[i + o49]];
+            const double2 sf = sh.lut.small_f[sh.lut.lut225[i + o225] | sh.lut.lut49[i + o49]];
             const uint64_t x = x0 + i;
             const double xd = x0d + static_cast<double>(i);
             // The even one of x, x + 1 has the factor 2^(a-1), half its lowest
