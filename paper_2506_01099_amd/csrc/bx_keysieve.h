@@ -427,15 +427,15 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
         // Below b / 2 a squarefree y of {x, x + 1} with y * M <= b is kept
         // too, M = max(2, rad(z) - 1) of its neighbour z: then e(z) >= ethr.
         // With ethr small every x with a non-squarefree neighbour is looked
-        // at; else those next to a z with 105 * 2^(a-1) * E(z) >= ethr, marked
-        // in cbits.
+        // at (68% of them); else those next to a z with 105 * 2^(a-1) * E(z) >=
+        // ethr, marked in cbits (from ethr = 1024 on at most a quarter).
         float ethr = 0.f;
         uint32_t look = 0;  // 0: the bits decide, 1: all, 2: one non-squarefree, 3: marked
         if (!P.prune) look = 1;
         if (lower) {
           const double bd = static_cast<double>(qb);
           ethr = static_cast<float>(0.99 * x0d / (bd / x0d + 1.0));
-          look = x0d * x0d <= bd + 8 ? 1 : ethr < 16384.f ? 2 : 3;
+          look = x0d * x0d <= bd + 8 ? 1 : ethr < 1024.f ? 2 : 3;
         }
         auto mark = [&](uint32_t pos, uint32_t e) {
           atomicOr(&bits[pos >> 5], 1u << (pos & 31u));

@@ -39,6 +39,7 @@ struct SmallParams {
 template <int T, int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(BLOCK / 128 > 4 ? 8 : 4))) void k_small(SmallParams P) {
   constexpr int ITER = T / BLOCK;
+  static_assert(ITER <= 32 && (ITER % 2 == 0), "kept bits; two parts");
   constexpr int SLOTS = (dense_slot_cap(T) + BLOCK - 1) / BLOCK;
   constexpr uint32_t kPart = T / 2;  // kept integers joined at once (table of T slots, load <= 0.5)
   constexpr uint32_t kEmpty = 0xFFFFFFFFu;
@@ -78,25 +79,42 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(BLOCK / 1
   // The other powers (q > T >= L): at most one multiple in [a, b] each.
   sparse_hits<BLOCK, 8>(P.powers, P.n_dense, S, Ld, tid, [&](uint32_t j, uint32_t p) { lds_div(&sh.tile[j], p, inv32(p)); });
   __syncthreads();
-  // Member test and fingerprints, kept in registers; kept integers are
-  // numbered over the workgroup.
-  uint64_t fp[ITER];
-  uint32_t mine = 0;
+  // Member test; the kept integers are numbered over the workgroup and their
+  // fingerprints made one per lane (made where they are found, eight rounds of
+  // which few lanes take part, they took a third of the kernel).
+  uint32_t keep = 0, mine = 0;  // bit it: integer it * BLOCK + tid
 #pragma unroll
   for (int it = 0; it < ITER; ++it) {
     const uint32_t i = it * BLOCK + tid;
-    fp[it] = ~0ull;
-    if (i < L) {
-      const uint64_t r0 = sh.tile[i], r1 = sh.tile[i + 1];
-      if (!P.prune || may_pair(qa + i, r0, r1, qb)) {
-        const uint64_t h = key64(r0 < r1 ? r0 : r1, r0 < r1 ? r1 : r0, grp);
-        fp[it] = (h >> 11) & P.fp_mask;
-        ++mine;
-      }
+    if (i < L && (!P.prune || may_pair(qa + i, sh.tile[i], sh.tile[i + 1], qb))) {
+      keep |= 1u << it;
+      ++mine;
     }
   }
   uint32_t n;
-  const uint32_t first = block_exclusive_scan<BLOCK>(mine, wsum, &n);  // (every radical has been read behind it)
+  const uint32_t first = block_exclusive_scan<BLOCK>(mine, wsum, &n);
+  constexpr int OWN = (T + BLOCK - 1) / BLOCK;  // kept integers tid + k * BLOCK
+  uint64_t fp[OWN];
+  uint32_t at[OWN];
+#pragma unroll
+  for (int part = 0; part < 2; ++part) {
+    if (part * kPart >= n) break;  // uniform
+    uint32_t idx = first - part * kPart;
+    for (uint32_t m = keep; m; m &= m - 1, ++idx)
+      if (idx < kPart) where[idx] = static_cast<uint16_t>(__builtin_ctz(m) * BLOCK + tid);
+    __syncthreads();
+#pragma unroll
+    for (int k = part * OWN / 2; k < (part + 1) * OWN / 2; ++k) {
+      const uint32_t e = k * BLOCK + tid;
+      if (e < n) {
+        const uint32_t i = where[e - part * kPart];
+        const uint64_t r0 = sh.tile[i], r1 = sh.tile[i + 1];
+        at[k] = i;
+        fp[k] = (key64(r0 < r1 ? r0 : r1, r0 < r1 ? r1 : r0, grp) >> 11) & P.fp_mask;
+      }
+    }
+    __syncthreads();
+  }
   if (tid == 0 && n) {
     atomicAdd(&P.acc[kAccEntries], static_cast<unsigned long long>(n));
     atomicAdd(&P.acc[kAccJoined], static_cast<unsigned long long>(n));
@@ -116,49 +134,45 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(BLOCK / 1
   // same chain, so the one that claims the later slot reports the pair (once).
   // More than kPart kept integers (low ranges, the member test off) are joined
   // part by part: those after a part probe it.
-  for (uint32_t p0 = 0; p0 < n; p0 += kPart) {
+#pragma unroll
+  for (int part = 0; part < 2; ++part) {
+    const uint32_t p0 = part * kPart;
+    if (p0 >= n) break;  // uniform
     uint32_t slots = 256;
     while (slots < 2 * min(n - p0, kPart) && slots < static_cast<uint32_t>(T)) slots <<= 1;
     for (uint32_t s = tid; s < slots; s += BLOCK) sh.join.table[s] = kEmpty;
-    uint32_t idx = first;
 #pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      if (fp[it] == ~0ull) continue;
-      if (idx - p0 < kPart) {
-        sh.join.fp[idx - p0] = fp[it];
-        where[idx - p0] = static_cast<uint16_t>(it * BLOCK + tid);
-      }
-      ++idx;
+    for (int k = part * OWN / 2; k < (part + 1) * OWN / 2; ++k) {
+      const uint32_t e = k * BLOCK + tid;
+      if (e >= n) continue;
+      sh.join.fp[e - p0] = fp[k];
+      where[e - p0] = static_cast<uint16_t>(at[k]);
     }
     __syncthreads();
-    idx = first;
 #pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      if (fp[it] == ~0ull) continue;
-      const uint32_t k = idx++ - p0;
-      if (k >= kPart) continue;
-      const uint32_t h = static_cast<uint32_t>(fp[it]);
-      const uint32_t word = (h & ~kIdxMask) | k;
+    for (int k = part * OWN / 2; k < (part + 1) * OWN / 2; ++k) {
+      const uint32_t e = k * BLOCK + tid;
+      if (e >= n) continue;
+      const uint32_t h = static_cast<uint32_t>(fp[k]);
+      const uint32_t word = (h & ~kIdxMask) | (e - p0);
       for (uint32_t s = h & (slots - 1);; s = (s + 1) & (slots - 1)) {
         const uint32_t v = atomicCAS(&sh.join.table[s], kEmpty, word);
         if (v == kEmpty) break;
         const uint32_t o = v & kIdxMask;
-        if (((v ^ word) & ~kIdxMask) == 0 && sh.join.fp[o] == fp[it]) found(it * BLOCK + tid, where[o], fp[it]);
+        if (((v ^ word) & ~kIdxMask) == 0 && sh.join.fp[o] == fp[k]) found(at[k], where[o], fp[k]);
       }
     }
     __syncthreads();
-    if (n - p0 <= kPart) break;
-    idx = first;
+    if (part == 1 || n <= kPart) break;
 #pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      if (fp[it] == ~0ull) continue;
-      const uint32_t k = idx++;
-      if (k < p0 + kPart) continue;
-      const uint32_t h = static_cast<uint32_t>(fp[it]);
+    for (int k = OWN / 2; k < OWN; ++k) {
+      const uint32_t e = k * BLOCK + tid;
+      if (e >= n) continue;
+      const uint32_t h = static_cast<uint32_t>(fp[k]);
       uint32_t s = h & (slots - 1);
       for (uint32_t v = sh.join.table[s]; v != kEmpty; s = (s + 1) & (slots - 1), v = sh.join.table[s]) {
         const uint32_t o = v & kIdxMask;
-        if (((v ^ h) & ~kIdxMask) == 0 && sh.join.fp[o] == fp[it]) found(it * BLOCK + tid, where[o], fp[it]);
+        if (((v ^ h) & ~kIdxMask) == 0 && sh.join.fp[o] == fp[k]) found(at[k], where[o], fp[k]);
       }
     }
     __syncthreads();
