@@ -522,6 +522,7 @@ uint32_t fit_seg_len(uint64_t n, uint64_t wgs, uint32_t longest, uint32_t unit) 
   return static_cast<uint32_t>(std::min<uint64_t>(len, longest));
 }
 constexpr uint32_t kKeySegUnit = 4 * kSub;  // a wave per SIMD at work at least
+constexpr uint32_t kLowSegUnit = kSub / 4;  // where all integers may be kept
 
 // Radical-sieve segments of a range: two workgroups per CU and tile shape.
 uint32_t rad_seg_len(const bx_ctx* c, uint64_t n) {
@@ -530,7 +531,7 @@ uint32_t rad_seg_len(const bx_ctx* c, uint64_t n) {
 
 struct Segs {
   uint32_t seg_len = 0;
-  std::vector<Query> q;
+  std::vector<Query> q;      // the queries; of a search of one range, its parts (make_segs)
   std::vector<uint64_t> prefix;
   std::vector<uint32_t> small;  // queries served by the small-query class (no segments)
   uint64_t n_segs = 0;
@@ -551,7 +552,7 @@ struct Segs {
 constexpr int kZones = 2;
 constexpr double kZoneRate[kZones] = {1.0, 0.125};
 
-double sqrt_b(const Query& q) { return std::sqrt(static_cast<double>(q.b)); }
+double sqrt_b(const Query& q) { return std::sqrt(static_cast<double>(q.top)); }
 
 // Zone k of query q covers x in [zone_lo(k), zone_lo(k + 1)).
 uint64_t zone_lo(const Query& q, int k) {
@@ -562,7 +563,7 @@ uint64_t zone_lo(const Query& q, int k) {
 
 // The scattered kept x above 2 sqrt(b) (none when the query lies above b / 2).
 double scattered(const bx_ctx* c, const Query& q) {
-  if (!c->prune || q.a > q.b / 2) return 0.0;
+  if (!c->prune || q.a > q.top / 2) return 0.0;
   return 2.0 * sqrt_b(q);
 }
 
@@ -581,7 +582,7 @@ double kept_expected(const bx_ctx* c, const Query& q) {
   if (!c->prune) return static_cast<double>(q.b - q.a);
   const uint64_t low = std::min(q.b, std::max(q.a, zone_lo(q, 1)));
   return static_cast<double>(low - q.a) + 0.108 * static_cast<double>(q.b - low) +
-         (q.a > q.b / 2 ? 0.0 : 1.2 * sqrt_b(q)) + 3.0;
+         (q.a > q.top / 2 ? 0.0 : 1.2 * sqrt_b(q)) + 3.0;
 }
 
 // Bound on the number of kept x in [u, v) of query q.
@@ -625,9 +626,9 @@ uint64_t max_share(const bx_ctx* c, const Segs& s, uint32_t W) {
   if (W == 0) return 0;
   std::vector<double> diff(W + 1, 0.0);
   std::vector<double> extra(W, 0.0);  // the shorter last segment of each query
-  const uint64_t L = s.seg_len;
   for (size_t i = 0; i < s.q.size(); ++i) {
     const Query& q = s.q[i];
+    const uint64_t L = q.seg_len;
     const uint64_t len = q.b > q.a ? q.b - q.a : 0;
     if (len == 0 || s.prefix[i + 1] == s.prefix[i]) continue;  // empty or small-class
     const uint64_t nseg = (len + L - 1) / L, nfull = nseg - 1;
@@ -680,28 +681,49 @@ bool is_small(const bx_ctx* c, const Query& q) {
 // Segments of every query; with small_class, the queries of the small-query
 // class take none and are listed in s->small instead (searches only: the
 // radical sieve segments every range).
-void make_segs(const bx_ctx* c, Segs* s, bool small_class) {
+//
+// The search of one range (one_range) that reaches below 32 sqrt(b) is sieved
+// in two parts, that low zone in shorter segments, so that it spreads over the
+// chip: there most integers are looked at or kept (one in nine above), and a
+// wave with 1024 kept integers takes ten times its time (3e6 integers: 70000
+// cycles beside 7000).  Sieve of 3e6 integers 41 -> 29 us, of 2^32 5.02 -> 4.91
+// ms.  A batch's segments are all alike: its queries fill the chip together.
+void make_segs(const bx_ctx* c, Segs* s, bool small_class, bool one_range) {
+  const uint64_t cus = static_cast<uint64_t>(std::max(1, c->n_cu));
+  uint64_t n = 0;
+  for (Query& q : s->q) {
+    q.top = q.b;
+    if (q.b > q.a && !(small_class && is_small(c, q))) n += q.b - q.a;
+  }
+  s->seg_len = small_class ? fit_seg_len(n, cus, c->seg_len, kKeySegUnit) : rad_seg_len(c, n);
+  for (Query& q : s->q) q.seg_len = s->seg_len;
+  if (one_range && c->prune && n > 0) {
+    Query low = s->q[0];
+    const uint64_t zl = static_cast<uint64_t>(32.0 * sqrt_b(low)) + 1;
+    if (low.a < zl && zl < low.b) {
+      low.b = zl;
+      low.seg_len = std::min(s->seg_len, fit_seg_len(zl - low.a, cus, c->seg_len, kLowSegUnit));
+      s->q[0].a = zl;
+      s->q[0].seg_len = fit_seg_len(s->q[0].b - zl, cus, c->seg_len, kKeySegUnit);
+      s->q.insert(s->q.begin(), low);
+    }
+  }
   s->prefix.assign(s->q.size() + 1, 0);
   s->small.clear();
   s->n_ints = 0;
-  uint64_t acc = 0, n = 0;
+  uint64_t acc = 0;
   double keys = 0.0, expect = 0.0;
-  for (const Query& q : s->q)
-    if (q.b > q.a && !(small_class && is_small(c, q))) n += q.b - q.a;
-  s->seg_len = small_class ? fit_seg_len(n, static_cast<uint64_t>(std::max(1, c->n_cu)), c->seg_len, kKeySegUnit)
-                           : rad_seg_len(c, n);
   for (size_t i = 0; i < s->q.size(); ++i) {
     s->prefix[i] = acc;
     const uint64_t L = s->q[i].b > s->q[i].a ? s->q[i].b - s->q[i].a : 0;
-    if (small_class && is_small(c, s->q[i])) {
+    s->n_ints += L;
+    if (small_class && (!one_range || n == 0) && is_small(c, s->q[i])) {
       s->small.push_back(static_cast<uint32_t>(i));
-      s->n_ints += L;
       continue;
     }
-    acc += (L + s->seg_len - 1) / s->seg_len;
+    acc += (L + s->q[i].seg_len - 1) / s->q[i].seg_len;
     keys += kept_bound(c, s->q[i], s->q[i].a, s->q[i].b);
     expect += kept_expected(c, s->q[i]);
-    s->n_ints += L;
   }
   s->prefix[s->q.size()] = acc;
   s->n_segs = acc;
@@ -718,7 +740,7 @@ int stage_segs(bx_ctx* c, const Segs& s) {
   if ((rc = ensure(c, c->queries, s.q.size() * sizeof(Query))) != BX_OK) return rc;
   if ((rc = ensure(c, c->segpref, s.prefix.size() * sizeof(uint64_t))) != BX_OK) return rc;
   if ((rc = ensure(c, c->smallq, s.small.size() * sizeof(uint32_t))) != BX_OK) return rc;
-  if (s.q.size() <= 1) return BX_OK;
+  if (s.q.size() <= 2) return BX_OK;
   const size_t nq = s.q.size() * sizeof(Query), np = s.prefix.size() * sizeof(uint64_t),
                ns = s.small.size() * sizeof(uint32_t), need = nq + np + ns;
   if (need > c->pin_bytes) {
@@ -752,15 +774,17 @@ int enqueue_begin(bx_ctx* c, const Segs& s, uint64_t n_cnt2, hipStream_t st, boo
   P.small = static_cast<uint32_t*>(c->smallq.p);
   P.n_queries = static_cast<uint32_t>(s.q.size());
   P.n_small = static_cast<uint32_t>(s.small.size());
-  P.one = s.q[0];
-  P.n_segs = s.n_segs;
-  if (s.q.size() > 1) {
+  if (s.q.size() <= 2) {
+    std::copy(s.q.begin(), s.q.end(), P.few);
+    std::copy(s.prefix.begin(), s.prefix.end(), P.few_prefix);
+    std::copy(s.small.begin(), s.small.end(), P.few_small);
+  } else {
     const uint8_t* h = static_cast<const uint8_t*>(c->pin);
     P.staged_queries = reinterpret_cast<const uint64_t*>(h);
     P.staged_prefix = reinterpret_cast<const uint64_t*>(h + s.q.size() * sizeof(Query));
     P.staged_small = reinterpret_cast<const uint32_t*>(h + s.q.size() * sizeof(Query) + s.prefix.size() * sizeof(uint64_t));
   }
-  const uint64_t words = std::max<uint64_t>(n_cnt2, 2 * s.q.size());
+  const uint64_t words = std::max<uint64_t>(n_cnt2, 4 * s.q.size());
   hipLaunchKernelGGL(k_begin, dim3(static_cast<uint32_t>(std::min<uint64_t>((words + 255) / 256, 64))), dim3(256), 0, st, P);
   BX_HIP(hipGetLastError());
   return BX_OK;
@@ -1283,7 +1307,7 @@ int run_search(bx_ctx* c, Segs& s, int batch, uint32_t kinds, std::vector<OutPai
   result->clear();
   int rc = order_after_last(c, st);
   if (rc != BX_OK) return rc;
-  make_segs(c, &s, true);  // (the call drains st: no later call has to wait for it)
+  make_segs(c, &s, true, !batch);  // (the call drains st: no later call has to wait for it)
   if (s.n_segs == 0 && s.small.empty()) return BX_OK;
   Job j;
   if ((rc = prepare_job(c, s, batch, kinds, &j)) != BX_OK) return rc;
@@ -1311,7 +1335,7 @@ int to_pairs(const std::vector<OutPair>& v, bx_pair** out, size_t* count) {
 int radicals_into(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t* dev_out, hipStream_t st, bool clear_flags = true) {
   Segs s;
   s.q.push_back(Query{lo, hi});
-  make_segs(c, &s, false);
+  make_segs(c, &s, false, false);
   if (s.n_segs == 0) return BX_OK;
   int rc;
   if ((rc = stage_segs(c, s)) != BX_OK) return rc;
@@ -1418,7 +1442,7 @@ int run_alg2(bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds, std::vector<OutP
   if ((rc = mark_done(c, st)) != BX_OK) return rc;
   Segs s;
   s.q.push_back(Query{a, b});
-  make_segs(c, &s, false);
+  make_segs(c, &s, false, false);
   const uint64_t cap = s.n_keys + 64;  // bound on the kept integers
   const uint64_t chunk = 1ull << 27;
   const uint64_t n_tiles_max = (cap + kRsTile - 1) / kRsTile, m_max = 256 * n_tiles_max;
@@ -1642,7 +1666,7 @@ void release_workspace(bx_ctx* c) {
 int batch_bytes(bx_ctx* c, const std::vector<Query>& q, bool released, uint64_t* bytes, uint32_t* passes = nullptr) {
   Segs s;
   s.q = q;
-  make_segs(c, &s, true);
+  make_segs(c, &s, true, false);
   *bytes = 0;
   if (passes) *passes = 1;
   if (s.n_segs == 0 && s.small.empty()) return BX_OK;
@@ -2018,8 +2042,8 @@ int bx_radical_segment_dev_noalloc(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t
   B.queries = q;
   B.seg_prefix = pref;
   B.n_queries = 1;
-  B.one = Query{lo, hi};
-  B.n_segs = n_segs;
+  B.few[0] = Query{lo, hi, hi, seg_len, 0};
+  B.few_prefix[1] = n_segs;
   hipLaunchKernelGGL(k_begin, dim3(1), dim3(256), 0, st, B);
   BX_HIP(hipGetLastError());
   SieveParams P;

@@ -301,7 +301,7 @@ struct WordSource {
   const Query* queries;
   const uint64_t* seg_prefix;
   uint32_t n_queries;
-  uint32_t seg_len, W;  // segment length; sieve workgroups
+  uint32_t seg_len, W;  // the longest segment; sieve workgroups
   uint32_t li_bits;
   int batch;
 };
@@ -318,7 +318,7 @@ __device__ __forceinline__ uint64_t word_integer(const WordSource& S, uint32_t w
       hi = mid;
   }
   *grp = S.batch ? lo : 0u;
-  return S.queries[lo].a + (s - S.seg_prefix[lo]) * S.seg_len + li % S.seg_len;
+  return S.queries[lo].a + (s - S.seg_prefix[lo]) * S.queries[lo].seg_len + li % S.seg_len;
 }
 
 // pos43 of an Entry (bx_device.h).
@@ -1054,9 +1054,10 @@ struct BeginParams {
   uint64_t* seg_prefix;
   uint32_t* small;
   uint32_t n_queries, n_small;
-  Query one;        // n_queries = 1
-  uint64_t n_segs;
-  const uint64_t* staged_queries;  // host memory: two words per query, n_queries + 1 words, n_small half words
+  Query few[2];     // n_queries <= 2
+  uint64_t few_prefix[3];
+  uint32_t few_small[2];
+  const uint64_t* staged_queries;  // host memory: the queries, n_queries + 1 words, n_small half words
   const uint64_t* staged_prefix;
   const uint32_t* staged_small;
 };
@@ -1067,17 +1068,15 @@ __global__ __launch_bounds__(256) void k_begin(BeginParams P) {
   if (P.n && t < kKernels) P.n->ticks[t] = 0;
   if (P.n && t == 0) P.n->running = 0;
   for (uint32_t i = t; i < P.n_cnt2; i += step) P.cnt2[i] = 0;
-  if (P.n_queries == 1) {
-    if (t == 0) {
-      P.queries[0] = P.one;
-      P.seg_prefix[0] = 0;
-      P.seg_prefix[1] = P.n_segs;
-      if (P.n_small) P.small[0] = 0;
-    }
+  if (P.n_queries <= 2) {
+    if (t < P.n_queries) P.queries[t] = P.few[t];
+    if (t <= P.n_queries) P.seg_prefix[t] = P.few_prefix[t];
+    if (t < P.n_small) P.small[t] = P.few_small[t];
     return;
   }
   uint64_t* q = reinterpret_cast<uint64_t*>(P.queries);
-  for (uint32_t i = t; i < 2 * P.n_queries; i += step) q[i] = P.staged_queries[i];
+  constexpr uint32_t kWords = sizeof(Query) / sizeof(uint64_t);
+  for (uint32_t i = t; i < kWords * P.n_queries; i += step) q[i] = P.staged_queries[i];
   for (uint32_t i = t; i < P.n_queries + 1; i += step) P.seg_prefix[i] = P.staged_prefix[i];
   for (uint32_t i = t; i < P.n_small; i += step) P.small[i] = P.staged_small[i];
 }

@@ -64,7 +64,7 @@ struct KeyParams {
   const uint64_t* seg_prefix;  // n_queries + 1: first segment of each query
   uint32_t n_queries;
   uint64_t n_segs;
-  uint32_t seg_len;
+  uint32_t seg_len;  // the longest segment
   const KeyLuts* luts;
   const MidSlot* mid;
   PowerTables powers;
@@ -295,9 +295,9 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
       qn = min(step, qn - k * step);
     }
     const uint32_t qi = __builtin_amdgcn_readfirstlane(qlo);
-    const uint64_t qa = P.queries[qi].a, qb = P.queries[qi].b;
-    const uint64_t seg0 = qa + (s - P.seg_prefix[qi]) * static_cast<uint64_t>(P.seg_len);
-    const uint64_t seg1 = min(seg0 + P.seg_len, qb);
+    const uint64_t qb = P.queries[qi].top;
+    const uint64_t seg0 = P.queries[qi].a + (s - P.seg_prefix[qi]) * static_cast<uint64_t>(P.queries[qi].seg_len);
+    const uint64_t seg1 = min(seg0 + P.queries[qi].seg_len, P.queries[qi].b);
     const uint32_t grp = P.batch ? qi : 0u;
 
     for (uint64_t start = seg0; start < seg1; start += kKeyLen) {

@@ -624,6 +624,36 @@ def test_key_sieve_edges(ctx, a, length):
     assert st["candidates"] == join_model.candidates(keys)
 
 
+def low_zone(b):
+    """The integers below which one range's search takes shorter segments."""
+    return int(32.0 * math.sqrt(b)) + 1
+
+
+@pytest.mark.parametrize("a,b", [
+    (1, 8194), (1, 1 << 16), (1, 3 * 10**6), (1, (1 << 24) + 1),
+    (low_zone(10**6) - 1, 10**6), (low_zone(10**6), 10**6), (low_zone(10**6) - 1025, 10**6),
+    (36, low_zone(10**5) + 1 + 10**5), (low_zone(1 << 22) - 257, (1 << 22) - 1)])
+def test_low_zone_parts(ctx, a, b):
+    """A search of one range in two parts of unlike segments against the oracle and
+    against the same range as a batch of one, whose segments are all alike: the pairs,
+    the kept integers and, with few fingerprint bits, the candidates of whole keys."""
+    say(f"low zone [{a}, {b}), parts at {low_zone(b)}")
+    want = oracle.search_range(a, b)
+    rad = oracle.radicals(a, b + 1)
+    got = []
+    try:
+        for keep in (0, 12):
+            ctx.set_option("fp_bits", keep)
+            one = ctx.search_range(a, b)
+            got.append((one, ctx.stats()["entries"], ctx.stats()["joined"]))
+            batch = ctx.search_batch(np.array([a], dtype=np.uint64), np.array([b], dtype=np.uint64))[0]
+            got.append((batch, ctx.stats()["entries"], ctx.stats()["joined"]))
+    finally:
+        ctx.set_option("fp_bits", 0)
+    n = join_model.group_keys(rad, a, b, 0, 0, 1, 12)[1]
+    assert got == [(want, n, n)] * 4
+
+
 @pytest.mark.parametrize("passes", [1, 2, 3, 5, 7, 16, 64])
 def test_pass_count_invariance(ctx, passes):
     ctx.set_option("passes", passes)
