@@ -932,13 +932,25 @@ __device__ __forceinline__ void report(const VerifyParams& P, uint32_t active) {
   if (threadIdx.x == 0) P.flags[kFlagCand] = P.flags[kFlagDone] = 0;
 }
 
+// value's word in lane l (the same in every lane).
+__device__ __forceinline__ uint64_t read_lane64(uint64_t value, int l) {
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(value), l);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(value >> 32), l);
+  return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+
 // One workgroup per candidate pair: rad of m, m+1, n, n+1 by trial division
 // (the definition of the radical), with the cofactor left after dividing out
 // every prime <= sqrt(v) being 1 or one more prime.
+//
+// Bound by latency, a few pairs a call: at most 15 primes divide a value, so a
+// wave multiplies the few lanes that hold one in turn, and the values' last
+// divisions run side by side.  Ten pairs of 3000000 or fewer: 9 -> 6 us
+// (a tree over LDS with eight barriers, four divisions in a row).
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_verify(VerifyParams P) {
   constexpr int NV = 6;  // m, m+1, n, n+1 and, for the third condition, m+d, n+d (d = 2)
-  __shared__ uint64_t red_r[NV][BLOCK], red_s[NV][BLOCK];
+  __shared__ uint64_t red_r[NV][BLOCK / 64], red_s[NV][BLOCK / 64], rad[NV];
   const int tid = threadIdx.x;
   note_time(P.flags, K_VERIFY);
   const uint32_t n_cand = min(*P.n_cand, P.cand_cap);
@@ -986,27 +998,29 @@ __global__ __launch_bounds__(BLOCK) void k_verify(VerifyParams P) {
     }
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      red_r[k][tid] = pr[k];
-      red_s[k][tid] = sm[k];
+      uint64_t r = 1, sq = 1;  // of the wave
+      for (uint64_t m_hit = __ballot(pr[k] != 1); m_hit; m_hit &= m_hit - 1) {
+        const int l = __builtin_ctzll(m_hit);
+        r *= read_lane64(pr[k], l);
+        sq *= read_lane64(sm[k], l);
+      }
+      if ((tid & 63) == 0) {
+        red_r[k][tid >> 6] = r;
+        red_s[k][tid >> 6] = sq;
+      }
     }
     __syncthreads();
-    for (int w = BLOCK / 2; w > 0; w >>= 1) {
-      if (tid < w) {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-          red_r[k][tid] *= red_r[k][tid + w];
-          red_s[k][tid] *= red_s[k][tid + w];
-        }
+    if (tid < NV) {
+      uint64_t r = red_r[tid][0], sq = red_s[tid][0];
+      for (int w = 1; w < BLOCK / 64; ++w) {
+        r *= red_r[tid][w];
+        sq *= red_s[tid][w];
       }
-      __syncthreads();
+      const uint64_t cof = (tid == 0 ? v[0] : tid == 1 ? v[1] : tid == 2 ? v[2] : tid == 3 ? v[3] : tid == 4 ? v[4] : v[5]) / sq;
+      rad[tid] = r * (cof > 1 ? cof : 1);
     }
+    __syncthreads();
     if (tid == 0) {
-      uint64_t rad[NV];
-#pragma unroll
-      for (int k = 0; k < NV; ++k) {
-        const uint64_t cof = v[k] / red_s[k][0];
-        rad[k] = red_r[k][0] * (cof > 1 ? cof : 1);
-      }
       const uint64_t lo_m = rad[0] < rad[1] ? rad[0] : rad[1], hi_m = rad[0] < rad[1] ? rad[1] : rad[0];
       const uint64_t lo_n = rad[2] < rad[3] ? rad[2] : rad[3], hi_n = rad[2] < rad[3] ? rad[3] : rad[2];
       const bool same = (lo_m == lo_n) && (hi_m == hi_n) && m != n &&
