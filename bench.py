@@ -21,16 +21,18 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, 8 TB/s
 VALU_PEAK_INT_OPS = 256 * 64 * 2.4e9  # 256 CUs x 64 lanes/clk x 2.4 GHz (32-bit integer lane-ops/s)
-# Algorithmic 32-bit integer ops per sieved integer: 9 to reduce the factor 2 of a
+# Algorithmic 32-bit integer ops per sieved integer, of the work as defined (the
+# sieve's bit and cell form does part of it with fewer): 9 to reduce the factor 2 of a
 # 64-bit x (add, count trailing zeros, shift), 1.6 for the odd prime-power divisions
 # (0.273 per integer, 6 ops each), 0.9 for the per-segment first-multiple offsets,
 # 6 for the member test, 2.7 to build the entries of the kept 10.7% (key, hash,
 # packing) and 1.1 to rank them for the first partition.
 SIEVE_OPS_PER_INT = 21.0
 ENTRY_BYTES = 12
+FIRST_LEVEL_BYTES = 8  # a word of the sieve's
 CALIB_BYTES = 4 << 30
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_plain_2p36.json")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2506_01099_amd", "csrc", f) for f in ("bx_kernels.h", "bx_device.h")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2506_01099_amd", "csrc", f) for f in ("bx_kernels.h", "bx_device.h", "bx_keysieve.h")]
 
 
 def log(msg):
@@ -172,7 +174,7 @@ def parse_counters(fetch_dir, write_dir):
     w_scale = CALIB_BYTES / (w_copy * 1024) if w_copy else None
     out = {"source_hash": kernel_source_hash(), "calib_bytes": CALIB_BYTES,
            "fetch_scale": f_scale, "write_scale": w_scale, "kernels": {}}
-    for k, keys in (("sieve", ("k_sieve<",)), ("partition", ("k_partition<",)), ("join", ("k_join<", "k_join_c<"))):
+    for k, keys in (("sieve", ("k_sieve<", "k_sieve_keys")), ("partition", ("k_partition<",)), ("join", ("k_join<", "k_join_c<"))):
         key = next((kk for kk in keys if any(kk in name for name in fetch)), keys[0])
         f, w = pick(fetch, key), pick(write, key)
         if f is None or w is None or not f_scale or not w_scale:
@@ -238,6 +240,7 @@ def run_plain(bx, N, steps, warmup, warm_s=None):
 def roofline_from(agg, n_ints_per_step, entries_per_step, steps, traffic):
     ms = agg["kernel_ms"]
     l2 = agg.get("l2_entry_bytes") or ENTRY_BYTES  # second-level entry: 12 B, or an 8 B compact word
+    l1 = agg.get("l1_entry_bytes") or ENTRY_BYTES  # first-level entry
     ln = agg["launches"]
     kinds = {k: ms[k] for k in ("sieve", "partition", "join")}
     dominant = max(kinds, key=kinds.get)
@@ -250,11 +253,11 @@ def roofline_from(agg, n_ints_per_step, entries_per_step, steps, traffic):
         out["sieve"] = {"bound": "alu", "achieved": ach, "peak": VALU_PEAK_INT_OPS / 1e12, "unit": "Tops/s",
                         "frac": ach / (VALU_PEAK_INT_OPS / 1e12), "traffic": traffic_of(traffic, "sieve", ln["sieve"], steps),
                         "avg_launch_ms": avg_ms, "integers_per_launch": ints_per_launch}
-    # Partition: HBM-bound, a 12 B read and a 12 B (or 8 B compact) write per
+    # Partition: HBM-bound, a first-level read and a second-level write per
     # entry (the entries the sieve wrote: the integers that pass the member test).
     if ln["partition"]:
         avg_ms = ms["partition"] / ln["partition"]
-        b = (ENTRY_BYTES + l2) * entries_per_step * steps / ln["partition"]
+        b = (l1 + l2) * entries_per_step * steps / ln["partition"]
         ach = b / (avg_ms * 1e-3) / 1e9
         out["partition"] = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                             "frac": ach / HBM_PEAK_GBS, "traffic": traffic_of(traffic, "partition", ln["partition"], steps),
@@ -268,12 +271,12 @@ def roofline_from(agg, n_ints_per_step, entries_per_step, steps, traffic):
                        "frac": ach / HBM_PEAK_GBS, "traffic": traffic_of(traffic, "join", ln["join"], steps),
                        "avg_launch_ms": avg_ms,
                        "bytes_per_launch": b}
-    # The join as a whole (second scatter + LDS join) against 24 B per key (the
-    # sieve's 12 B entry read and its second-level copy written), whatever the
-    # second-level format, over the join kernels' time.
+    # The join as a whole (second scatter + LDS join) against the bytes per
+    # key of the scatter (the sieve's entry read and its second-level copy
+    # written), over the join kernels' time.
     if ln["partition"] and ln["join"]:
         t = (ms["partition"] + ms["join"]) * 1e-3
-        ach = 2 * ENTRY_BYTES * entries_per_step * steps / t / 1e9
+        ach = (l1 + l2) * entries_per_step * steps / t / 1e9
         out["join_total"] = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                              "frac": ach / HBM_PEAK_GBS}
     return dominant, out
@@ -334,7 +337,7 @@ def main():
     pairs, total, per_step, agg = run_plain(bx, N, args.steps, args.warmup, warm_s)
     ms_step = total / args.steps * 1e3
     value = N / (total / args.steps)
-    dominant, roof = roofline_from(agg, N, agg["entries"], args.steps,
+    dominant, roof = roofline_from(dict(agg, l1_entry_bytes=FIRST_LEVEL_BYTES), N, agg["entries"], args.steps,
                                    load_traffic() if args.log2n == 36 else {})
     line = {
         "metric": "integers sieved+joined/s at N=2^36 (both kinds), %HBM roofline; batched vs plain",

@@ -194,8 +194,10 @@ int bx_autotune(bx_ctx* ctx, const uint64_t* a, const uint64_t* b, size_t q, int
  * architecture is ignored (returns BX_OK, nothing changes). */
 int bx_load_tuning(bx_ctx* ctx, const char* path);
 
-/* Statistics of the last completed call on this context (device times from HIP
- * events recorded on the stream the kernels ran on). */
+/* Statistics of the last completed call on this context.  A search's kernel
+ * times are taken on the device's clock, each from the kernel's start to the
+ * next one's; those of the radical calls and of the schedules 1 and 2 from HIP
+ * events on the stream the kernels ran on. */
 typedef struct {
   uint32_t passes;            /* hash passes run (including split re-runs)        */
   uint32_t retries;           /* passes re-run split in two after an overflow     */
@@ -207,7 +209,8 @@ typedef struct {
   double kernel_ms[6];        /* summed device time per kernel, same order        */
   double total_ms;            /* host wall time of the call                       */
   uint32_t b1_bits, b2_bits;  /* partition fan-outs used                          */
-  uint32_t seg_len, tile;     /* segment length and LDS tile used by the sieve    */
+  uint32_t seg_len, tile;     /* longest segment (short ranges take shorter ones than
+                                 the option) and the radical sieve's LDS tile     */
   double graph_ms;            /* device time of the captured graph (batched calls) */
   uint64_t joined;            /* entries the join kernels read (equals entries)   */
   uint64_t false_candidates;  /* candidates whose sets differ (dropped by verify) */
@@ -220,8 +223,8 @@ int bx_get_stats(bx_ctx* ctx, bx_stats* out);
 
 /* Options (name = value); unknown names are BX_EINVAL.
  *   "passes"       force the number of hash passes (any count, 0 = plan)
- *   "seg_len"      sieve segment length (multiple of the tile, 0 = default)
- *   "timing"       1 = record HIP events per kernel (default 1)
+ *   "seg_len"      longest sieve segment (multiple of the tile, 0 = default)
+ *   "timing"       1 = record HIP events per kernel where they are used (default 1)
  *   "b1_bits"      force the first partition fan-out (0 = plan)
  *   "b2_bits"      force the second partition fan-out, <= 11 (0 = plan)
  *   "group"        first-level buckets per second-level launch (1, 2, 4, 8; 0 = 8)

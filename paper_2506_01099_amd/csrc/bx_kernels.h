@@ -62,10 +62,9 @@ struct SieveSh {
 // bucket: LDS histogram, one global reservation per non-empty bucket, then the
 // runs are written with consecutive threads on consecutive entries (coalesced
 // stores).  cnt/gofs hold NB words; perm holds n.  gcur[b] is the cursor of
-// bucket b: shared by all workgroups (global, one atomic per non-empty bucket)
-// or, with PRIVATE, owned by this workgroup (no atomics).  dst(b, k) stores the
-// k-th entry of the bucket (k < cap).
-template <int BLOCK, int NB, int NMAX, bool PRIVATE, typename Item, typename Bucket, typename Dst, typename Mid>
+// bucket b, shared by all workgroups (global, one atomic per non-empty bucket).
+// dst(b, k) stores the k-th entry of the bucket (k < cap).
+template <int BLOCK, int NB, int NMAX, typename Item, typename Bucket, typename Dst, typename Mid>
 __device__ void scatter_runs(uint32_t n, uint32_t nb, const Item* ent, Bucket sb, uint16_t* perm,
                              uint32_t* cnt, uint32_t* gofs, uint32_t* wsum, uint32_t* gcur, uint64_t cap,
                              uint32_t* flag, Dst dst, Mid mid) {
@@ -101,13 +100,7 @@ __device__ void scatter_runs(uint32_t n, uint32_t nb, const Item* ent, Bucket sb
   for (int k = 0; k < BINS; ++k) {
     const uint32_t b = tid * BINS + k;
     if (b < nb) {
-      uint32_t g;
-      if constexpr (PRIVATE) {  // gcur is this workgroup's own cursor array (LDS)
-        g = gcur[b];
-        gcur[b] = g + loc[k];
-      } else {
-        g = loc[k] ? atomicAdd(&gcur[b], loc[k]) : 0u;
-      }
+      const uint32_t g = loc[k] ? atomicAdd(&gcur[b], loc[k]) : 0u;
       gofs[b] = g - ex;  // slot j of the sorted order lands at run position g + (j - ex)
       cnt[b] = ex;       // becomes the LDS cursor of bucket b
     }
@@ -151,14 +144,16 @@ __device__ void scatter_runs(uint32_t n, uint32_t nb, const Item* ent, Bucket sb
   __syncthreads();
 }
 
-// Orders the LDS accesses of one wave (its lanes share stage slots).
+// Orders the LDS accesses of one wave (its lanes read what others of it wrote).
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// (Two workgroups of 1024 threads share a CU: 64 registers at most.)
+// Bound by the LDS compare-and-swaps of the divisions and three barriers per
+// tile.  Two workgroups of 1024 threads share a CU: with 66 registers only one
+// did, 446 us for 2e8 integers against 365 (1.6 GB written, 4.4 TB/s).
 template <int T, int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void k_sieve(SieveParams P) {
   constexpr uint32_t kHitCap = hit_cap<T>();
@@ -358,7 +353,9 @@ struct PartParams {
 // and the partial lines of its sub-buckets are completed in that XCD's L2
 // before they are written back.  The bucket's chunks are split into nbw
 // contiguous ranges, one per workgroup; the next chunk is loaded into
-// registers while the current one is scattered.
+// registers while the current one is scattered.  Bound by memory: 8 bytes read
+// and 8 written per entry, at 3.6 TB/s of the 4.4 a large copy takes on this
+// card (2^36: 36.4 -> 32 ms with 8-byte words read instead of 12-byte entries).
 template <int BLOCK, bool COMPACT>
 __global__ __launch_bounds__(BLOCK) void k_partition(PartParams P) {
   constexpr int EPT = kPartChunk / BLOCK;
@@ -431,7 +428,7 @@ __global__ __launch_bounds__(BLOCK) void k_partition(PartParams P) {
     };
     __syncthreads();
     if (n_cur)  // uniform over the workgroup
-      scatter_runs<BLOCK, kB2Max, kPartChunk, false>(
+      scatter_runs<BLOCK, kB2Max, kPartChunk>(
           n_cur, B2, ent, bucket_of, perm, cnt, gofs, wsum, gcur, cap2, &P.flags[kFlagL2Overflow],
           [=](uint32_t b, uint32_t kk, const Item& x) {
             if constexpr (COMPACT)
@@ -646,6 +643,8 @@ __device__ __forceinline__ bool may_be_equal(const JoinParams& P, uint64_t x, ui
 // DIRECT: of a short range the first level's buckets are the partitions, and
 // the workgroup gathers its bucket's words from the regions into LDS (2^20
 // integers: a partition launch of 15 us less).
+//
+// Bound by memory and LDS round trips: 58 GB of words at 3.2 TB/s at 2^36.
 template <int BLOCK, bool DIRECT>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DIRECT ? 4 : 8))) void k_join_c(JoinParams P) {
   constexpr int EPT = kJoinCap / BLOCK;

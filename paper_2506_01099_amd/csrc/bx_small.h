@@ -12,7 +12,9 @@
 // What bounds it is the look at every power up to b (8.4e4 at 2^40) by one
 // workgroup (PowerTables).  The join's table lies over the tile once the
 // fingerprints are in registers, which leaves room for two workgroups per CU:
-// 300 queries of up to 8192 integers in one round of them.
+// 300 queries of up to 8192 integers in one round of them.  Their
+// fingerprints take one kept integer per lane (300 queries 28 -> 19 us, one of
+// 4096 integers 12 -> 8).
 #pragma once
 #include "bx_kernels.h"
 

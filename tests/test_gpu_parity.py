@@ -654,6 +654,114 @@ def test_low_zone_parts(ctx, a, b):
     assert got == [(want, n, n)] * 4
 
 
+@pytest.mark.parametrize("a,length,keep", [
+    (1 << 40, 8193, 12), (1 << 40, 1 << 16, 12), ((1 << 40) + 5, (1 << 20) + 1, 13), (1, 1 << 21, 13),
+    ((1 << 30) - 3, 3 << 21, 15)])
+def test_direct_join(ctx, a, length, keep):
+    """First-level buckets joined as they are (short ranges), counted exactly: the words
+    whose kept bits meet are the pairs of equal keys of the model, in lists that fit and
+    (a few bits kept) that do not, and the pairs are those of two partition levels."""
+    b = a + length
+    say(f"direct join [{a}, {b}), {keep} bits")
+    want = oracle.search_range(a, b)
+    ctx.set_option("compact_fp_bits", keep)
+    try:
+        assert ctx.search_range(a, b) == want
+        st = ctx.stats()
+        ctx.set_option("b1_bits", st["b1_bits"])
+        ctx.set_option("b2_bits", 2)
+        assert ctx.search_range(a, b) == want
+        two = ctx.stats()
+        ctx.set_option("compact", 0)
+        assert ctx.search_range(a, b) == want
+        whole = ctx.stats()
+    finally:
+        ctx.set_option("compact_fp_bits", 0)
+        ctx.set_option("compact", 1)
+        ctx.set_option("b1_bits", 0)
+        ctx.set_option("b2_bits", 0)
+    assert st["launches"]["partition"] == 0 and st["b2_bits"] == 0 and st["retries"] == 0
+    assert two["launches"]["partition"] > 0 and two["l2_entry_bytes"] == 8 and whole["l2_entry_bytes"] == 12
+    keys, n = join_model.compact_keys(oracle.radicals(a, b + 1), a, b, 0, st["b1_bits"], 0, keep)
+    for s in (st, two, whole):
+        assert s["entries"] == s["joined"] == n
+    assert st["word_matches"] == join_model.candidates(keys)
+    assert st["false_candidates"] == 0
+
+
+@pytest.mark.parametrize("entries", [4096 * 1024])
+def test_direct_join_boundary(ctx, entries):
+    """Ranges just below and above the expected entries up to which buckets are joined as
+    they are: Theorem 1's pairs on both sides of the line."""
+    below, above = int((entries - 40000) / 0.1085), int((entries + 40000) / 0.1075)
+    for N, direct in ((below, True), (above, False)):
+        say(f"direct boundary N={N}")
+        assert ctx.search(N) == theorem1_pairs(N)
+        st = ctx.stats()
+        assert (st["launches"]["partition"] == 0) == direct
+        assert st["entries"] == st["joined"] == member_count(N) and st["retries"] == 0
+
+
+@pytest.mark.parametrize("p", [8191, 8209, 65537, 1048583, 2097143])
+def test_large_squares(ctx, p):
+    """Multiples of the squares of large primes at the edges of a range: the sieves look
+    for them in single precision first, and none may be missed or invented."""
+    top = (1 << 42) - 1
+    for k in sorted({1, 2, (top - 9000) // (p * p)}):
+        x = k * p * p
+        for lo, hi in ((x - 8200, x + 500), (x, x + 3), (x - 1, x + 1), (x - 300, x), (x - 300, x + 1), (x + 1, x + 300)):
+            if lo < 1 or hi + 1 >= top:
+                continue
+            say(f"p={p} x={x} [{lo}, {hi})")
+            want = oracle.radicals(lo, hi + 1)
+            assert (np.asarray(ctx.radical_segment(lo, hi + 1)) == want).all()
+            n = join_model.group_keys(want, lo, hi, 0, 0, 1, 12)[1]
+            for small in (8192, 0):  # one workgroup's class, the segmented sieve
+                ctx.set_option("small_max", small)
+                try:
+                    assert ctx.search_range(lo, hi) == oracle.search_range(lo, hi)
+                    entries = ctx.stats()["entries"]
+                finally:
+                    ctx.set_option("small_max", 8192)
+                assert entries == n or hi - lo < 2
+
+
+@pytest.mark.parametrize("length", [2, 3, 64, 4095, 4096, 4097, 8191, 8192])
+def test_small_class_parts(ctx, length):
+    """The one-workgroup class at the edges of its lanes and of its join's two parts,
+    every integer joined: the candidates counted exactly."""
+    for a in (1, (1 << 33) + 7):
+        b = a + length
+        ctx.set_option("fp_bits", 12)
+        ctx.set_option("prune", 0)
+        try:
+            got, st = ctx.search_range(a, b), ctx.stats()
+        finally:
+            ctx.set_option("fp_bits", 0)
+            ctx.set_option("prune", 1)
+        assert got == oracle.search_range(a, b)
+        keys, n = join_model.group_keys(oracle.radicals(a, b + 1), a, b, 0, 0, 1, 12, prune=False)
+        assert st["launches"]["small"] == 1 and st["entries"] == st["joined"] == n == length
+        assert st["candidates"] == join_model.candidates(keys)
+
+
+def test_fresh_context_first_call_batch():
+    """The first call of a context may be a captured batch, and later calls of every
+    kind may follow; more pairs than one report holds come back whole."""
+    from paper_2506_01099_amd import Benelux
+
+    c = Benelux(device=0)
+    try:
+        a, b = np.full(100, 1, dtype=np.uint64), np.full(100, 3 * 10**5, dtype=np.uint64)
+        want = theorem1_pairs(3 * 10**5 - 1)
+        for _ in range(3):
+            assert [list(q) for q in c.search_batch(a, b)] == [want] * 100
+            assert c.stats()["pairs"] == 100 * len(want) > 256
+            assert c.search(4096) == theorem1_pairs(4096)
+    finally:
+        c.close()
+
+
 @pytest.mark.parametrize("passes", [1, 2, 3, 5, 7, 16, 64])
 def test_pass_count_invariance(ctx, passes):
     ctx.set_option("passes", passes)
