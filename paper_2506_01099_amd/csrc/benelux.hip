@@ -457,11 +457,13 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
     // partition in 0.160 ms with 2^3 x 2^9 against 0.296 with 2 x 2^11.  With
     // fewer (1.1e5 entries: 18 against 36 us) the regions are too short.
     if (n_pass >= 8.0 * 2048.0 * W) b1 = std::max(b1, 3u);
-    // A short range needs no second level: up to 2^10 buckets of 512 entries
-    // on average, or up to 4096, are joined as they are.  (1.1e5 entries: 21 us
-    // for partition and join become one launch of 8; beyond 4e6 the regions of
-    // a bucket have too few words each to gather.)
-    p.direct = words_ok(c) && c->force_b1 < 0 && c->force_b2 < 0 && c->force_group == 0 && n_pass <= 4096.0 * 1024.0;
+    // A short range needs no second level: up to 2^8 buckets of 512 entries or
+    // more, then up to 2^10 of at most 4096, are joined as they are.  (1.1e5
+    // entries: 21 us for partition and join become one launch of 8; beyond 4e6
+    // the regions of a bucket have too few words each to gather.)  A forced
+    // group or a tuning file's says how many buckets a partition launch takes,
+    // and holds where there is one.
+    p.direct = words_ok(c) && c->force_b1 < 0 && c->force_b2 < 0 && n_pass <= 4096.0 * 1024.0;
     if (p.direct) b1 = n_pass <= 4096.0 * 256.0 ? std::min<uint32_t>(8, ceil_log2(n_pass / 512.0)) : ceil_log2(n_pass / 4096.0);
     if (c->force_b1 >= 0) b1 = static_cast<uint32_t>(c->force_b1);
     p.b1bits = b1;
