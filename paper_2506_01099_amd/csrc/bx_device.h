@@ -249,9 +249,10 @@ __device__ __forceinline__ void sparse_hits(const PowerTables& T, uint32_t first
 }
 
 // Divide the LDS cell by p (p divides it).  Different prime powers can hit the
-// same cell at once, so the update is a 64-bit compare-and-swap loop.
-__device__ __forceinline__ void lds_div(uint64_t* cell, uint32_t p, uint32_t pinv) {
-  unsigned long long v = __atomic_load_n(reinterpret_cast<unsigned long long*>(cell), __ATOMIC_RELAXED);
+// same cell at once, so the update is a 64-bit compare-and-swap loop, from a
+// value of the cell seen before.
+__device__ __forceinline__ void lds_div(uint64_t* cell, uint64_t seen, uint32_t p, uint32_t pinv) {
+  unsigned long long v = seen;
   for (;;) {
     const unsigned long long nv = div_exact(v, p, pinv);
     const unsigned long long old = atomicCAS(reinterpret_cast<unsigned long long*>(cell), v, nv);
@@ -259,6 +260,8 @@ __device__ __forceinline__ void lds_div(uint64_t* cell, uint32_t p, uint32_t pin
     v = old;
   }
 }
+__device__ __forceinline__ uint64_t lds_read(const uint64_t* cell) { return __atomic_load_n(cell, __ATOMIC_RELAXED); }
+__device__ __forceinline__ void lds_div(uint64_t* cell, uint32_t p, uint32_t pinv) { lds_div(cell, lds_read(cell), p, pinv); }
 
 // rad(x) restricted to the prime 2: keep one factor 2 (shift by ctz(x) - 1
 // when 4 | x), the count-trailing-zeros step of Section 3.1.

@@ -47,12 +47,12 @@ struct SieveParams {
   uint32_t spill_cap;
   uint32_t* flags;
   uint64_t* rad_out;
-  uint64_t rad_lo, rad_hi;
+  uint64_t rad_lo;  // the first radical's integer
 };
 
 template <int T, int BLOCK>
 struct SieveSh {
-  uint64_t tile[T + 1];
+  uint64_t tile[T];
   uint64_t hits[hit_cap<T>()];
   uint32_t dres[kDenseMax], doff[kDenseMax], dq[kDenseMax], dtq[kDenseMax];
   uint32_t hit_n;
@@ -151,10 +151,14 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Bound by the LDS compare-and-swaps of the divisions and three barriers per
-// tile.  Two workgroups of 1024 threads share a CU: with 66 registers only one
-// did, 446 us for 2e8 integers against 365 (1.6 GB written, 4.4 TB/s).
-template <int T, int BLOCK>
+// Bound by its writes: 2e8 radicals (1.6 GB) take 0.18 ms without them, and a
+// fill alone 0.24.  Two workgroups of 1024 threads share a CU (64 registers; with
+// 66 only one did, 0.45 ms), one writing while the other divides; a thread
+// reads its cells together, and goes on to the next tile without a barrier after
+// its writes, which of a large output go past the caches (PAST): 0.372 -> 0.346 ms.
+// (Segments twice as long, for half the looks at the large powers, measured
+// 0.354; 16-byte writes the same as 8-byte ones.)
+template <int T, int BLOCK, bool PAST>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void k_sieve(SieveParams P) {
   constexpr uint32_t kHitCap = hit_cap<T>();
   static_assert(T % BLOCK == 0 && T <= 65536, "tile shape");
@@ -236,11 +240,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
         // Uniform: no x of the tile (x0 .. x0 + T) has a zero low word.
 #pragma unroll
         for (int it = 0; it < ITER; ++it) sh.tile[it * BLOCK + tid] = strip_two_lo(x0 + it * BLOCK + tid);
-        if (tid == 0) sh.tile[T] = strip_two_lo(x0 + T);
       } else {
 #pragma unroll
         for (int it = 0; it < ITER; ++it) sh.tile[it * BLOCK + tid] = strip_two(x0 + it * BLOCK + tid);
-        if (tid == 0) sh.tile[T] = strip_two(x0 + T);
       }
       // dres[d] = x0 mod q_d, advanced by T mod q_d from tile to tile.
       if (static_cast<uint32_t>(tid) < nd) {
@@ -255,18 +257,25 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
       }
       __syncthreads();
       // Dense odd prime powers: divide r by p at every multiple of q = p^k.
+      // (All of a thread's offsets, then all of its cells, are read together.)
+      uint32_t pos[SLOTS];
+      uint64_t v[SLOTS];
+#pragma unroll
+      for (int k = 0; k < SLOTS; ++k) pos[k] = sh.doff[sdj[k] & 63u];
 #pragma unroll
       for (int k = 0; k < SLOTS; ++k) {
-        if (sq[k] == 0) continue;
-        const uint32_t pos = sh.doff[sdj[k] & 63u] + ((sdj[k] >> 6) & 1023u) * sq[k];
-        if (pos <= cnt) lds_div(&sh.tile[pos], sdj[k] >> 16, spinv[k]);
+        pos[k] = sq[k] ? pos[k] + ((sdj[k] >> 6) & 1023u) * sq[k] : cnt;
+        v[k] = lds_read(&sh.tile[pos[k] < cnt ? pos[k] : 0u]);
       }
+#pragma unroll
+      for (int k = 0; k < SLOTS; ++k)
+        if (pos[k] < cnt) lds_div(&sh.tile[pos[k]], v[k], sdj[k] >> 16, spinv[k]);
       // Sparse hits of this tile: the LDS list, then the rare spill.
       const uint32_t nh_lds = min(nh, kHitCap);
       for (uint32_t h = tid; h < nh_lds; h += BLOCK) {
         const uint64_t e = sh.hits[h];
         const uint32_t pos = static_cast<uint32_t>(e >> 32);
-        if (pos >= base && pos <= base + cnt) {
+        if (pos - base < cnt) {
           const uint32_t p = static_cast<uint32_t>(e);
           lds_div(&sh.tile[pos - base], p, inv32(p));
         }
@@ -274,18 +283,29 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
       for (uint32_t h = kHitCap + tid; h < nh; h += BLOCK) {
         const uint64_t e = spill[h - kHitCap];
         const uint32_t pos = static_cast<uint32_t>(e >> 32);
-        if (pos >= base && pos <= base + cnt) {
+        if (pos - base < cnt) {
           const uint32_t p = static_cast<uint32_t>(e);
           lds_div(&sh.tile[pos - base], p, inv32(p));
         }
       }
       __syncthreads();
 
-      for (uint32_t i = tid; i < cnt; i += BLOCK) {
-        const uint64_t x = x0 + i;
-        if (x >= P.rad_lo && x < P.rad_hi) P.rad_out[x - P.rad_lo] = sh.tile[i];
+      // (No barrier after this: a thread writes the same cells again next.)
+      uint64_t* out = P.rad_out + (x0 - P.rad_lo) + tid;
+      if (cnt == T) {
+        uint64_t w[ITER];
+#pragma unroll
+        for (int it = 0; it < ITER; ++it) w[it] = sh.tile[it * BLOCK + tid];
+        if constexpr (PAST) {
+#pragma unroll
+          for (int it = 0; it < ITER; ++it) __builtin_nontemporal_store(w[it], &out[it * BLOCK]);
+        } else {
+#pragma unroll
+          for (int it = 0; it < ITER; ++it) out[it * BLOCK] = w[it];
+        }
+      } else {
+        for (uint32_t i = tid; i < cnt; i += BLOCK) out[i - tid] = sh.tile[i];
       }
-      __syncthreads();
     }
   }
 }

@@ -726,6 +726,31 @@ def test_large_squares(ctx, p):
                 assert entries == n or hi - lo < 2
 
 
+@pytest.mark.parametrize("tile", [2048, 8192])
+@pytest.mark.parametrize("length", [(1 << 25) - 1, 1 << 25, (1 << 25) + 8191])
+def test_large_radical_outputs(ctx, length, tile):
+    """Outputs that are written past the caches, and the largest that is not, equal those
+    of short calls, and the oracle's at both ends."""
+    import torch
+
+    lo = (1 << 40) + 12345
+    say(f"radicals of {length} integers, tile {tile}")
+    whole = torch.empty(length, dtype=torch.int64, device="cuda")
+    part = torch.zeros_like(whole)
+    ctx.set_option("tile", tile)
+    try:
+        ctx.radical_segment_dev(lo, lo + length, whole)
+        for at in range(0, length, 1 << 23):
+            end = min(at + (1 << 23), length)
+            ctx.radical_segment_dev(lo + at, lo + end, part[at:end])
+        torch.cuda.synchronize()
+    finally:
+        ctx.set_option("tile", 0)
+    assert torch.equal(whole, part)
+    for a, b in ((0, 3000), (length - 3000, length)):
+        assert (whole[a:b].cpu().numpy().astype(np.uint64) == oracle.radicals(lo + a, lo + b)).all()
+
+
 @pytest.mark.parametrize("length", [2, 3, 64, 4095, 4096, 4097, 8191, 8192])
 def test_small_class_parts(ctx, length):
     """The one-workgroup class at the edges of its lanes and of its join's two parts,
