@@ -862,6 +862,13 @@ struct Job {
   uint64_t cand_fp_mask = 0;  // fingerprint bits the candidates' entries hold
 };
 
+// Whether the job's second-level entries (12 bytes) hold fewer bits of whole
+// fingerprints than there are: equal ones of different sets are then expected.
+// (With a test's mask every pair of equal masked fingerprints is a candidate.)
+bool cut_fingerprints(const bx_ctx* c, const Job& j) {
+  return !j.compact && j.s && j.s->n_segs && c->fp_mask == (1ull << kFpBits) - 1 && j.cand_fp_mask != c->fp_mask;
+}
+
 // Bytes of every workspace buffer a job needs.
 struct JobBufs {
   size_t l1, l2, cnt1, cnt2, cand, out, counters, spill, queries, segpref, smallq;
@@ -1058,6 +1065,7 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
     J.primes = c->d_primes;
     J.pinv = c->d_pinv;
     J.n_primes = static_cast<uint32_t>(c->primes.size());
+    J.screen = cut_fingerprints(c, j);
     {
       c->stats.launches[K_JOIN]++;
       if (plan.direct)
@@ -1139,7 +1147,7 @@ int enqueue_verify(bx_ctx* c, const Job& j, uint32_t grid, hipStream_t st) {
   V.kinds = j.kinds;
   V.third_off = c->third_off;
   V.fp_mask = j.cand_fp_mask;
-  V.compact = j.compact;
+  V.compact = j.compact || cut_fingerprints(c, j);
   V.out = static_cast<OutPair*>(c->out.p);
   V.out_cap = kCandCap;
   V.flags = flags_of(c);

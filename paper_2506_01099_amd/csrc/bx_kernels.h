@@ -485,6 +485,7 @@ struct JoinParams {
   const uint32_t* primes;  // 2, 3, 5, ...
   const PrimeInv* pinv;
   uint32_t n_primes;
+  bool screen;  // k_join, k_join_sort: look at equal entries' integers first
 };
 
 __device__ __forceinline__ void emit_cand(const JoinParams& P, const Entry& a, const Entry& b) {
@@ -495,6 +496,26 @@ __device__ __forceinline__ void emit_cand(const JoinParams& P, const Entry& a, c
     c.b = b;
     P.cand[k] = c;
   }
+}
+
+// A candidate of k_join or k_join_sort.  The first level's words hold 35 of the
+// fingerprint's 53 bits at 2^36, of which 1.5e6 pairs of different sets share
+// all (the candidate buffer takes 2^20): with `screen` the divisibility of both
+// integers by the primes 3 .. 313 has to agree as a pair's does (may_be_equal).
+__device__ __forceinline__ void emit_equal(const JoinParams& P, const Entry& a, const Entry& b) {
+  if (P.screen) {
+    const uint64_t off = P.src.batch ? P.src.queries[entry_grp(a, P.gmask)].a : 0ull;
+    const uint64_t x = entry_pos(a, P.src.batch) + off, y = entry_pos(b, P.src.batch) + off;
+    const bool cross = (x ^ y) & 1;
+    const uint32_t n = min(P.n_primes, 65u);
+    for (uint32_t i = 1; i < n; ++i) {
+      const PrimeInv v = P.pinv[i];
+      const bool a0 = x * v.inv <= v.lim, a1 = (x + 1) * v.inv <= v.lim;
+      const bool b0 = y * v.inv <= v.lim, b1 = (y + 1) * v.inv <= v.lim;
+      if (cross ? a0 != b1 || a1 != b0 : a0 != b0 || a1 != b1) return;
+    }
+  }
+  emit_cand(P, a, b);
 }
 
 // LDS hash join of one second-level partition.  Each insert walks its probe
@@ -573,7 +594,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
         for (;;) {
           if (((v ^ mine) & ~kIdxMask) == 0) {
             const Entry f = src[i0 + (v & kIdxMask)];
-            if (entry_fp(f) == fk && entry_grp(f, P.gmask) == gk) emit_cand(P, e[k], f);
+            if (entry_fp(f) == fk && entry_grp(f, P.gmask) == gk) emit_equal(P, e[k], f);
           }
           s = (s + 1) & smask;
           v = atomicCAS(&table[s], kEmpty, mine);
@@ -593,7 +614,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
         if (v == kEmpty) break;
         if (((v ^ h) & ~kIdxMask) == 0) {
           const Entry f = src[i0 + (v & kIdxMask)];
-          if (entry_fp(f) == fk && entry_grp(f, P.gmask) == gk) emit_cand(P, g, f);
+          if (entry_fp(f) == fk && entry_grp(f, P.gmask) == gk) emit_equal(P, g, f);
         }
         s = (s + 1) & smask;
       }
@@ -874,7 +895,7 @@ __global__ __launch_bounds__(BLOCK) void k_join_sort(JoinParams P) {
         const Entry ea = src[i0 + static_cast<uint32_t>(key[a] & ((1u << kIdx) - 1))];
         for (uint32_t b = a + 1; b < end; ++b) {
           const Entry eb = src[i0 + static_cast<uint32_t>(key[b] & ((1u << kIdx) - 1))];
-          if (same(ea, eb)) emit_cand(P, ea, eb);
+          if (same(ea, eb)) emit_equal(P, ea, eb);
         }
       }
     }
@@ -892,7 +913,7 @@ __global__ __launch_bounds__(BLOCK) void k_join_sort(JoinParams P) {
       }
       for (uint32_t a = lo; a < m && (key[a] >> kIdx) == h; ++a) {
         const Entry f = src[i0 + static_cast<uint32_t>(key[a] & ((1u << kIdx) - 1))];
-        if (same(g, f)) emit_cand(P, g, f);
+        if (same(g, f)) emit_equal(P, g, f);
       }
     }
     __syncthreads();

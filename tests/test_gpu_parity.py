@@ -751,6 +751,26 @@ def test_large_radical_outputs(ctx, length, tile):
         assert (whole[a:b].cpu().numpy().astype(np.uint64) == oracle.radicals(lo + a, lo + b)).all()
 
 
+@pytest.mark.parametrize("log2n", [32, 36])
+@pytest.mark.parametrize("option", [("compact", 0, 1), ("join", 1, 0)])
+def test_large_searches_on_entries(ctx, log2n, option):
+    """Large searches whose second level holds 12-byte entries: the first level's words cut
+    the fingerprints, the many equal ones of different sets (6e3 at 2^32, 1.5e6 at 2^36,
+    past what the candidate buffer holds) are told apart in the join.  Whole fingerprints
+    (53 bits, and the bucket's) are shared by different sets 6 times at most on average."""
+    name, value, default = option
+    ctx.set_option(name, value)
+    say(f"2^{log2n} with {name} = {value}")
+    try:
+        got = ctx.search(1 << log2n)
+        st = ctx.stats()
+    finally:
+        ctx.set_option(name, default)
+    assert got == theorem1_pairs(1 << log2n)
+    assert st["l2_entry_bytes"] == 12 and st["retries"] == 0
+    assert st["candidates"] == st["pairs"] + st["false_candidates"] and st["false_candidates"] <= 12
+
+
 @pytest.mark.parametrize("length", [2, 3, 64, 4095, 4096, 4097, 8191, 8192])
 def test_small_class_parts(ctx, length):
     """The one-workgroup class at the edges of its lanes and of its join's two parts,
