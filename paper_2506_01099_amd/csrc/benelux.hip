@@ -541,6 +541,11 @@ struct Segs {
   uint64_t n_ints = 0;  // integers sieved
   uint64_t n_keys = 0;    // bound on the entries they produce (all of them without the member test)
   uint64_t n_expect = 0;  // expected entries
+  bool captured = false;  // the launches go into a graph, which later calls replay
+  // Whether k_begin copies the tables from the staging buffer, or takes them as
+  // arguments.  A graph would keep arguments, and answer a later call of the
+  // same shape with this one's queries.
+  bool staged() const { return captured || q.size() > kFewQueries; }
 };
 
 // Bounds on the entries the member test (may_pair) keeps in a query [a, b):
@@ -736,14 +741,14 @@ void make_segs(const bx_ctx* c, Segs* s, bool small_class, bool one_range) {
 
 // Device room for the query tables; a batch's tables are staged in pinned host
 // memory, from where k_begin copies them (one launch instead of three copies;
-// a single query travels in its arguments).  No kernel that reads the staging
-// buffer is in flight here: calls with more than one query drain their stream.
+// outside a graph one or two queries travel in its arguments).  No kernel that
+// reads the staging buffer is in flight here: the calls that stage drain their stream.
 int stage_segs(bx_ctx* c, const Segs& s) {
   int rc;
   if ((rc = ensure(c, c->queries, s.q.size() * sizeof(Query))) != BX_OK) return rc;
   if ((rc = ensure(c, c->segpref, s.prefix.size() * sizeof(uint64_t))) != BX_OK) return rc;
   if ((rc = ensure(c, c->smallq, s.small.size() * sizeof(uint32_t))) != BX_OK) return rc;
-  if (s.q.size() <= 2) return BX_OK;
+  if (!s.staged()) return BX_OK;
   const size_t nq = s.q.size() * sizeof(Query), np = s.prefix.size() * sizeof(uint64_t),
                ns = s.small.size() * sizeof(uint32_t), need = nq + np + ns;
   if (need > c->pin_bytes) {
@@ -777,7 +782,7 @@ int enqueue_begin(bx_ctx* c, const Segs& s, uint64_t n_cnt2, hipStream_t st, boo
   P.small = static_cast<uint32_t*>(c->smallq.p);
   P.n_queries = static_cast<uint32_t>(s.q.size());
   P.n_small = static_cast<uint32_t>(s.small.size());
-  if (s.q.size() <= 2) {
+  if (!s.staged()) {
     std::copy(s.q.begin(), s.q.end(), P.few);
     std::copy(s.prefix.begin(), s.prefix.end(), P.few_prefix);
     std::copy(s.small.begin(), s.small.end(), P.few_small);
@@ -1261,7 +1266,8 @@ int run_passes_graph(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* re
   *redo = 0;
   char key[1024];
   // Every launch shape, every option baked into a kernel argument or choice,
-  // and every buffer address the graph's kernels use.
+  // and every buffer address the graph's kernels use.  What a call's queries
+  // are is read from the staging buffer by each replay (Segs::staged).
   std::snprintf(key, sizeof(key),
                 "%u %llu %u %u %u %u %d %llu %u %d %u %u %d %u %d %d %llx %u %d %zu %d %u %llx %p %p %p %p %p %p %p %p %p %p %p %p %p %p",
                 j.plan.passes, static_cast<unsigned long long>(j.plan.cap1), j.plan.cap2, j.plan.b1bits, j.plan.b2bits,
@@ -1329,6 +1335,7 @@ int run_search(bx_ctx* c, Segs& s, int batch, uint32_t kinds, std::vector<OutPai
   result->clear();
   int rc = order_after_last(c, st);
   if (rc != BX_OK) return rc;
+  s.captured = use_graph;
   make_segs(c, &s, true, !batch);  // (the call drains st: no later call has to wait for it)
   if (s.n_segs == 0 && s.small.empty()) return BX_OK;
   Job j;

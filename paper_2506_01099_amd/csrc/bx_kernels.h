@@ -1099,7 +1099,8 @@ __global__ __launch_bounds__(BLOCK) void k_verify(VerifyParams P) {
 }
 
 // Start of a call: counters and group cursors to zero, and the query tables,
-// from the arguments (one query) or from the host's staging buffer.
+// from the host's staging buffer or (at most kFewQueries) from the arguments.
+constexpr uint32_t kFewQueries = 2;
 struct BeginParams {
   Counters* n;
   uint32_t* cnt2;  // n_cnt2 cursors
@@ -1108,9 +1109,9 @@ struct BeginParams {
   uint64_t* seg_prefix;
   uint32_t* small;
   uint32_t n_queries, n_small;
-  Query few[2];     // n_queries <= 2
-  uint64_t few_prefix[3];
-  uint32_t few_small[2];
+  Query few[kFewQueries];  // without staged_queries
+  uint64_t few_prefix[kFewQueries + 1];
+  uint32_t few_small[kFewQueries];
   const uint64_t* staged_queries;  // host memory: the queries, n_queries + 1 words, n_small half words
   const uint64_t* staged_prefix;
   const uint32_t* staged_small;
@@ -1122,7 +1123,7 @@ __global__ __launch_bounds__(256) void k_begin(BeginParams P) {
   if (P.n && t < kKernels) P.n->ticks[t] = 0;
   if (P.n && t == 0) P.n->running = 0;
   for (uint32_t i = t; i < P.n_cnt2; i += step) P.cnt2[i] = 0;
-  if (P.n_queries <= 2) {
+  if (!P.staged_queries) {
     if (t < P.n_queries) P.queries[t] = P.few[t];
     if (t <= P.n_queries) P.seg_prefix[t] = P.few_prefix[t];
     if (t < P.n_small) P.small[t] = P.few_small[t];

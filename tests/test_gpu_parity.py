@@ -1315,3 +1315,19 @@ def test_autotune_and_load(ctx, tmp_path):
         ctx.set_option("tile", 0)
         ctx.set_option("seg_len", 0)
         ctx.set_option("group", 0)
+
+
+@pytest.mark.parametrize("length", [4700, 65537, 300001])
+@pytest.mark.parametrize("apart", [None, 0, 10**6])
+def test_batches_of_few_queries_one_after_another(ctx, length, apart):
+    """Batches of one query and of two, call after call with no option between and shapes
+    that stay the same (the captured graph is replayed): each call's pairs and kept
+    integers are those of its own ranges."""
+    for a in (1, 3, 36, 10**8, 71, 10**8 + 1, 1):
+        starts = [a] if apart is None else [a, a + apart]
+        say(f"queries of {length} at {starts}")
+        lo = np.array(starts, dtype=np.uint64)
+        got, st = ctx.search_batch(lo, lo + np.uint64(length)), ctx.stats()
+        assert got == [oracle.search_range(x, x + length) for x in starts]
+        n = sum(join_model.group_keys(oracle.radicals(x, x + length + 1), x, x + length, 0, 0, 1, 12)[1] for x in starts)
+        assert st["entries"] == st["joined"] == n
