@@ -416,8 +416,6 @@ uint32_t ceil_log2(double v) {
   return b;
 }
 
-uint64_t round_up(uint64_t v, uint64_t m) { return (v + m - 1) / m * m; }
-
 // Sparse hits per workgroup beyond the radical sieve's LDS list (worst case).
 uint32_t spill_cap_of(const bx_ctx* c) {
   return static_cast<uint32_t>(c->pp.size() - c->n_dense[0] + c->seg_len / 128 + 64);
@@ -513,27 +511,13 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
   return fail(BX_ENOMEM, "HBM budget too small for the search");
 }
 
-// Segment length for n integers over `wgs` workgroups: as many equal rounds of
-// all workgroups as segments of at most `longest` need, in multiples of `unit`.
-// Segments of 2^18 left the chip idle on short ranges (2^20 integers at 2^40 on
-// 4 of 256 CUs: sieve 81 us) and ran a last round for a few of them; a short
-// segment repeats the hit list's look at every large power (about 9 us at 2^40),
-// so those of a range run side by side.
-uint32_t fit_seg_len(uint64_t n, uint64_t wgs, uint32_t longest, uint32_t unit) {
-  const uint64_t rounds = std::max<uint64_t>(1, (n + wgs * longest - 1) / (wgs * longest));
-  const uint64_t len = round_up(std::max<uint64_t>(1, (n + wgs * rounds - 1) / (wgs * rounds)), unit);
-  return static_cast<uint32_t>(std::min<uint64_t>(len, longest));
-}
-constexpr uint32_t kKeySegUnit = 4 * kSub;  // a wave per SIMD at work at least
-constexpr uint32_t kLowSegUnit = kSub / 4;  // where all integers may be kept
-
 // Radical-sieve segments of a range: two workgroups per CU and tile shape.
 uint32_t rad_seg_len(const bx_ctx* c, uint64_t n) {
   return fit_seg_len(n, 2ull * static_cast<uint64_t>(std::max(1, c->n_cu)), c->seg_len, kTileLarge);
 }
 
 struct Segs {
-  uint32_t seg_len = 0;
+  uint32_t seg_len = 0;      // the longest of any query or part
   std::vector<Query> q;      // the queries; of a search of one range, its parts (make_segs)
   std::vector<uint64_t> prefix;
   std::vector<uint32_t> small;  // queries served by the small-query class (no segments)
@@ -689,13 +673,6 @@ bool is_small(const bx_ctx* c, const Query& q) {
 // Segments of every query; with small_class, the queries of the small-query
 // class take none and are listed in s->small instead (searches only: the
 // radical sieve segments every range).
-//
-// The search of one range (one_range) that reaches below 32 sqrt(b) is sieved
-// in two parts, that low zone in shorter segments, so that it spreads over the
-// chip: there most integers are looked at or kept (one in nine above), and a
-// wave with 1024 kept integers takes ten times its time (3e6 integers: 70000
-// cycles beside 7000).  Sieve of 3e6 integers 41 -> 29 us, of 2^32 5.02 -> 4.91
-// ms.  A batch's segments are all alike: its queries fill the chip together.
 void make_segs(const bx_ctx* c, Segs* s, bool small_class, bool one_range) {
   const uint64_t cus = static_cast<uint64_t>(std::max(1, c->n_cu));
   uint64_t n = 0;
@@ -703,18 +680,11 @@ void make_segs(const bx_ctx* c, Segs* s, bool small_class, bool one_range) {
     q.top = q.b;
     if (q.b > q.a && !(small_class && is_small(c, q))) n += q.b - q.a;
   }
-  s->seg_len = small_class ? fit_seg_len(n, cus, c->seg_len, kKeySegUnit) : rad_seg_len(c, n);
-  for (Query& q : s->q) q.seg_len = s->seg_len;
-  if (one_range && c->prune && n > 0) {
-    Query low = s->q[0];
-    const uint64_t zl = static_cast<uint64_t>(32.0 * sqrt_b(low)) + 1;
-    if (low.a < zl && zl < low.b) {
-      low.b = zl;
-      low.seg_len = std::min(s->seg_len, fit_seg_len(zl - low.a, cus, c->seg_len, kLowSegUnit));
-      s->q[0].a = zl;
-      s->q[0].seg_len = fit_seg_len(s->q[0].b - zl, cus, c->seg_len, kKeySegUnit);
-      s->q.insert(s->q.begin(), low);
-    }
+  if (small_class) {
+    s->seg_len = cut_search(&s->q, n, cus, c->seg_len, one_range && c->prune && n > 0);
+  } else {
+    s->seg_len = rad_seg_len(c, n);
+    for (Query& q : s->q) q.seg_len = s->seg_len;
   }
   s->prefix.assign(s->q.size() + 1, 0);
   s->small.clear();
@@ -883,6 +853,8 @@ struct JobBufs {
 // needs; nothing is allocated.
 int plan_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, Job* j, JobBufs* nb) {
   int rc;
+  for (const Query& q : s.q)
+    if (q.seg_len > s.seg_len) return fail(BX_EINTERNAL, "segment longer than the index step");
   j->s = &s;
   j->batch = batch;
   j->kinds = kinds;
@@ -905,15 +877,8 @@ int plan_job(bx_ctx* c, Segs& s, int batch, uint32_t kinds, Job* j, JobBufs* nb)
   j->gmask = batch ? kGrpMask : 0u;
   nb->l1 = j->n_regions * plan.cap1 * sizeof(uint64_t);
   {
-    auto bits_of = [](uint64_t v) {  // the least b with v < 2^b
-      uint32_t b = 0;
-      while (b < 64 && (v >> b)) ++b;
-      return b;
-    };
-    // Indices run up to segments per workgroup * seg_len - 1; the bit length
-    // of that product keeps the all-ones index free.
     const uint64_t W = std::max<uint64_t>(1, j->sieve_grid);
-    j->li_bits = std::max(1u, bits_of((s.n_segs + W - 1) / W * s.seg_len));
+    j->li_bits = index_bits(s.n_segs, W, s.seg_len);
     const uint32_t kl = std::min<uint32_t>(42, 53 - j->li_bits);  // li_bits <= 43: x < 2^42
     j->kl_mask = (1ull << kl) - 1;
     j->wl_bits = j->li_bits + bits_of(W - 1);

@@ -15,6 +15,8 @@
 
 #include <cstdint>
 
+#include "bx_segments.h"
+
 namespace bx {
 
 constexpr uint32_t kGrpShift = 28;    // query id position inside pos (batched mode)
@@ -71,14 +73,6 @@ constexpr uint64_t kNoWord = ~0ull;
 __device__ __forceinline__ uint64_t l1_word(uint64_t h, uint64_t kl_mask, uint32_t li_bits, uint64_t li) {
   return (h & ~((1ull << 53) - 1)) | (((h >> 11) & kl_mask) << li_bits) | li;
 }
-
-// A range to sieve: a query, or one of the parts of a single query.
-struct Query {
-  uint64_t a, b;     // x in [a, b); radicals over [a, b]
-  uint64_t top;      // the query's end (the bound of the member test)
-  uint32_t seg_len;  // of its segments
-  uint32_t pad;
-};
 
 struct Cand {
   Entry a, b;

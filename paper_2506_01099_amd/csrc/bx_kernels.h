@@ -310,32 +310,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
   }
 }
 
-// Where the first level's words came from: enough to turn a word's index back
-// into its integer.
-struct WordSource {
-  const Query* queries;
-  const uint64_t* seg_prefix;
-  uint32_t n_queries;
-  uint32_t seg_len, W;  // the longest segment; sieve workgroups
-  uint32_t li_bits;
-  int batch;
-};
-
-// The integer with index li of sieve workgroup w, and its query (0 unless batched).
-__device__ __forceinline__ uint64_t word_integer(const WordSource& S, uint32_t w, uint64_t li, uint32_t* grp) {
-  const uint64_t s = w + (li / S.seg_len) * S.W;
-  uint32_t lo = 0, hi = S.n_queries;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (S.seg_prefix[mid] <= s)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  *grp = S.batch ? lo : 0u;
-  return S.queries[lo].a + (s - S.seg_prefix[lo]) * S.queries[lo].seg_len + li % S.seg_len;
-}
-
 // pos43 of an Entry (bx_device.h).
 __device__ __forceinline__ uint64_t word_pos43(const WordSource& S, uint32_t w, uint64_t li) {
   uint32_t grp;

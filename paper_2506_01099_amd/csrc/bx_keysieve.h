@@ -26,6 +26,7 @@ namespace bx {
 
 constexpr int kSub = 1024;               // integers of a subtile
 constexpr int kPerLane = kSub / 64;      // consecutive integers of a lane
+static_assert(kKeySegUnit == 4 * kSub && kLowSegUnit == kSub / 4, "segments in subtiles");
 constexpr int kKeyBlock = 1024;          // threads of a workgroup
 constexpr int kKeyWaves = kKeyBlock / 64;
 constexpr uint32_t kRow = kSub * kKeyWaves;  // integers of a row of subtiles

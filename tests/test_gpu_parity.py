@@ -1331,3 +1331,29 @@ def test_batches_of_few_queries_one_after_another(ctx, length, apart):
         assert got == [oracle.search_range(x, x + length) for x in starts]
         n = sum(join_model.group_keys(oracle.radicals(x, x + length + 1), x, x + length, 0, 0, 1, 12)[1] for x in starts)
         assert st["entries"] == st["joined"] == n
+
+
+@pytest.mark.parametrize("k,past", [(k, past) for k in (1, 2, 5, 33) for past in (-1, 1, 1000)])
+def test_search_past_a_round_of_segments(ctx, k, past):
+    """Searches of a few integers more than k segments a workgroup hold: the part above the
+    low zone then needs a round less, and takes longer segments, than the whole range."""
+    N = (k << 26) + past
+    say(f"N = {k} * 2^26 + {past}")
+    assert ctx.search(N) == theorem1_pairs(N)
+    st = ctx.stats()
+    assert st["candidates"] == st["pairs"] + st["false_candidates"] and st["retries"] == 0
+    if k == 1:
+        assert st["entries"] == member_count(N)
+
+
+@pytest.mark.parametrize("seg,N", [(1 << 15, (1 << 23) + 1), (1 << 15, (1 << 23) + 30000), (1 << 16, (3 << 24) + 1),
+                                   (1 << 17, (1 << 25) + 100001)])
+def test_ranges_past_a_round_of_segments(ctx, seg, N):
+    """The same with shorter segments, as a search and as ranges from inside the low zone."""
+    ctx.set_option("seg_len", seg)
+    try:
+        for a in (1, 36, 1000):
+            say(f"[{a}, {N + a}) in segments of {seg}")
+            assert ctx.search_range(a, N + a) == [p for p in theorem1_pairs(N + a - 1) if p[0] >= a]
+    finally:
+        ctx.set_option("seg_len", 0)
