@@ -472,22 +472,31 @@ __device__ __forceinline__ void emit_cand(const JoinParams& P, const Entry& a, c
   }
 }
 
+// Whether S_x = S_y can hold, from the primes 3 .. 313, by one lane.  A prime
+// that divides one of x, x + 1 has to divide the same one of y, y + 1 when x
+// and y have the same parity (a pair of the first kind), and the other one else
+// (the second kind; the prime 2 tells).  About one in 390 of different
+// sets passes.
+__device__ __forceinline__ bool small_primes_agree(const JoinParams& P, uint64_t x, uint64_t y) {
+  const bool cross = (x ^ y) & 1;
+  const uint32_t n = min(P.n_primes, 65u);
+  for (uint32_t i = 1; i < n; ++i) {
+    const PrimeInv v = P.pinv[i];
+    const bool a0 = x * v.inv <= v.lim, a1 = (x + 1) * v.inv <= v.lim;
+    const bool b0 = y * v.inv <= v.lim, b1 = (y + 1) * v.inv <= v.lim;
+    if (cross ? a0 != b1 || a1 != b0 : a0 != b0 || a1 != b1) return false;
+  }
+  return true;
+}
+
 // A candidate of k_join or k_join_sort.  The first level's words hold 35 of the
 // fingerprint's 53 bits at 2^36, of which 1.5e6 pairs of different sets share
 // all (the candidate buffer takes 2^20): with `screen` the divisibility of both
-// integers by the primes 3 .. 313 has to agree as a pair's does (may_be_equal).
+// integers by small primes has to agree as a pair's does.
 __device__ __forceinline__ void emit_equal(const JoinParams& P, const Entry& a, const Entry& b) {
   if (P.screen) {
     const uint64_t off = P.src.batch ? P.src.queries[entry_grp(a, P.gmask)].a : 0ull;
-    const uint64_t x = entry_pos(a, P.src.batch) + off, y = entry_pos(b, P.src.batch) + off;
-    const bool cross = (x ^ y) & 1;
-    const uint32_t n = min(P.n_primes, 65u);
-    for (uint32_t i = 1; i < n; ++i) {
-      const PrimeInv v = P.pinv[i];
-      const bool a0 = x * v.inv <= v.lim, a1 = (x + 1) * v.inv <= v.lim;
-      const bool b0 = y * v.inv <= v.lim, b1 = (y + 1) * v.inv <= v.lim;
-      if (cross ? a0 != b1 || a1 != b0 : a0 != b0 || a1 != b1) return;
-    }
+    if (!small_primes_agree(P, entry_pos(a, P.src.batch) + off, entry_pos(b, P.src.batch) + off)) return;
   }
   emit_cand(P, a, b);
 }
@@ -601,7 +610,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
 struct WordMatch {
   uint64_t a, b;
 };
-constexpr uint32_t kMatchMax = 128;  // listed per chunk of a partition, in LDS
+// Listed per chunk of a partition, in LDS.  Full partitions (7400 words) of one
+// range expect 2 meetings at 2^36 and, with the 19 fingerprint bits left beside
+// the index, 52 just below 2^42; fewer kept bits or larger partitions, which
+// only options ask for, pass the list (k_join_c).
+constexpr uint32_t kMatchMax = 128;
 
 // The integers of a match; false if they belong to different queries.
 struct MatchPair {
@@ -621,11 +634,8 @@ __device__ __forceinline__ void emit_match(const JoinParams& P, uint64_t a, uint
   emit_cand(P, make_entry((r.x - off) | grp, a >> P.wl_bits), make_entry((r.y - off) | grp, b >> P.wl_bits));
 }
 
-// One wave: whether S_x = S_y can hold, from the primes 3 .. 2^11 and some more, one per lane.
-// A prime that divides one of x, x + 1 has to divide the same one of y, y + 1
-// when x and y have the same parity (a pair of the first kind), and the other
-// one else (the second kind; the prime 2 tells).  Different sets seldom pass
-// the first 64 primes.
+// The same by one wave, from the primes 3 .. 2^11 and some more, one per lane.
+// Different sets seldom pass the first 64.
 __device__ __forceinline__ bool may_be_equal(const JoinParams& P, uint64_t x, uint64_t y) {
   const bool cross = (x ^ y) & 1;
   for (uint32_t i0 = 1; i0 < P.n_primes; i0 += 256) {
@@ -652,8 +662,9 @@ __device__ __forceinline__ bool may_be_equal(const JoinParams& P, uint64_t x, ui
 // from the words themselves, different queries and sets that a small prime
 // tells apart are dropped, and the rest are candidates.  (The look takes a lane
 // that found it 0.5 ms for an equal pair, a wave about a microsecond.)  A chunk
-// with more matches than the list holds walks its chains once more instead and
-// makes every match a candidate.
+// with more matches than the list holds walks its chains once more instead, and
+// the lane that finds a match looks at it, by fewer primes (small_primes_agree):
+// 3e6 matches are more than the candidate buffer holds.
 //
 // DIRECT: of a short range the first level's buckets are the partitions, and
 // the workgroup gathers its bucket's words from the regions into LDS (2^20
@@ -797,7 +808,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DIRECT ? 
           if (((v ^ h) & ~kIdxMask) != 0 || o >= i) continue;
           const uint64_t f = src[o];
           MatchPair r;
-          if ((f >> pb) == (g >> pb) && match_pair(P.src, pb, g, f, &r)) emit_match(P, g, f, r);
+          if ((f >> pb) == (g >> pb) && match_pair(P.src, pb, g, f, &r) && small_primes_agree(P, r.x, r.y)) emit_match(P, g, f, r);
         }
       }
     }

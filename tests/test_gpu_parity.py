@@ -1357,3 +1357,26 @@ def test_ranges_past_a_round_of_segments(ctx, seg, N):
             assert ctx.search_range(a, N + a) == [p for p in theorem1_pairs(N + a - 1) if p[0] >= a]
     finally:
         ctx.set_option("seg_len", 0)
+
+
+@pytest.mark.parametrize("b1,b2", [(0, 0), (3, 7)])
+def test_compact_more_meetings_than_candidates(ctx, b1, b2):
+    """More meetings of different sets' kept bits than the candidate buffer holds, in
+    chunks that list them and that cannot (first-level buckets and partitions): the
+    search still answers, and the meetings are counted exactly."""
+    N, keep = 1 << 25, 12
+    ctx.set_option("compact_fp_bits", keep)
+    ctx.set_option("b1_bits", b1)
+    ctx.set_option("b2_bits", b2)
+    try:
+        got = ctx.search(N)
+        st = ctx.stats()
+    finally:
+        ctx.set_option("compact_fp_bits", 0)
+        ctx.set_option("b1_bits", 0)
+        ctx.set_option("b2_bits", 0)
+    assert got == theorem1_pairs(N)
+    keys, n = join_model.compact_keys(oracle.radicals(1, N + 2), 1, N + 1, 0, st["b1_bits"], st["b2_bits"], keep)
+    assert st["entries"] == st["joined"] == n
+    assert st["word_matches"] == join_model.candidates(keys) > 1 << 20
+    assert st["candidates"] == st["pairs"] and st["false_candidates"] == 0
