@@ -837,11 +837,12 @@ struct Job {
   uint64_t cand_fp_mask = 0;  // fingerprint bits the candidates' entries hold
 };
 
-// Whether the job's second-level entries (12 bytes) hold fewer bits of whole
-// fingerprints than there are: equal ones of different sets are then expected.
-// (With a test's mask every pair of equal masked fingerprints is a candidate.)
+// Whether the job's second-level entries (12 bytes) hold fewer fingerprint bits
+// than the call keeps (all, or a test's mask): equal ones of different sets are
+// then expected.  (Where a test's mask is the smaller, every pair of equal
+// masked fingerprints is a candidate.)
 bool cut_fingerprints(const bx_ctx* c, const Job& j) {
-  return !j.compact && j.s && j.s->n_segs && c->fp_mask == (1ull << kFpBits) - 1 && j.cand_fp_mask != c->fp_mask;
+  return !j.compact && j.s && j.s->n_segs && (c->fp_mask & ~j.cand_fp_mask) != 0;
 }
 
 // Bytes of every workspace buffer a job needs.
@@ -1117,6 +1118,7 @@ int enqueue_verify(bx_ctx* c, const Job& j, uint32_t grid, hipStream_t st) {
   V.kinds = j.kinds;
   V.third_off = c->third_off;
   V.fp_mask = j.cand_fp_mask;
+  V.whole_mask = c->fp_mask;
   V.compact = j.compact || cut_fingerprints(c, j);
   V.out = static_cast<OutPair*>(c->out.p);
   V.out_cap = kCandCap;

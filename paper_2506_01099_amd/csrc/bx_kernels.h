@@ -475,7 +475,7 @@ __device__ __forceinline__ void emit_cand(const JoinParams& P, const Entry& a, c
 // Whether S_x = S_y can hold, from the primes 3 .. 313, by one lane.  A prime
 // that divides one of x, x + 1 has to divide the same one of y, y + 1 when x
 // and y have the same parity (a pair of the first kind), and the other one else
-// (the second kind; the prime 2 tells).  About one in 390 of different
+// (the second kind; the prime 2 tells).  About one in 390 pairs of different
 // sets passes.
 __device__ __forceinline__ bool small_primes_agree(const JoinParams& P, uint64_t x, uint64_t y) {
   const bool cross = (x ^ y) & 1;
@@ -917,7 +917,8 @@ struct VerifyParams {
   uint32_t kinds;
   uint32_t third_off;  // the third condition compares rad(m + third_off), rad(n + third_off) (2 in use)
   uint64_t fp_mask;  // fingerprint bits every candidate's entries hold
-  int compact;
+  uint64_t whole_mask;  // those the call keeps
+  int compact;       // entries hold fewer than that
   OutPair* out;
   uint32_t out_cap;
   uint32_t* flags;
@@ -1053,8 +1054,8 @@ __global__ __launch_bounds__(BLOCK) void k_verify(VerifyParams P) {
       const uint64_t fp_m = key64(lo_m, hi_m, P.batch ? qa_idx : 0u) >> 11;
       if (!same) {
         // Different sets (or queries).  A candidate made from compact words
-        // counts as one only if the whole fingerprints agree.
-        if (P.compact && fp_m != key64(lo_n, hi_n, P.batch ? qa_idx : 0u) >> 11)
+        // (or from cut fingerprints) counts as one only if the whole ones agree.
+        if (P.compact && ((fp_m ^ (key64(lo_n, hi_n, P.batch ? qa_idx : 0u) >> 11)) & P.whole_mask))
           atomicAdd(&P.flags[kFlagDropped], 1u);
         else
           atomicAdd(&P.flags[kFlagFalseCand], 1u);

@@ -1380,3 +1380,19 @@ def test_compact_more_meetings_than_candidates(ctx, b1, b2):
     assert st["entries"] == st["joined"] == n
     assert st["word_matches"] == join_model.candidates(keys) > 1 << 20
     assert st["candidates"] == st["pairs"] and st["false_candidates"] == 0
+
+
+@pytest.mark.parametrize("keep", [25, 40])
+def test_large_search_with_masked_fingerprints(ctx, keep):
+    """A test's mask that keeps more fingerprint bits than a first-level word holds at
+    2^36 (24 low ones, shared by 1.5e6 pairs of different sets): answered, not refused."""
+    ctx.set_option("fp_bits", keep)
+    say(f"2^36 with fp_bits = {keep}")
+    try:
+        got = ctx.search(1 << 36)
+        st = ctx.stats()
+    finally:
+        ctx.set_option("fp_bits", 0)
+    assert got == theorem1_pairs(1 << 36)
+    assert st["l2_entry_bytes"] == 12 and st["retries"] == 0
+    assert st["candidates"] == st["pairs"] + st["false_candidates"]
