@@ -960,10 +960,9 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
   P.spill = static_cast<uint64_t*>(c->spill.p);
   P.flags = d_flags;
   P.batch = j.batch;
-  P.prune = c->prune;
-  P.pfilter = !(ph_lo == 0 && ph_hi == (1ull << 32));
-  P.ph_lo = ph_lo;
-  P.ph_hi = ph_hi;
+  const bool all_keys = ph_lo == 0 && ph_hi == (1ull << 32);
+  P.ph_lo = static_cast<uint32_t>(ph_lo);
+  P.ph_len = static_cast<uint32_t>(ph_hi - ph_lo);  // (read for part of the keys only)
   P.W = j.sieve_grid;
   P.b1bits = plan.b1bits;
   P.li_bits = j.li_bits;
@@ -974,7 +973,19 @@ int enqueue_pass(bx_ctx* c, const Job& j, uint64_t ph_lo, uint64_t ph_hi, hipStr
   P.entries = acc_of(c) + kAccEntries;
   {
     c->stats.launches[K_SIEVE]++;
-    hipLaunchKernelGGL(k_sieve_keys, dim3(j.sieve_grid), dim3(kKeyBlock), 0, st, P);
+#define BX_KEYS_LAUNCH(FILTER, ALL) \
+  hipLaunchKernelGGL((k_sieve_keys<FILTER, ALL>), dim3(j.sieve_grid), dim3(kKeyBlock), 0, st, P)
+    if (c->prune) {
+      if (all_keys)
+        BX_KEYS_LAUNCH(false, false);
+      else
+        BX_KEYS_LAUNCH(true, false);
+    } else if (all_keys) {
+      BX_KEYS_LAUNCH(false, true);
+    } else {
+      BX_KEYS_LAUNCH(true, true);
+    }
+#undef BX_KEYS_LAUNCH
   }
   BX_HIP(hipGetLastError());
   WordSource src;

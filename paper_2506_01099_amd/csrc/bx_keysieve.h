@@ -73,9 +73,7 @@ struct KeyParams {
   uint64_t* spill;       // kKeySpill words per workgroup
   uint32_t* flags;
   int batch;
-  uint32_t prune;    // drop x that cannot be a member of any pair (may_pair)
-  uint32_t pfilter;  // keep x only when pass_hash(key) is in [ph_lo, ph_hi)
-  uint64_t ph_lo, ph_hi;
+  uint32_t ph_lo, ph_len;  // FILTER: keep x only when pass_hash(key) is in [ph_lo, ph_lo + ph_len)
   uint32_t b1bits;   // first-level bucket = low b1bits bits of key64
   uint32_t li_bits;  // words: L1Word
   uint64_t kl_mask;
@@ -251,6 +249,16 @@ __device__ __forceinline__ void put_words(KeySh& sh, const KeyParams& P, bool ke
 // took 70% longer (latency); a sorted stage with coalesced flushes instead of
 // the queues 40%.
 // 2^36 integers 158 -> 77.5 ms, 2^32 9.55 -> 4.9 ms, 2^28 at 2^40 0.71 -> 0.30.
+//
+// FILTER: one of several passes.  Every record's radicals are made, and those of
+// the pass wait in lanes until 64 are together, so that the key and the queues
+// are paid for the pass's own records alone.
+//
+// ALL: the member test is off and every integer is kept: no bits, and no list
+// (which took 1024 records in eight parts; 2^32 29.6 -> 20.2 ms, and with FILTER
+// 2^36 in five passes 2278 -> 1203 ms).  Else x that cannot be a member of any
+// pair (may_pair) are dropped.
+template <bool FILTER, bool ALL>
 __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
   __shared__ KeySh sh;
   note_time(P.flags, K_SIEVE);
@@ -436,21 +444,21 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
         const uint64_t x0 = start + static_cast<uint64_t>(sub) * kSub;
         const double x0d = S + static_cast<double>(sub * kSub);
         const uint32_t cntv = min(static_cast<uint32_t>(kSub), len - sub * kSub);
-        const bool lower = P.prune && (x0 <= 3 || x0 <= (qb >> 1));
+        const bool lower = !ALL && (x0 <= 3 || x0 <= (qb >> 1));
         // Below b / 2 a squarefree y of {x, x + 1} with y * M <= b is kept
         // too, M = max(2, rad(z) - 1) of its neighbour z: then e(z) >= ethr.
         // With ethr small every x with a non-squarefree neighbour is looked
         // at (68% of them); else those next to a z with 105 * 2^(a-1) * E(z) >=
         // ethr, marked in cbits (from ethr = 1024 on at most a quarter).
         float ethr = 0.f;
-        uint32_t look = 0;  // 0: the bits decide, 1: all, 2: one non-squarefree, 3: marked
-        if (!P.prune) look = 1;
+        uint32_t look = 0;  // 0: the bits decide, 1: any, 2: one non-squarefree, 3: marked
         if (lower) {
           const double bd = static_cast<double>(qb);
           ethr = static_cast<float>(0.99 * x0d / (bd / x0d + 1.0));
           look = x0d * x0d <= bd + 8 ? 1 : ethr < 1024.f ? 2 : 3;
         }
         auto mark = [&](uint32_t pos, uint32_t e) {
+          if constexpr (ALL) return;
           atomicOr(&bits[pos >> 5], 1u << (pos & 31u));
           if (look == 3) {
             const uint64_t z = x0 + pos;
@@ -538,12 +546,17 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
         }
         const uint32_t pc = __popc(K);
         const uint32_t inc = wave_inclusive_scan(pc);
-        const uint32_t total = __builtin_amdgcn_readlane(inc, 63);
+        const uint32_t total = ALL ? cntv : __builtin_amdgcn_readlane(inc, 63);
         const uint64_t li = li0 + (x0 - seg0);
         const uint32_t x0odd = static_cast<uint32_t>(x0) & 1u;
         const bool wraps = static_cast<uint32_t>(x0) - 1u > 0xFFFFFFFFu - kSub - 1u;  // a multiple of 2^32 near the subtile
+        auto put = [&](uint64_t klo, uint64_t khi, uint32_t i, bool keep) {
+          const uint64_t h = key64(klo, khi, grp);
+          put_words(sh, P, keep, static_cast<uint32_t>(h) & ((1u << P.b1bits) - 1u), l1_word(h, P.kl_mask, P.li_bits, li + i));
+        };
+        uint32_t held = 0, h0 = 0, h1 = 0, h2 = 0;  // FILTER: records waiting, one in each of the first lanes
         for (uint32_t rb = 0; rb < total; rb += kRecMax) {
-          {
+          if constexpr (!ALL) {
             uint32_t kt = K, slot = inc - pc - rb;
             if (total <= kRecMax) {
               while (kt) {
@@ -554,12 +567,12 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
               for (; kt; ++slot, kt &= kt - 1)
                 if (slot < kRecMax) rec[slot] = static_cast<uint16_t>(kPerLane * lane + __builtin_ctz(kt));
             }
+            wave_sync();
           }
-          wave_sync();
           const uint32_t nrec = min(total - rb, kRecMax);
           for (uint32_t q0 = 0; q0 < nrec; q0 += 64) {
             bool keep = q0 + lane < nrec;
-            const uint32_t i = rec[keep ? q0 + lane : 0u];
+            const uint32_t i = ALL ? (keep ? rb + q0 + lane : 0u) : rec[keep ? q0 + lane : 0u];
             const uint32_t E0 = cell[i], E1 = cell[i + 1];
             const double2 sf = sh.lut.small_f[sh.lut.lut225[i + o225] | sh.lut.lut49[i + o49]];
             const uint64_t x = x0 + i;
@@ -588,12 +601,35 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
             const uint64_t khi = __builtin_bit_cast(uint64_t, __builtin_fmax(q0d, q1d)) & kMant;
             if (lower)
               keep = keep && may_pair(x, __builtin_bit_cast(uint64_t, q0d) & kMant, __builtin_bit_cast(uint64_t, q1d) & kMant, qb);
-            if (P.pfilter) {
-              const uint64_t ph = pass_hash(klo, khi, grp);
-              keep = keep && ph >= P.ph_lo && ph < P.ph_hi;
+            if constexpr (FILTER) {
+              keep = keep && pass_hash(klo, khi, grp) - P.ph_lo < P.ph_len;
+              // The pass's records go behind those that wait (the others to the
+              // remaining lanes): two radicals below 2^42 and a place below 2^10.
+              const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+              const uint32_t rank = rank_in(m), have = held + static_cast<uint32_t>(__popcll(m));
+              const int to = static_cast<int>(((keep ? held + rank : have + lane - rank) & 63u) * 4u);
+              const uint32_t w0 = __builtin_amdgcn_ds_permute(to, static_cast<int>(klo));
+              const uint32_t w1 = __builtin_amdgcn_ds_permute(to, static_cast<int>(khi));
+              const uint32_t w2 = __builtin_amdgcn_ds_permute(
+                  to, static_cast<int>(static_cast<uint32_t>(klo >> 32) | static_cast<uint32_t>(khi >> 32) << 10 | i << 20));
+              if (lane >= held) {
+                h0 = w0;
+                h1 = w1;
+                h2 = w2;
+              }
+              held = have;
+              const bool last = rb + q0 + 64 >= total;
+              while (held >= 64 || (last && held)) {
+                put(h0 | static_cast<uint64_t>(h2 & 1023u) << 32, h1 | static_cast<uint64_t>(h2 >> 10 & 1023u) << 32, h2 >> 20,
+                    lane < held);
+                h0 = w0;  // (those past the 64th, in the first lanes)
+                h1 = w1;
+                h2 = w2;
+                held = held > 64 ? held - 64 : 0;
+              }
+            } else {
+              put(klo, khi, i, keep);
             }
-            const uint64_t h = key64(klo, khi, grp);
-            put_words(sh, P, keep, static_cast<uint32_t>(h) & ((1u << P.b1bits) - 1u), l1_word(h, P.kl_mask, P.li_bits, li + i));
           }
           wave_sync();
         }

@@ -1396,3 +1396,27 @@ def test_large_search_with_masked_fingerprints(ctx, keep):
     assert got == theorem1_pairs(1 << 36)
     assert st["l2_entry_bytes"] == 12 and st["retries"] == 0
     assert st["candidates"] == st["pairs"] + st["false_candidates"]
+
+
+@pytest.mark.parametrize("prune,passes,a,length", [
+    (0, 1, 1, 8193), (0, 2, 1, 8193), (0, 3, 36, 70001), (0, 7, (1 << 32) - 40000, 81921), (0, 64, 5, 30011),
+    (1, 3, 1, 70001), (1, 7, (1 << 40) - 5, (1 << 18) + 1025), (1, 64, 1, 20001)])
+def test_records_of_a_pass(ctx, prune, passes, a, length):
+    """The sieve's forms for one pass of several and for every integer kept: all entries
+    of all passes, and with few fingerprint bits the pairs of equal keys among each
+    pass's (lanes that wait for a full wave lose, repeat or mix none)."""
+    b = a + length
+    say(f"passes={passes} prune={prune} [{a}, {b})")
+    options = (("small_max", 0, 8192), ("fp_bits", 12, 0), ("prune", prune, 1), ("passes", passes, 0))
+    for name, value, _ in options:
+        ctx.set_option(name, value)
+    try:
+        got, st = ctx.search_range(a, b), ctx.stats()
+    finally:
+        for name, _, default in options:
+            ctx.set_option(name, default)
+    assert got == oracle.search_range(a, b)
+    keys, n = join_model.group_keys(oracle.radicals(a, b + 1), a, b, 0, st["b1_bits"], passes, 12, prune=bool(prune))
+    assert st["passes"] == passes and st["retries"] == 0
+    assert st["entries"] == st["joined"] == n
+    assert st["candidates"] == join_model.candidates(keys)
