@@ -1420,3 +1420,21 @@ def test_records_of_a_pass(ctx, prune, passes, a, length):
     assert st["passes"] == passes and st["retries"] == 0
     assert st["entries"] == st["joined"] == n
     assert st["candidates"] == join_model.candidates(keys)
+
+
+@pytest.mark.parametrize("N", [20011, (1 << 20) + 1, 1 << 24])
+@pytest.mark.parametrize("prune", [1, 0])
+def test_forced_fan_out_with_few_words_a_region(ctx, N, prune):
+    """2^10 first-level buckets of short ranges, sieved by fewer workgroups than the chip
+    has: every kept integer is joined and the pairs are Theorem 1's."""
+    options = (("b1_bits", 10, 0), ("b2_bits", 1, 0), ("prune", prune, 1))
+    for name, value, _ in options:
+        ctx.set_option(name, value)
+    try:
+        got, st = ctx.search(N), ctx.stats()
+    finally:
+        for name, _, default in options:
+            ctx.set_option(name, default)
+    assert got == theorem1_pairs(N)
+    assert st["b1_bits"] == 10 and st["retries"] == 0
+    assert st["entries"] == st["joined"] == (member_count(N) if prune else N)
