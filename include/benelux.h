@@ -180,13 +180,13 @@ double bx_now(void);
 
 /* Autotuner.  Times the batched search of the queries [a[i], b[i]) (q >= 1;
  * one query [1, N+1) stands for a plain search) under every combination of
- * sieve tile {2048, 8192}, segment length {2^15 .. 2^19} and second-level group
- * {2, 4, 8}, then, with the fastest of those, every small-query cutoff
+ * segment length {2^15 .. 2^19} and second-level group {2, 4, 8}, then, with
+ * the fastest of those, every small-query cutoff
  * {0, 1024, 2048, 4096, 8192} and workgroup size {256, 512, 1024} of that
  * class; `reps` timed runs per setting after one warm-up.  Keeps the fastest,
  * applies it to ctx and, when path is not NULL, writes it as a one-line JSON
- * object (arch, tile, seg_len, group, small_max, small_block, ms).  Results of
- * every run are checked
+ * object (arch, tile, seg_len, group, small_max, small_block, ms; the tile is the
+ * context's, which searches do not use).  Results of every run are checked
  * to be identical.  Errors as bx_search_batch, plus BX_EDEVICE when a file
  * cannot be written and BX_EINTERNAL when two settings disagree. */
 int bx_autotune(bx_ctx* ctx, const uint64_t* a, const uint64_t* b, size_t q, int reps, const char* path);

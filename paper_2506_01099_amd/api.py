@@ -90,7 +90,7 @@ class Benelux:
         }
 
     def autotune(self, a, b, reps=1, path=None):
-        """Sweep tile / segment length / group on the queries [a[i], b[i]); keep the fastest."""
+        """Sweep segment length / group / small class on the queries [a[i], b[i]); keep the fastest."""
         a = np.ascontiguousarray(a, dtype=np.uint64)
         b = np.ascontiguousarray(b, dtype=np.uint64)
         P64 = ctypes.POINTER(ctypes.c_uint64)

@@ -2369,10 +2369,11 @@ int tune_one(bx_ctx* c, const uint64_t* a, const uint64_t* b, size_t q, int reps
 int bx_autotune(bx_ctx* c, const uint64_t* a, const uint64_t* b, size_t q, int reps, const char* path) {
   if (!c || !a || !b || q == 0 || reps < 1) return fail(BX_EINVAL, "bad autotune arguments");
   if (q > kMaxQueries) return fail(BX_EINVAL, "at most 32768 queries per batch");
-  const int saved_tile = c->tile, saved_group = c->force_group, saved_sblock = c->small_block;
+  // (Searches do not use the radical sieve's tile: it stays as it is.)
+  const int tile = c->tile, saved_group = c->force_group, saved_sblock = c->small_block;
   const uint32_t saved_seg = c->seg_len, saved_smax = c->small_max;
   struct Best {
-    int tile = kTileSmall, group = 8;
+    int group = 8;
     uint32_t seg = kDefaultSegLen;
     uint32_t small_max = kSmallMaxLen;
     int small_block = 1024;
@@ -2381,48 +2382,45 @@ int bx_autotune(bx_ctx* c, const uint64_t* a, const uint64_t* b, size_t q, int r
   std::vector<OutPair> ref;
   bool have_ref = false;
   int rc = BX_OK;
-  auto set = [&](int tile, uint32_t seg, int group, uint32_t smax, int sblock) {
+  auto set = [&](uint32_t seg, int group, uint32_t smax, int sblock) {
     std::lock_guard<std::mutex> lk(c->mu);
-    c->tile = tile;
     c->seg_len = seg;
     c->force_group = group;
     c->small_max = smax;
     c->small_block = sblock;
   };
   // The passes' shape first, with the small-query class at its default ...
-  for (int tile : {kTileSmall, kTileLarge}) {
-    for (uint32_t seg : {1u << 15, 1u << 16, 1u << 17, 1u << 18, 1u << 19}) {
-      for (int group : {2, 4, 8}) {
-        if (rc != BX_OK) break;
-        set(tile, seg, group, saved_smax, saved_sblock);
-        double t = 0.0;
-        rc = tune_one(c, a, b, q, reps, &ref, &have_ref, &t);
-        if (rc == BX_OK && t < best.ms) best = Best{tile, group, seg, saved_smax, saved_sblock, t};
-      }
+  for (uint32_t seg : {1u << 15, 1u << 16, 1u << 17, 1u << 18, 1u << 19}) {
+    for (int group : {2, 4, 8}) {
+      if (rc != BX_OK) break;
+      set(seg, group, saved_smax, saved_sblock);
+      double t = 0.0;
+      rc = tune_one(c, a, b, q, reps, &ref, &have_ref, &t);
+      if (rc == BX_OK && t < best.ms) best = Best{group, seg, saved_smax, saved_sblock, t};
     }
   }
   // ... then the class's cutoff and workgroup size with that shape.
   for (uint32_t smax : {0u, 1024u, 2048u, 4096u, 8192u}) {
     for (int sblock : {256, 512, 1024}) {
       if (rc != BX_OK || (smax == 0 && sblock != 1024)) continue;
-      set(best.tile, best.seg, best.group, smax, sblock);
+      set(best.seg, best.group, smax, sblock);
       double t = 0.0;
       rc = tune_one(c, a, b, q, reps, &ref, &have_ref, &t);
-      if (rc == BX_OK && t < best.ms) best = Best{best.tile, best.group, best.seg, smax, sblock, t};
+      if (rc == BX_OK && t < best.ms) best = Best{best.group, best.seg, smax, sblock, t};
     }
   }
   if (rc != BX_OK) {
-    set(saved_tile, saved_seg, saved_group, saved_smax, saved_sblock);
+    set(saved_seg, saved_group, saved_smax, saved_sblock);
     return rc;
   }
-  set(best.tile, best.seg, best.group, best.small_max, best.small_block);
+  set(best.seg, best.group, best.small_max, best.small_block);
   if (path) {
     FILE* f = std::fopen(path, "w");
     if (!f) return fail(BX_EDEVICE, std::string("cannot write ") + path);
     std::fprintf(f,
                  "{\"arch\": \"%s\", \"tile\": %d, \"seg_len\": %u, \"group\": %d, \"small_max\": %u, "
                  "\"small_block\": %d, \"ms\": %.3f}\n",
-                 c->arch.c_str(), best.tile, best.seg, best.group, best.small_max, best.small_block, best.ms);
+                 c->arch.c_str(), tile, best.seg, best.group, best.small_max, best.small_block, best.ms);
     std::fclose(f);
   }
   return BX_OK;

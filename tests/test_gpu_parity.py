@@ -1438,3 +1438,20 @@ def test_forced_fan_out_with_few_words_a_region(ctx, N, prune):
     assert got == theorem1_pairs(N)
     assert st["b1_bits"] == 10 and st["retries"] == 0
     assert st["entries"] == st["joined"] == (member_count(N) if prune else N)
+
+
+@pytest.mark.parametrize("tile", [2048, 8192])
+def test_autotune_leaves_the_radical_tile(ctx, tmp_path, tile):
+    """The autotuner times searches, which do not use the radical sieve's tile: neither
+    its file nor the context gets another one by the noise of those times."""
+    from paper_2506_01099_amd import Benelux
+    from paper_2506_01099_amd.inputs import planted_queries
+
+    a, b = planted_queries()
+    path = tmp_path / "tune.json"
+    with Benelux(device=0) as t:
+        t.set_option("tile", tile)
+        t.autotune(a, b, reps=1, path=path)
+        t.radical_segment(1, 10000)
+        t.search(1 << 14)
+        assert f'"tile": {tile},' in path.read_text() and t.stats()["tile"] == tile
