@@ -45,8 +45,8 @@ int fail(int code, const std::string& msg) {
   } while (0)
 
 // Two shapes of the radical sieve: LDS tiles of 2048 values with 512 threads or
-// of 8192 values with 1024 threads (two workgroups per CU; eight values per
-// thread between barriers, the faster shape).
+// of 8192 values with 1024 threads (eight values per thread between barriers,
+// the faster shape).
 constexpr int kTileSmall = 2048, kTileLarge = 8192;
 constexpr int kTileDefault = kTileLarge;
 constexpr int kVerifyGrid = 2048;
@@ -511,7 +511,7 @@ int make_plan(bx_ctx* c, uint64_t n_keys, uint64_t n_expect, uint64_t share, uin
   return fail(BX_ENOMEM, "HBM budget too small for the search");
 }
 
-// Radical-sieve segments of a range: two workgroups per CU and tile shape.
+// Radical-sieve segments of a range: two for every CU.
 uint32_t rad_seg_len(const bx_ctx* c, uint64_t n) {
   return fit_seg_len(n, 2ull * static_cast<uint64_t>(std::max(1, c->n_cu)), c->seg_len, kTileLarge);
 }
@@ -822,8 +822,9 @@ void launch_sieve(const bx_ctx* c, const SieveParams& P, uint64_t n, uint32_t gr
 #undef BX_SIEVE_LAUNCH
 }
 
-// Radical-sieve workgroups per CU (LDS bound).
-uint32_t sieve_wg_per_cu(const bx_ctx* c) { return c->tile == kTileLarge ? 1u : 2u; }
+// Radical-sieve workgroups at most: two for every CU (one after the other) with
+// the large tile, four (side by side) with the small one.
+uint64_t rad_wgs(const bx_ctx* c) { return (c->tile == kTileLarge ? 2ull : 4ull) * static_cast<uint64_t>(c->n_cu); }
 
 // One search: plan, buffers and launch shapes.
 struct Job {
@@ -1355,7 +1356,7 @@ int radicals_into(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t* dev_out, hipStr
   int rc;
   if ((rc = stage_segs(c, s)) != BX_OK) return rc;
   if ((rc = ensure(c, c->counters, sizeof(Counters))) != BX_OK) return rc;
-  const uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>(s.n_segs, 2ull * sieve_wg_per_cu(c) * c->n_cu));
+  const uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>(s.n_segs, rad_wgs(c)));
   if ((rc = ensure(c, c->spill, static_cast<size_t>(grid) * spill_cap_of(c) * 8)) != BX_OK) return rc;
   if ((rc = enqueue_begin(c, s, 0, st, clear_flags)) != BX_OK) return rc;
   SieveParams P = base_sieve_params(c, s);
@@ -2047,8 +2048,7 @@ int bx_radical_segment_dev_noalloc(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t
   uint64_t* pref = reinterpret_cast<uint64_t*>(na->ptr + kNaPrefOff);
   const uint32_t seg_len = rad_seg_len(c, hi - lo);
   const uint64_t n_segs = (hi - lo + seg_len - 1) / seg_len;
-  const uint32_t grid = static_cast<uint32_t>(
-      std::min<uint64_t>({n_segs, kNaGrid, 2ull * sieve_wg_per_cu(c) * static_cast<uint64_t>(c->n_cu)}));
+  const uint32_t grid = static_cast<uint32_t>(std::min<uint64_t>({n_segs, kNaGrid, rad_wgs(c)}));
   // The counters start at zero, the query table is written from kernel arguments.
   BeginParams B;
   std::memset(&B, 0, sizeof(B));

@@ -152,14 +152,16 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // Bound by its writes: 2e8 radicals (1.6 GB) take 0.18 ms without them, and a
-// fill alone 0.24.  Two workgroups of 1024 threads share a CU (64 registers; with
-// 66 only one did, 0.45 ms), one writing while the other divides; a thread
-// reads its cells together, and goes on to the next tile without a barrier after
-// its writes, which of a large output go past the caches (PAST): 0.372 -> 0.346 ms.
+// fill alone 0.24.  A thread reads its cells together, and goes on to the next
+// tile without a barrier after its writes, which of a large output go past the
+// caches (PAST).  With the large tile one workgroup of 1024 threads has a CU to
+// itself: two would share it at 64 registers, but then 60 bytes a thread go to
+// scratch, and the writes of 2e8 radicals at 2^40 take 0.354 ms instead of
+// 0.317, those of 2^28 at 2^32 0.445 instead of 0.394.
 // (Segments twice as long, for half the looks at the large powers, measured
-// 0.354; 16-byte writes the same as 8-byte ones.)
+// slower; 16-byte writes the same as 8-byte ones.)
 template <int T, int BLOCK, bool PAST>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void k_sieve(SieveParams P) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T >= 8192 ? 4 : 8))) void k_sieve(SieveParams P) {
   constexpr uint32_t kHitCap = hit_cap<T>();
   static_assert(T % BLOCK == 0 && T <= 65536, "tile shape");
   constexpr int ITER = T / BLOCK;                                     // keys per thread per tile
