@@ -1256,9 +1256,9 @@ int run_passes_graph(bx_ctx* c, Job& j, hipStream_t st, std::vector<OutPair>* re
   // and every buffer address the graph's kernels use.  What a call's queries
   // are is read from the staging buffer by each replay (Segs::staged).
   std::snprintf(key, sizeof(key),
-                "%u %llu %u %u %u %u %d %llu %u %d %u %u %d %u %d %d %llx %u %d %zu %d %u %llx %p %p %p %p %p %p %p %p %p %p %p %p %p %p",
+                "%u %llu %u %u %u %u %d %llu %u %u %d %u %u %d %u %d %d %llx %u %d %zu %d %u %llx %p %p %p %p %p %p %p %p %p %p %p %p %p %p",
                 j.plan.passes, static_cast<unsigned long long>(j.plan.cap1), j.plan.cap2, j.plan.b1bits, j.plan.b2bits,
-                j.G, static_cast<int>(j.plan.direct), static_cast<unsigned long long>(j.s->n_segs), static_cast<uint32_t>(j.s->q.size()), j.batch,
+                j.G, static_cast<int>(j.plan.direct), static_cast<unsigned long long>(j.s->n_segs), j.sieve_grid, static_cast<uint32_t>(j.s->q.size()), j.batch,
                 j.kinds, c->third_off, c->tile, j.s->seg_len, c->prune, c->join_sort,
                 static_cast<unsigned long long>(c->fp_mask), c->small_max, c->small_block, j.s->small.size(),
                 static_cast<int>(j.compact), j.wl_bits, static_cast<unsigned long long>(j.low_mask), c->l1.p,

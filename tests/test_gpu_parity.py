@@ -1455,3 +1455,19 @@ def test_autotune_leaves_the_radical_tile(ctx, tmp_path, tile):
         t.radical_segment(1, 10000)
         t.search(1 << 14)
         assert f'"tile": {tile},' in path.read_text() and t.stats()["tile"] == tile
+
+
+def test_batches_with_a_forced_fan_out(ctx):
+    """Batches of unlike lengths under a forced first fan-out, which sets the number of
+    sieve workgroups by their length: graphs are replayed for the same number only."""
+    ctx.set_option("b1_bits", 10)
+    ctx.set_option("b2_bits", 1)
+    try:
+        for n in (3 * 10**6, 14 * 10**6, 3 * 10**6, 10 * 10**6, 14 * 10**6, 9 * 10**6):
+            lo = np.array([1, 7], dtype=np.uint64)
+            got, st = ctx.search_batch(lo, lo + np.uint64(n)), ctx.stats()
+            assert got == [[p for p in theorem1_pairs(a + n - 1) if p[0] >= a] for a in (1, 7)]
+            assert st["entries"] == st["joined"] and st["b1_bits"] == 10
+    finally:
+        ctx.set_option("b1_bits", 0)
+        ctx.set_option("b2_bits", 0)
