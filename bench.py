@@ -32,7 +32,7 @@ ENTRY_BYTES = 12
 FIRST_LEVEL_BYTES = 8  # a word of the sieve's
 CALIB_BYTES = 4 << 30
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_plain_2p36.json")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2506_01099_amd", "csrc", f) for f in ("bx_kernels.h", "bx_device.h", "bx_keysieve.h")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2506_01099_amd", "csrc", f) for f in ("bx_kernels.h", "bx_device.h", "bx_segments.h", "bx_keysieve.h")]
 
 
 def log(msg):

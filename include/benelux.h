@@ -224,7 +224,9 @@ int bx_get_stats(bx_ctx* ctx, bx_stats* out);
 /* Options (name = value); unknown names are BX_EINVAL.
  *   "passes"       force the number of hash passes (any count, 0 = plan)
  *   "seg_len"      longest sieve segment (multiple of the tile, 0 = default)
- *   "timing"       1 = record HIP events per kernel where they are used (default 1)
+ *   "timing"       1 = report kernel_ms (default 1), 0 = leave it zero: the radical
+ *                  calls and the schedules 1 and 2 then record no HIP events (the
+ *                  kernels of a search note the device's clock either way)
  *   "b1_bits"      force the first partition fan-out (0 = plan)
  *   "b2_bits"      force the second partition fan-out, <= 11 (0 = plan)
  *   "group"        first-level buckets per second-level launch (1, 2, 4, 8; 0 = 8)

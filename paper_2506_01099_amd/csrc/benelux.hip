@@ -804,7 +804,7 @@ int check_query(const bx_ctx* c, uint64_t a, uint64_t b, uint32_t kinds) {
 }
 
 // The radical sieve, of n integers.  An output that no cache holds is written
-// past them (2e8 radicals 0.372 -> 0.346 ms); a smaller one is left where its
+// past them (2e8 radicals at 2^40 0.345 -> 0.315 ms); a smaller one is left where its
 // reader finds it (3e5 to the host: 0.18 ms either way).
 void launch_sieve(const bx_ctx* c, const SieveParams& P, uint64_t n, uint32_t grid, hipStream_t st) {
   const bool past = n >= kPastCaches;
@@ -2032,7 +2032,7 @@ int bx_radical_segment_dev_noalloc(bx_ctx* c, uint64_t lo, uint64_t hi, uint64_t
       c->pp.begin());
   const double expect = static_cast<double>(c->seg_len) *
                         (c->cum_inv_q[std::max<size_t>(top, first_sparse)] - c->cum_inv_q[first_sparse]);
-  const double room = static_cast<double>(hit_cap<kTileLarge>() + kNaSpill);
+  const double room = static_cast<double>(kHitCap + kNaSpill);
   if (2.0 * expect > room)
     return fail(BX_ENOMEM, "segment length " + std::to_string(c->seg_len) + " needs about " +
                                std::to_string(static_cast<uint64_t>(expect)) +

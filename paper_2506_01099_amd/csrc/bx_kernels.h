@@ -21,11 +21,10 @@
 
 namespace bx {
 
-// Sparse-hit list held in LDS per segment (about 850 hits per 2^18 values
-// with the 8192 tile, 2050 with the 2048 tile); the excess goes to a global
-// spill list.
-template <int T>
-constexpr int hit_cap() { return 1024; }
+// Sparse hits held in LDS per segment of the radical sieve: the 8192 tile has
+// about 850 per 2^18 values; of the 2050 of the 2048 tile the excess goes to a
+// list in device memory.
+constexpr uint32_t kHitCap = 1024;
 constexpr int kB1Max = 1024;       // first partition fan-out
 constexpr int kB2Max = 2048;       // second partition fan-out
 constexpr int kPartChunk = 8192;   // entries per workgroup in k_partition
@@ -53,7 +52,7 @@ struct SieveParams {
 template <int T, int BLOCK>
 struct SieveSh {
   uint64_t tile[T];
-  uint64_t hits[hit_cap<T>()];
+  uint64_t hits[kHitCap];
   uint32_t dres[kDenseMax], doff[kDenseMax], dq[kDenseMax], dtq[kDenseMax];
   uint32_t hit_n;
 };
@@ -162,7 +161,6 @@ __device__ __forceinline__ void wave_sync() {
 // slower; 16-byte writes the same as 8-byte ones.)
 template <int T, int BLOCK, bool PAST>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(T >= 8192 ? 4 : 8))) void k_sieve(SieveParams P) {
-  constexpr uint32_t kHitCap = hit_cap<T>();
   static_assert(T % BLOCK == 0 && T <= 65536, "tile shape");
   constexpr int ITER = T / BLOCK;                                     // keys per thread per tile
   constexpr int SLOTS = (dense_slot_cap(T) + BLOCK - 1) / BLOCK;      // dense slots per thread
@@ -350,8 +348,9 @@ struct PartParams {
 // before they are written back.  The bucket's chunks are split into nbw
 // contiguous ranges, one per workgroup; the next chunk is loaded into
 // registers while the current one is scattered.  Bound by memory: 8 bytes read
-// and 8 written per entry, at 3.6 TB/s of the 4.4 a large copy takes on this
-// card (2^36: 36.4 -> 32 ms with 8-byte words read instead of 12-byte entries).
+// and 8 written per entry, at 3.2 to 3.6 TB/s (by the distance of the partitions
+// in memory) of the 4.4 a large copy takes on this card (2^36: 36 to 42 ms, by
+// process, -> 33 to 37 with 8-byte words read instead of 12-byte entries).
 template <int BLOCK, bool COMPACT>
 __global__ __launch_bounds__(BLOCK) void k_partition(PartParams P) {
   constexpr int EPT = kPartChunk / BLOCK;
@@ -672,7 +671,7 @@ __device__ __forceinline__ bool may_be_equal(const JoinParams& P, uint64_t x, ui
 // the workgroup gathers its bucket's words from the regions into LDS (2^20
 // integers: a partition launch of 15 us less).
 //
-// Bound by memory and LDS round trips: 58 GB of words at 3.2 TB/s at 2^36.
+// Bound by memory and LDS round trips: 58 GB of words at 3.0 to 3.2 TB/s at 2^36.
 template <int BLOCK, bool DIRECT>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DIRECT ? 4 : 8))) void k_join_c(JoinParams P) {
   constexpr int EPT = kJoinCap / BLOCK;

@@ -16,7 +16,7 @@
 // kept list are private to it, so no barrier falls inside a subtile (LDS
 // accesses of one wave execute in order).  The words of the kept x leave
 // through per-bucket queues in LDS, from which any wave writes out a run as
-// soon as the run is claimed, without a barrier too (KeyQueue).  The workgroup
+// soon as the run is claimed, without a barrier too (put_words).  The workgroup
 // meets only to list the hits of the powers above 361: per chunk of 2^18
 // integers those of the powers above 2^16, per block of 2^17 all of them.
 #pragma once
@@ -75,7 +75,7 @@ struct KeyParams {
   int batch;
   uint32_t ph_lo, ph_len;  // FILTER: keep x only when pass_hash(key) is in [ph_lo, ph_lo + ph_len)
   uint32_t b1bits;   // first-level bucket = low b1bits bits of key64
-  uint32_t li_bits;  // words: L1Word
+  uint32_t li_bits;  // of a word (l1_word)
   uint64_t kl_mask;
   uint32_t W;      // workgroups
   uint64_t* l1;    // region (w, b) of bucket b written by workgroup w: l1 + (w * B1 + b) * cap1
@@ -239,8 +239,8 @@ __device__ __forceinline__ void put_words(KeySh& sh, const KeyParams& P, bool ke
 
 // One workgroup per CU walks its segments (s mod W).
 //
-// Bound by instruction issue: 33 VALU lane-operations per integer, issued in
-// 72% of the cycles.  (A tile of 64-bit radicals divided in place by
+// Bound by instruction issue: 30 VALU lane-operations per integer, issued in
+// 75% of the cycles.  (A tile of 64-bit radicals divided in place by
 // compare-and-swap took 42 and 45%, with three barriers per 8192 integers.)
 // Of a workgroup's cycles at 2^40, 74% are rows of subtiles, 14% the look at
 // the large powers (in single precision first: in double it took twice that),
@@ -248,7 +248,7 @@ __device__ __forceinline__ void put_words(KeySh& sh, const KeyParams& P, bool ke
 // high priority so that they reach these at nearly one time.  A subtile of 512
 // took 70% longer (latency); a sorted stage with coalesced flushes instead of
 // the queues 40%.
-// 2^36 integers 158 -> 77.5 ms, 2^32 9.55 -> 4.9 ms, 2^28 at 2^40 0.71 -> 0.30.
+// 2^36 integers 158 -> 76.7 ms, 2^32 9.55 -> 4.8 ms, 2^28 at 2^40 0.71 -> 0.29.
 //
 // FILTER: one of several passes.  Every record's radicals are made, and those of
 // the pass wait in lanes until 64 are together, so that the key and the queues
@@ -586,8 +586,11 @@ __global__ __launch_bounds__(kKeyBlock) void k_sieve_keys(KeyParams P) {
             const double d0 = static_cast<double>(E0) * sf.x * (odd ? 1.0 : low);
             const double d1 = static_cast<double>(E1) * sf.y * (odd ? low : 1.0);
             // rad = x / e, an integer below 2^42: one Newton step on the
-            // hardware's reciprocal of both e's product (2^-46 relative),
-            // rounded to the integer by adding 2^52.
+            // hardware's reciprocal of both e's product, rounded to the integer
+            // by adding 2^52.  The e's are exact (each divides its integer); the
+            // instruction is specified to 2^29 ulp (2^-23 relative), so the step
+            // leaves 2^-46 and the four roundings 2^-51: rad is off by less than
+            // 1/8 before it is rounded.
             const double dd = d0 * d1;
             double ri = __builtin_amdgcn_rcp(dd);
             ri = __builtin_fma(ri, __builtin_fma(-dd, ri, 1.0), ri);
